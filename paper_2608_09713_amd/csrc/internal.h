@@ -237,7 +237,7 @@ void light_numeric(const LightArgs& a, hipStream_t s);
 // most kFusedEntries entries and kFusedProducts off-diagonal products.
 constexpr int kFusedEntries = 256;
 constexpr int kFusedProducts = 512;
-constexpr int kFusedRows = 32;
+constexpr int kFusedRows = 64;
 struct FusedArgs {
     int64_t m = 0;
     const int64_t* rp = nullptr;

@@ -2,56 +2,50 @@
 //
 // Work unit: a chunk of R consecutive rows per wavefront.  Each wavefront
 // works alone in its own slice of LDS (no workgroup barriers), in batches of
-// consecutive light rows that fit the LDS budget:
+// consecutive light rows of at most kCap products:
 //
-//   1. partner runs of the batch's entries (written by the column-index
-//      build, read in entry order; the next batch's runs are loaded while
-//      this batch's keys are in flight);
-//   2. products flattened over the entries (the owner entry of every product
-//      comes from a scatter of run starts and a max-scan), every key loaded
-//      in one round;
-//   3. ordered buckets per row (bucket order = column order, about one
-//      product per bucket): count, scan, scatter; each small bucket is sorted
-//      by (column, product index) in one lane's registers and its equal
-//      columns merged (terms summed in product order); the rare large bucket
-//      is resolved by the whole wavefront (leader = first product of a
-//      column, its rank among the bucket's distinct columns, its value);
-//   4. the row is written at its staging slot (row upper bound = products +
-//      diagonal, known from the column index), its exact length recorded.
+//   1. the batch's entries, 64 at a time: the partner run of every entry
+//      (written by the column-index build), a prefix sum of the run lengths,
+//      and at every run's first product slot the run's start less that slot;
+//   2. the batch's rows listed by size class (8, 16, 32 or 64 lanes, two
+//      registers, more), so that one wavefront register holds several short
+//      rows side by side;
+//   3. per register: every lane is one product; the nearest marked slot at or
+//      below its own gives its position in the column index (one ballot), all
+//      keys are loaded together, and every row is sorted by (column, product
+//      index) in registers (wave_sort.h), rows of more than 128 products 64
+//      at a time with merges in LDS.  The first product of every column
+//      takes the column's terms in product order; with no equal columns, the
+//      usual case, each lane is one output, written at its place in the row;
+//   4. diagonals and exact lengths, one row per lane.
 //
 // A scan of the exact lengths gives the row pointers and a streaming copy
 // moves the rows into place, so no row waits for the lengths of earlier
 // rows.  Rows with too many entries or products ("heavy") are left to the
 // dense-tile kernel.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 #include "lookup.h"
+#include "wave_sort.h"
 
 namespace spsyrk {
 namespace {
 
-constexpr int kFE = kFusedEntries;   // entries per batch
-constexpr int kFP = kFusedProducts;  // products per batch
-constexpr int kFR = kFusedRows;      // rows per chunk (upper limit)
-constexpr int kFB = kFP + kFR;       // buckets per batch
+constexpr int kFE = kFusedEntries;   // entries of a light row
+constexpr int kFP = kFusedProducts;  // products of a light row
+constexpr int kFR = kFusedRows;      // rows per chunk (upper limit: one per lane)
+constexpr int kCap = 1024;           // product slots per batch
 constexpr int kWavesF = 2;           // wavefronts per workgroup
 constexpr int kDealtBelow = 16;      // chunks per launched wavefront below which chunks are dealt out
-constexpr int kRunRegs = kFE / kWave;  // partner runs per lane held in registers
-constexpr int kSmall = 8;              // buckets up to this size are merged in registers
-constexpr int kTBits = 9;              // product index bits in s_t (row above them)
-constexpr uint32_t kTMask = (1u << kTBits) - 1u;
-// Output tag of a slot once its bucket is merged: the slot's output index in
-// the bucket (low kKBits bits) and, for a small bucket, the number of terms
-// merged into it (above them; 0 when the value is already final), or 0xffff
-// for a slot that writes nothing.
-constexpr int kKBits = 9;
-constexpr uint32_t kKMask = (1u << kKBits) - 1u;
-constexpr uint32_t kNoOut = 0xffffu;
-static_assert(kFP <= (1 << kKBits), "an output index must fit kKBits");
-static_assert(((kSmall + 1) << kKBits) < int(kNoOut), "a tag must fit 16 bits");
-static_assert(kFP <= (1 << kTBits), "product index must fit kTBits");
-static_assert(kFR <= (1 << (16 - kTBits)), "chunk row must fit above the product index");
-
+constexpr int kOrdBits = 9;          // product index bits of a 32-bit plus-times key (column above them)
+constexpr uint32_t kNoRun = 0x80000000u;  // a slot where no run starts (starts are below 2^31, slots below kCap)
+static_assert(kFR <= kWave, "one row per lane");
+static_assert(kFP <= kCap, "a row fits a batch");
+static_assert(kFP <= (1 << kOrdBits), "a product index must fit kOrdBits");
+static_assert(kCap <= (1 << 11) && kFP <= (1 << 10) && kFR <= (1 << 6), "fields of a listed row");
+static_assert(kFR * kFE <= (1 << 16), "an entry's index in its batch must fit 16 bits");
 
 __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -59,811 +53,575 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int SR>
-struct ItemOf {
-    using T = int32_t;  // unused (count) or |S(j)|, then the Jaccard bits (Jaccard)
-};
-template <>
-struct ItemOf<kF64> {
-    using T = double;
-};
-template <>
-struct ItemOf<kF32> {
-    using T = double;
-};
-
-template <typename Item>
+// (5 KiB: 32 wavefronts per compute unit; with values 9 or 11 KiB: 17 or 14)
+template <bool VAL, typename Key>
 struct WaveLds {
-    int64_t rp[kFR + 1];
-    int64_t rcnt[kFR];        // output entries per row; later the row's first output slot
-    uint16_t rprod[kFR];      // products of light rows (0 for heavy rows)
-    uint16_t rnb[kFR + 1];    // buckets of the row in the current batch
-    uint16_t rbb[kFR + 1];    // first bucket of the row in the current batch
-    uint32_t rscale[kFR];     // bucket of column j: (j * rscale) >> 32 spreads [0, range) evenly
-    uint32_t ent_start[kFE];
-    uint16_t ent_len[kFE];
-    alignas(4) uint8_t ent_row[kFE];
-    int32_t rlen[kFR];        // entries of every row of the batch
-    alignas(16) int16_t owner[kFP];
-    alignas(16) uint16_t ent_poff[kFE + 1];
-    uint32_t s_j[kFP];
-    uint16_t s_t[kFP];
-    uint16_t s_rank[kFP];     // output tag of every slot (see kKBits)
-    uint16_t big[kFP / (kSmall + 1) + 1];  // large buckets of the batch
-    uint32_t nbig;
-    int64_t rbase[kFR];
-    Item s_v[kFP];
-    // per bucket (16 bits: every count and offset is at most kFP + kFR)
-    alignas(16) uint16_t hist[(kFB + 8) & ~7];
-    alignas(16) uint16_t ucnt[kFB + 2];
+    // a long row's keys; without values 32-bit keys take the row's slots of d
+    static constexpr bool kOwnKeys = VAL || sizeof(Key) > 4;
+    Key key[kOwnKeys ? kFP : 1];
+    alignas(16) uint32_t d[kCap];  // start of the run that begins at the slot, less the slot; else kNoRun
+    uint16_t x[VAL ? kCap : 2];    // the run's entry (index in the batch)
+    int64_t out[kFR];              // first output slot of every row
+    uint32_t ord[kFR];             // rows by size class: first slot | products << 11 | row << 21
+    uint16_t cnt[kFR];             // outputs off the diagonal
+    uint16_t len[kFR];             // entries of every light row
 };
-// Two wavefronts' slices must stay within 26880 bytes for six workgroups per
-// compute unit (a few bytes more and only five fit, while the occupancy
-// query still reports six).
-static_assert(sizeof(WaveLds<int32_t>) * kWavesF <= 26880, "LDS slice of the count and Jaccard kernels");
 
-static_assert(kFP + kFR < (1 << 16), "bucket counters are 16 bits");
-
-// atomic add of one to the 16-bit counter h[b] (two counters share a 32-bit
-// LDS word; no counter reaches 2^16); returns the old value
-__device__ inline uint32_t add16(uint16_t* h, uint32_t b) {
-    uint32_t* w = reinterpret_cast<uint32_t*>(h) + (b >> 1);
-    const uint32_t sh = (b & 1u) * 16u;
-    return (atomicAdd(w, 1u << sh) >> sh) & 0xffffu;
-}
-
-// exclusive scan in place of the 16-bit a[0..n) by one wavefront, eight
-// elements per lane on 16-byte LDS words (a is 16-byte aligned and holds n
-// rounded up to eight; elements past n read as zero); returns the total
-__device__ inline uint32_t wave_scan16(uint16_t* a, int n) {
-    const int lane = lane_id();
-    uint32_t carry = 0;
-    for (int base = 0; base < n; base += 8 * kWave) {
-        const int i0 = base + 8 * lane;
-        uint32_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (i0 < n) {
-            const uint4 w = *reinterpret_cast<const uint4*>(a + i0);
-            const uint32_t wd[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                v[2 * k] = i0 + 2 * k < n ? (wd[k] & 0xffffu) : 0u;
-                v[2 * k + 1] = i0 + 2 * k + 1 < n ? (wd[k] >> 16) : 0u;
-            }
-        }
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) sum += v[k];
-        const uint32_t inc = wave_inclusive_scan(sum);
-        uint32_t off = carry + inc - sum;
-        if (i0 < n) {
-            uint32_t od[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t lo16 = off;
-                off += v[2 * k];
-                const uint32_t hi16 = off;
-                off += v[2 * k + 1];
-                od[k] = (lo16 & 0xffffu) | (hi16 << 16);
-            }
-            *reinterpret_cast<uint4*>(a + i0) = make_uint4(od[0], od[1], od[2], od[3]);
-        }
-        carry += __shfl(inc, kWave - 1, kWave);
-    }
-    wave_sync();
-    return carry;
-}
-
-template <int SR, bool LOWER>
+// WIDE: 64-bit sort keys.  Plus-times: column and product index, where both
+// do not fit 32 bits.  Jaccard without packed words: column and the
+// partner's length (packed words are sorted as they are; counts need the
+// column only).
+template <int SR, bool LOWER, bool WIDE>
 struct Chunk {
     using Tr = SrTraits<SR>;
     using In = typename Tr::In;
     using Out = typename Tr::Out;
-    using Item = typename ItemOf<SR>::T;
+    using Key = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
     static constexpr bool kVal = (SR == kF64 || SR == kF32);
+    static constexpr Key kDead = ~Key(0);  // sorts behind every product of its row
 
     const FusedArgs& a;
-    WaveLds<Item>& L;
-    int64_t r0 = 0;
-    int lane;
+    WaveLds<kVal, Key>& L;
+    const int lane;
+    const wsort::Sides sides;
+    const uint64_t upto;  // lanes up to this one
     uint32_t rowmask;
     uint32_t lenmax;  // saturated length in a key (Jaccard keys carrying lengths)
-    int jbits_right;
+    int64_t r0 = 0;
 
-    __device__ Chunk(const FusedArgs& a_, WaveLds<Item>& L_) : a(a_), L(L_) {
-        lane = lane_id();
+    __device__ Chunk(const FusedArgs& a_, WaveLds<kVal, Key>& L_)
+        : a(a_), L(L_), lane(lane_id()), sides(lane), upto((uint64_t(2) << lane) - 1) {
         rowmask = a.cx.rowbits >= 32 ? 0xffffffffu : ((1u << a.cx.rowbits) - 1u);
         lenmax = a.cx.lenbits > 0 ? ((a.cx.lenbits >= 32 ? 0xffffffffu : (1u << a.cx.lenbits) - 1u)) : 0u;
-        jbits_right = bit_width_u64(a.m_right > 1 ? uint64_t(a.m_right - 1) : 0);
     }
 
-    // Issue the loads of the partner runs of the light rows [ra, rb) (entry
-    // lane + kWave * u in rn[u]); they are consumed by the batch's first step.
-    __device__ void fetch_runs(int ra, int rb, uint32_t (&rn)[kRunRegs]) {
-        const int64_t ebase = L.rp[ra];
-        const int ne = int(L.rp[rb] - ebase);
-#pragma unroll
-        for (int u = 0; u < kRunRegs; ++u) {
-            const int x = lane + u * kWave;
-            // (a packed word is decoded where the run is used, so that the
-            // loads stay in flight)
-            rn[u] = x < ne ? a.run.r4[ebase + x] : 0u;
-        }
-    }
-
-    // Partner runs, buckets, merged columns and per-bucket distinct counts
-    // for the light rows [ra, rb), whose runs were fetched into rn.  The
-    // batch's columns stay in LDS, grouped by (row, bucket).  The runs of the
-    // next batch [na, nb) (if na >= 0) are fetched into rn while the batch's
-    // keys are in flight.  Returns the number of products.
-    __device__ int batch(int ra, int rb, uint32_t (&rn)[kRunRegs], int na, int nbx) {
-        const int64_t ebase = L.rp[ra];
-        const int ne = int(L.rp[rb] - ebase);
-        const uint32_t* __restrict__ key = a.cx.key;
-        // row of every entry: every non-empty row marks its first entry, then
-        // a max-scan (four entries per lane, one LDS word)
-        static_assert(kFE == 4 * kWave, "one word of entry rows per lane");
-        reinterpret_cast<uint32_t*>(L.ent_row)[lane] = 0u;
-        wave_sync();
-        if (lane < rb - ra) {
-            const int r = ra + lane;
-            if (L.rp[r + 1] > L.rp[r]) L.ent_row[L.rp[r] - ebase] = uint8_t(r);
-        }
-#pragma unroll
-        for (int u = 0; u < kRunRegs; ++u) {
-            const int x = lane + u * kWave;
-            if (x < ne) {
-                const uint2 r = run_from(a.run, rn[u], ebase + x);
-                const uint32_t len = r.y - r.x;
-                L.ent_start[x] = r.x;
-                L.ent_len[x] = uint16_t(len);
-                L.ent_poff[x] = uint16_t(len);
-            }
-        }
-        wave_sync();
-        {
-            const uint32_t wv = reinterpret_cast<const uint32_t*>(L.ent_row)[lane];
-            const uint32_t m0 = wv & 0xffu, m1 = max(m0, (wv >> 8) & 0xffu);
-            const uint32_t m2 = max(m1, (wv >> 16) & 0xffu), m3 = max(m2, wv >> 24);
-            uint32_t inc = m3;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t o = __shfl_up(inc, d, kWave);
-                if (lane >= d) inc = max(inc, o);
-            }
-            uint32_t before = __shfl_up(inc, 1, kWave);
-            if (lane == 0) before = 0;
-            reinterpret_cast<uint32_t*>(L.ent_row)[lane] = max(before, m0) | (max(before, m1) << 8) |
-                                                           (max(before, m2) << 16) | (max(before, m3) << 24);
-        }
-        wave_sync();
-        const int P = int(wave_scan16(L.ent_poff, ne));
-        if (lane == 0) L.ent_poff[ne] = uint16_t(P);
-        // per-row buckets: one per product (at most one per possible column);
-        // bucket of column j = floor(j * nb / range), monotone in j
-        const int nrb = rb - ra;
-        uint32_t nb = 0;
-        if (lane < nrb) {
-            const int r = ra + lane;
-            L.rlen[r] = int32_t(L.rp[r + 1] - L.rp[r]);
-            const int64_t range = LOWER ? (r0 + r) : a.m_right;
-            uint64_t want = L.rprod[r] > 0 ? L.rprod[r] : 1;
-            if (range > 0 && uint64_t(range) < want) want = uint64_t(range);
-            nb = uint32_t(want);
-            L.rnb[r] = uint16_t(nb);
-            // floor(nb 2^32 / range) rounded down by one more: bucket < nb for
-            // every j < range (the quotient's error is far below one); nb <=
-            // range, so the scale fits 32 bits
-            uint64_t sc = 0;
-            if (range > 0) {
-                sc = uint64_t(ldexp(double(nb), 32) / double(range));
-                sc = sc > 0 ? sc - 1 : 0;
-            }
-            L.rscale[r] = uint32_t(sc);
-        }
-        const uint32_t inc = wave_inclusive_scan(nb);
-        if (lane < nrb) L.rbb[ra + lane] = uint16_t(inc - nb);
-        const uint32_t B = __shfl(inc, kWave - 1, kWave);
-        // bucket counters zeroed eight at a time (every bucket's distinct count
-        // is set when the buckets are sorted by size)
-        for (uint32_t g = lane; 8 * g <= B; g += kWave) reinterpret_cast<uint4*>(L.hist)[g] = make_uint4(0, 0, 0, 0);
-        // owner entry of every product: run starts scattered, then a max-scan
-        // (eight products per lane, one 16-byte LDS word)
-        static_assert(kFP == 8 * kWave, "one 16-byte word of owners per lane");
-        reinterpret_cast<uint4*>(L.owner)[lane] = make_uint4(~0u, ~0u, ~0u, ~0u);
-        wave_sync();
-        for (int x = lane; x < ne; x += kWave)
-            if (L.ent_len[x]) L.owner[L.ent_poff[x]] = int16_t(x);
-        wave_sync();
-        {
-            const uint4 wv = reinterpret_cast<const uint4*>(L.owner)[lane];
-            const uint32_t wd[4] = {wv.x, wv.y, wv.z, wv.w};
-            int o[8];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                o[2 * k] = int(int16_t(wd[k] & 0xffffu));
-                o[2 * k + 1] = int(int16_t(wd[k] >> 16));
-            }
-#pragma unroll
-            for (int k = 1; k < 8; ++k) o[k] = max(o[k], o[k - 1]);
-            int incm = o[7];
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const int u = __shfl_up(incm, d, kWave);
-                if (lane >= d) incm = max(incm, u);
-            }
-            int run = __shfl_up(incm, 1, kWave);
-            if (lane == 0) run = -1;
-            uint32_t od[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                od[k] = (uint32_t(max(o[2 * k], run)) & 0xffffu) | (uint32_t(max(o[2 * k + 1], run)) << 16);
-            reinterpret_cast<uint4*>(L.owner)[lane] = make_uint4(od[0], od[1], od[2], od[3]);
-        }
-        wave_sync();
-        // products: every key (and partner value) of the lane loaded in one round,
-        // kept in registers for both passes
-        constexpr int kPV = kFP / kWave;
-        uint32_t pj[kPV], pb[kPV];
-        Item pv[kPV];
-#pragma unroll
-        for (int v = 0; v < kPV; ++v) {
-            const int t = lane + v * kWave;
-            pj[v] = 0;
-            pb[v] = 0;
-            if (t < P) {
-                const int x = L.owner[t];
-                const uint32_t pos = L.ent_start[x] + uint32_t(t - L.ent_poff[x]);
-                pj[v] = key[pos];
-                if constexpr (SR == kJaccard) {
-                    if (!a.cx.lenbits) pv[v] = static_cast<const int32_t*>(a.cx.val)[pos];
-                } else if constexpr (kVal) {
-                    pv[v] = double(static_cast<const In*>(a.val)[ebase + x]) *
-                            double(static_cast<const In*>(a.cx.val)[pos]);
-                }
-                pb[v] = uint32_t(L.ent_row[x]);
-            }
-        }
-        if (na >= 0) fetch_runs(na, nbx, rn);
-#pragma unroll
-        for (int v = 0; v < kPV; ++v) {
-            const int t = lane + v * kWave;
-            if (t < P) {
-                const uint32_t j = pj[v] & rowmask;
-                if constexpr (SR == kJaccard) {
-                    if (a.cx.lenbits) {
-                        // the partner's length from its key; saturated: from the row pointers
-                        const uint32_t lf = pj[v] >> a.cx.rowbits;
-                        pv[v] = lf < lenmax ? int32_t(lf) : int32_t(a.rp_right[j + 1] - a.rp_right[j]);
-                    }
-                }
-                const int r = int(pb[v]);
-                pj[v] = j;
-                const uint32_t b = L.rbb[r] + __umulhi(j, L.rscale[r]);
-                pb[v] = b | (uint32_t(r) << 16);
-                add16(L.hist, b);
-            }
-        }
-        wave_sync();
-        wave_scan16(L.hist, int(B));
-        // scatter into buckets; hist[b] ends as the end of bucket b.  s_t keeps
-        // the product index and, above it, the row (one row per bucket)
-#pragma unroll
-        for (int v = 0; v < kPV; ++v) {
-            const int t = lane + v * kWave;
-            if (t < P) {
-                const uint32_t q = add16(L.hist, pb[v] & 0xffffu);
-                // (the owner array is free by now: it keeps every slot's bucket)
-                reinterpret_cast<uint16_t*>(L.owner)[q] = uint16_t(pb[v] & 0xffffu);
-                L.s_j[q] = pj[v];
-                L.s_t[q] = uint16_t(uint32_t(t) | ((pb[v] >> 16) << kTBits));
-                if constexpr (SR == kJaccard || kVal) L.s_v[q] = pv[v];
-            }
-        }
-        wave_sync();
-        // Buckets by size: empty and single-product buckets are done at once;
-        // the others are listed by size class so that every class runs with
-        // full lanes.  Small buckets (up to kSmall products), one per lane:
-        // sorted by (column, product index) in registers, equal columns merged
-        // (terms summed in product order); every column's first product keeps
-        // its slot and gets the column's tag in s_rank (term count, index among
-        // the bucket's distinct columns), the others are marked as writing
-        // nothing; ucnt[b] = distinct columns.  Larger buckets go to the cooperative
-        // pass below.  (The entry arrays are free by now and hold the lists.)
-        uint16_t* list2 = reinterpret_cast<uint16_t*>(L.ent_start);       // 2 products
-        uint16_t* list4 = reinterpret_cast<uint16_t*>(L.ent_start) + kFE;  // 3 or 4
-        uint16_t* list8 = L.ent_len;                                       // 5 to 8
-        uint32_t n2 = 0, n4 = 0, n8 = 0, nlarge = 0;  // (wave-uniform list lengths)
-        const uint64_t lt = lanemask_lt();
-        for (uint32_t b0 = 0; b0 < B; b0 += kWave) {
-            const uint32_t b = b0 + lane;
-            uint32_t sz = 0, lo = 0;
-            if (b < B) {
-                lo = b ? L.hist[b - 1] : 0u;
-                sz = L.hist[b] - lo;
-                if (sz == 1) L.s_rank[lo] = uint16_t(1u << kKBits);
-                L.ucnt[b] = sz <= 1 ? sz : 0u;
-            }
-            // wave-aggregated appends
-            const uint64_t m2 = __ballot(sz == 2), m4 = __ballot(sz == 3 || sz == 4);
-            const uint64_t m8 = __ballot(sz > 4 && sz <= uint32_t(kSmall)), mb = __ballot(sz > uint32_t(kSmall));
-            if (sz == 2) list2[n2 + __popcll(m2 & lt)] = uint16_t(b);
-            if (sz == 3 || sz == 4) list4[n4 + __popcll(m4 & lt)] = uint16_t(b);
-            if (sz > 4 && sz <= uint32_t(kSmall)) list8[n8 + __popcll(m8 & lt)] = uint16_t(b);
-            if (sz > uint32_t(kSmall)) L.big[nlarge + __popcll(mb & lt)] = uint16_t(b);
-            n2 += __popcll(m2);
-            n4 += __popcll(m4);
-            n8 += __popcll(m8);
-            nlarge += __popcll(mb);
-        }
-        if (lane == 0) L.nbig = nlarge;
-        wave_sync();
-        for (uint32_t q = lane; q < n2; q += kWave) {
-            const uint32_t b = list2[q];
-            const uint32_t lo = b ? L.hist[b - 1] : 0u;
-            L.ucnt[b] = merge_two(lo);
-        }
-        const bool cols32 = !kVal && a.m_right <= (int64_t(1) << 29);
-        for (uint32_t q = lane; q < n4; q += kWave) {
-            const uint32_t b = list4[q];
-            const uint32_t lo = b ? L.hist[b - 1] : 0u, hi = L.hist[b];
-            L.ucnt[b] = cols32 ? merge_small_cols<kSmall / 2>(lo, hi - lo) : merge_small<kSmall / 2>(lo, hi - lo);
-        }
-        for (uint32_t q = lane; q < n8; q += kWave) {
-            const uint32_t b = list8[q];
-            const uint32_t lo = b ? L.hist[b - 1] : 0u, hi = L.hist[b];
-            L.ucnt[b] = cols32 ? merge_small_cols<kSmall>(lo, hi - lo) : merge_small<kSmall>(lo, hi - lo);
-        }
-        wave_sync();
-        // larger buckets, one at a time by the whole wavefront: leaders (first
-        // product of each column), their rank among the bucket's distinct
-        // columns and their column's value; ucnt[b] = leaders
-        const int nbig = int(L.nbig);
-        for (int g = 0; g < nbig; ++g) {
-            const uint32_t b = L.big[g];
-            const uint32_t lo = b ? L.hist[b - 1] : 0u, hi = L.hist[b];
-            if (hi - lo <= uint32_t(kWave)) {
-                const uint32_t u = merge_wave(lo, hi - lo);
-                if (lane == 0) L.ucnt[b] = u;
-                wave_sync();
-                continue;
-            }
-            for (uint32_t q = lo + lane; q < hi; q += kWave) {
-                const uint32_t j = L.s_j[q];
-                const uint32_t t = L.s_t[q] & kTMask;
-                bool lead = true;
-                for (uint32_t u = lo; u < hi; ++u)
-                    if (L.s_j[u] == j && (L.s_t[u] & kTMask) < t) lead = false;
-                L.s_rank[q] = lead ? 0 : 0xffff;
-            }
-            wave_sync();
-            uint32_t leaders = 0;
-            for (uint32_t q0 = lo; q0 < hi; q0 += kWave) {
-                const uint32_t q = q0 + lane;
-                bool lead = false;
-                Item val = Item(0);
-                uint32_t rank = 0;
-                if (q < hi && L.s_rank[q] == 0) {
-                    lead = true;
-                    const uint32_t j = L.s_j[q];
-                    const uint32_t t = L.s_t[q] & kTMask;
-                    const int r = int(L.s_t[q] >> kTBits);
-                    int32_t cnt = 0;
-                    for (uint32_t u = lo; u < hi; ++u) {
-                        const uint32_t ju = L.s_j[u];
-                        rank += (ju < j && L.s_rank[u] != 0xffff) ? 1u : 0u;
-                        cnt += ju == j ? 1 : 0;
-                    }
-                    Item acc = L.s_v[q];
-                    if constexpr (kVal) {
-                        // terms of column j in product order
-                        uint32_t last = t;
-                        for (int c = 1; c < cnt; ++c) {
-                            uint32_t best = 0xffffffffu, bu = q;
-                            for (uint32_t u = lo; u < hi; ++u) {
-                                const uint32_t tu = L.s_t[u] & kTMask;
-                                if (L.s_j[u] == j && tu > last && tu < best) {
-                                    best = tu;
-                                    bu = u;
-                                }
-                            }
-                            acc += L.s_v[bu];
-                            last = best;
-                        }
-                    }
-                    val = finish(acc, cnt, L.rp[r + 1] - L.rp[r]);
-                }
-                leaders += uint32_t(__popcll(__ballot(lead)));
-                wave_sync();
-                if (lead) {
-                    L.s_v[q] = val;
-                    L.s_rank[q] = uint16_t(rank);
-                }
-            }
-            if (lane == 0) L.ucnt[b] = leaders;
-            wave_sync();
-        }
-        const uint32_t U = wave_scan16(L.ucnt, int(B));
-        if (lane == 0) L.ucnt[B] = U;
-        wave_sync();
-        // first output slot of every row minus its first bucket's offset
-        if (lane < nrb) L.rbase[ra + lane] = L.rcnt[ra + lane] - int64_t(L.ucnt[L.rbb[ra + lane]]);
-        wave_sync();
-        return P;
-    }
-
-    // A bucket of up to a wavefront of products at lo, one per lane: a bitonic
-    // sort across the lanes by (column, product index, slot), then the first
-    // product of every column takes the column's value (terms summed in
-    // product order, then finished) and its index among the bucket's distinct
-    // columns; the others write nothing.  Returns the distinct columns (the
-    // same on every lane).
-    __device__ uint32_t merge_wave(uint32_t lo, uint32_t sz) {
-        const bool in = uint32_t(lane) < sz;
-        uint64_t key = ~uint64_t(0);
-        Item v = Item(0);
-        if (in) {
-            const uint32_t q = lo + uint32_t(lane);
-            key = (uint64_t(L.s_j[q]) << 32) | (uint64_t(L.s_t[q] & kTMask) << 6) | uint64_t(lane);
-            v = L.s_v[q];
-        }
-#pragma unroll
-        for (int k = 2; k <= kWave; k <<= 1) {
-#pragma unroll
-            for (int d = k >> 1; d > 0; d >>= 1) {
-                const uint64_t pk = (uint64_t(uint32_t(__shfl_xor(uint32_t(key >> 32), d, kWave))) << 32) |
-                                    uint64_t(uint32_t(__shfl_xor(uint32_t(key), d, kWave)));
-                const Item pv = __shfl_xor(v, d, kWave);
-                // keep the smaller key where this lane is the low end of an
-                // ascending pair or the high end of a descending one
-                const bool keep_min = ((lane & k) == 0) == ((lane & d) == 0);
-                if (keep_min ? pk < key : pk > key) {
-                    key = pk;
-                    v = pv;
-                }
-            }
-        }
-        const bool valid = uint32_t(lane) < sz;
-        const uint32_t j = uint32_t(key >> 32);
-        const uint32_t jp = __shfl_up(j, 1, kWave);
-        const bool head = valid && (lane == 0 || jp != j);
-        const uint64_t hm = __ballot(head);
-        const uint32_t rank = uint32_t(__popcll(hm & lanemask_lt()));
-        // the column's terms are this lane's and the next ones up to the next head
-        const uint64_t above = lane + 1 < kWave ? hm >> (lane + 1) : 0;
-        const uint32_t cnt = above ? uint32_t(__ffsll((long long)above)) : sz - uint32_t(lane);
-        Item acc = v;
-        if constexpr (kVal) {
-            uint32_t cmax = head ? cnt : 1u;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) cmax = max(cmax, uint32_t(__shfl_xor(cmax, d, kWave)));
-            for (uint32_t c = 1; c < cmax; ++c) {
-                const Item w = __shfl_down(v, c, kWave);
-                if (head && c < cnt) acc += w;
-            }
-        }
-        if (valid) {
-            const uint32_t q = lo + uint32_t(key & 63u);
-            if (head) {
-                const int r = int(L.s_t[q] >> kTBits);
-                L.s_v[q] = finish(acc, int32_t(cnt), L.rp[r + 1] - L.rp[r]);
-                L.s_rank[q] = uint16_t(rank);
-            } else {
-                L.s_rank[q] = uint16_t(kNoOut);
-            }
-        }
-        wave_sync();
-        return uint32_t(__popcll(hm));
-    }
-
-    // Sort the sz (<= N) products at [lo, lo + sz) by (column, product index)
-    // in registers, each key carrying its slot.  The first product of every
-    // column takes the column's tag (term count, index among the bucket's
-    // distinct columns) and, for plus-times with several terms, their sum in
-    // product order; the other products of the column write nothing.  Returns
-    // the number of distinct columns.
-    template <int N>
-    __device__ uint32_t merge_small(uint32_t lo, uint32_t sz) {
-        static_assert(N <= 16, "slots in four bits");
-        uint64_t k[N];
-        Item v[N];
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-            const bool in = uint32_t(u) < sz;
-            k[u] = in ? ((((uint64_t(L.s_j[lo + u]) << 16) | L.s_t[lo + u]) << 4) | uint64_t(u)) : ~uint64_t(0);
-            v[u] = in ? L.s_v[lo + u] : Item(0);
-        }
-        if constexpr (N == 4) {
-            cswap(k, v, 0, 1); cswap(k, v, 2, 3); cswap(k, v, 0, 2); cswap(k, v, 1, 3); cswap(k, v, 1, 2);
+    // sort key of the product with key word w at position pos, product index o of its row
+    __device__ Key sort_key(uint32_t w, uint32_t o) const {
+        const uint32_t j = w & rowmask;
+        if constexpr (SR == kCount) {
+            return Key(j);
+        } else if constexpr (kVal) {
+            if constexpr (WIDE)
+                return (uint64_t(j) << 32) | o;
+            else
+                return (j << kOrdBits) | o;
         } else {
-            static_assert(N == 8, "networks for 4 and 8 products");
-            cswap(k, v, 0, 1); cswap(k, v, 2, 3); cswap(k, v, 4, 5); cswap(k, v, 6, 7);
-            cswap(k, v, 0, 2); cswap(k, v, 1, 3); cswap(k, v, 4, 6); cswap(k, v, 5, 7);
-            cswap(k, v, 1, 2); cswap(k, v, 5, 6); cswap(k, v, 0, 4); cswap(k, v, 3, 7);
-            cswap(k, v, 1, 5); cswap(k, v, 2, 6);
-            cswap(k, v, 1, 4); cswap(k, v, 3, 6);
-            cswap(k, v, 2, 4); cswap(k, v, 3, 5);
-            cswap(k, v, 3, 4);
+            // the partner's length from its key; saturated: from the row pointers
+            uint32_t len = w >> a.cx.rowbits;
+            if (len >= lenmax) len = uint32_t(a.rp_right[j + 1] - a.rp_right[j]);
+            if constexpr (WIDE)
+                return (uint64_t(j) << 32) | len;
+            else
+                return j * a.pack_rr + a.pack_r2 + len;
         }
-        uint32_t d = 0;
-        uint32_t gj = uint32_t(k[0] >> 20);
-        uint32_t gs = uint32_t(k[0] & 15u);
-        Item acc = v[0];
-        uint32_t cnt = 1;
-#pragma unroll
-        for (int u = 1; u <= N; ++u) {
-            const bool in = uint32_t(u) < sz;
-            const uint64_t ku = k[u < N ? u : 0];
-            const uint32_t j = in ? uint32_t(ku >> 20) : 0u;
-            if (in && j == gj) {
-                ++cnt;
-                if constexpr (kVal) acc += v[u < N ? u : 0];
-                L.s_rank[lo + uint32_t(ku & 15u)] = uint16_t(kNoOut);
-            } else if (uint32_t(u) <= sz) {
-                // the group of gj ends
-                L.s_rank[lo + gs] = uint16_t((cnt << kKBits) | d);
-                if constexpr (kVal)
-                    if (cnt > 1) L.s_v[lo + gs] = acc;
-                ++d;
-                if (in) {
-                    gj = j;
-                    gs = uint32_t(ku & 15u);
-                    acc = v[u < N ? u : 0];
-                    cnt = 1;
-                }
-            }
-        }
-        return d;
     }
-
-    // The same for counts and Jaccard values, whose terms need no order: the
-    // keys are (column, slot) in 32 bits (columns below 2^29), sorted with
-    // min/max pairs, and only the columns are loaded.  Any product of a
-    // column may take its tag: the output is the same.
-    template <int N>
-    __device__ uint32_t merge_small_cols(uint32_t lo, uint32_t sz) {
-        static_assert(N <= 8, "slots in three bits");
-        uint32_t k[N];
-#pragma unroll
-        for (int u = 0; u < N; ++u) k[u] = uint32_t(u) < sz ? ((L.s_j[lo + u] << 3) | uint32_t(u)) : 0xffffffffu;
-        auto cs = [&](int x, int y) {
-            const uint32_t a = min(k[x], k[y]), b = max(k[x], k[y]);
-            k[x] = a;
-            k[y] = b;
-        };
-        if constexpr (N == 4) {
-            cs(0, 1); cs(2, 3); cs(0, 2); cs(1, 3); cs(1, 2);
-        } else {
-            static_assert(N == 8, "networks for 4 and 8 products");
-            cs(0, 1); cs(2, 3); cs(4, 5); cs(6, 7);
-            cs(0, 2); cs(1, 3); cs(4, 6); cs(5, 7);
-            cs(1, 2); cs(5, 6); cs(0, 4); cs(3, 7);
-            cs(1, 5); cs(2, 6);
-            cs(1, 4); cs(3, 6);
-            cs(2, 4); cs(3, 5);
-            cs(3, 4);
-        }
-        uint32_t d = 0, gj = k[0] >> 3, gs = k[0] & 7u, cnt = 1;
-#pragma unroll
-        for (int u = 1; u <= N; ++u) {
-            const bool in = uint32_t(u) < sz;
-            const uint32_t ku = k[u < N ? u : 0];
-            const uint32_t j = in ? ku >> 3 : 0u;
-            if (in && j == gj) {
-                ++cnt;
-                L.s_rank[lo + (ku & 7u)] = uint16_t(kNoOut);
-            } else if (uint32_t(u) <= sz) {
-                L.s_rank[lo + gs] = uint16_t((cnt << kKBits) | d);
-                ++d;
-                if (in) {
-                    gj = j;
-                    gs = ku & 7u;
-                    cnt = 1;
-                }
-            }
-        }
-        return d;
-    }
-
-    // A bucket of two products at lo.  Distinct columns keep their slots and
-    // get their output order in their tags; equal columns merge into the
-    // first slot (terms in product order).  Returns the distinct columns.
-    __device__ uint32_t merge_two(uint32_t lo) {
-        const uint32_t j0 = L.s_j[lo], j1 = L.s_j[lo + 1];
-        if (j0 != j1) {
-            const uint32_t f = j1 < j0 ? 1u : 0u;
-            L.s_rank[lo] = uint16_t((1u << kKBits) | f);
-            L.s_rank[lo + 1] = uint16_t((1u << kKBits) | (f ^ 1u));
-            return 2;
-        }
-        if constexpr (kVal) {
-            const uint32_t t0 = L.s_t[lo], t1 = L.s_t[lo + 1];
-            const Item v0 = L.s_v[lo], v1 = L.s_v[lo + 1];
-            L.s_v[lo] = t0 < t1 ? v0 + v1 : v1 + v0;
-        }
-        L.s_rank[lo] = uint16_t(2u << kKBits);
-        L.s_rank[lo + 1] = uint16_t(kNoOut);
-        return 1;
-    }
-
-    // value of a merged column: the sum (plus-times), the count, or the
-    // Jaccard bits from the count and the two row lengths (with packed
-    // staging: the count and the partner's length, cnt * pack_r2 + |S(j)|,
-    // for the compaction to finish)
-    __device__ Item finish(Item acc, int32_t cnt, int64_t len_i) const {
-        if constexpr (kVal)
-            return acc;
-        else if constexpr (SR == kCount)
-            return cnt;
+    __device__ static uint32_t index_of(Key k) { return WIDE ? uint32_t(k) : uint32_t(k) & ((1u << kOrdBits) - 1u); }
+    // equal for two keys of a row exactly when their columns are equal
+    __device__ static uint32_t column_of(Key k) {
+        if constexpr (WIDE)
+            return uint32_t(k >> 32);
         else
-            return a.pack_rr ? int32_t(uint32_t(cnt) * a.pack_r2 + uint32_t(acc))
-                             : __float_as_int(jaccard(cnt, len_i, acc));
+            return kVal ? uint32_t(k) >> kOrdBits : uint32_t(k);
     }
 
-    template <int N>
-    __device__ static void cswap(uint64_t (&k)[N], Item (&v)[N], int x, int y) {
-        const bool sw = k[y] < k[x];
-        const uint64_t kx = sw ? k[y] : k[x], ky = sw ? k[x] : k[y];
-        const Item vx = sw ? v[y] : v[x], vy = sw ? v[x] : v[y];
-        k[x] = kx;
-        k[y] = ky;
-        v[x] = vx;
-        v[y] = vy;
-    }
-
-    // Write the batch left in LDS by batch(ra, rb, ...) (nprod products):
-    // rcnt holds each row's first output slot, rbase that slot minus the
-    // offset of the row's first bucket.
-    __device__ void write(int ra, int rb, int nprod) {
-        // outputs in slot order (about output order), each found from its
-        // slot's bucket: consecutive lanes write consecutive slots of a row
-        const uint16_t* sbk = reinterpret_cast<const uint16_t*>(L.owner);
-        for (int q = lane; q < nprod; q += kWave) {
-            const uint32_t tag = L.s_rank[q];
-            if (tag == kNoOut) continue;
-            const uint32_t b = sbk[q];
-            const int r = int(L.s_t[q] >> kTBits);
-            Item v = L.s_v[q];
-            const uint32_t cnt = tag >> kKBits;
-            if (cnt) v = finish(v, int32_t(cnt), L.rlen[r]);
-            emit(L.rbase[r] + int64_t(uint32_t(L.ucnt[b]) + (tag & kKMask)), L.s_j[q], v);
-        }
-        // diagonals (lower triangle): the last entry of every non-empty row
-        if (LOWER && lane < rb - ra) {
-            const int r = ra + lane;
-            const int64_t len = L.rp[r + 1] - L.rp[r];
-            if (len > 0) {
-                const int64_t p = L.rcnt[r] + int64_t(L.ucnt[L.rbb[r] + L.rnb[r]] - L.ucnt[L.rbb[r]]);
-                Item dv;
-                if constexpr (kVal) {
-                    double s = 0.0;
-                    for (int64_t e = L.rp[r]; e < L.rp[r + 1]; ++e) {
-                        const double v = double(static_cast<const In*>(a.val)[e]);
-                        s += v * v;
-                    }
-                    dv = s;
-                } else {
-                    dv = finish(Item(len), int32_t(len), len);  // |S(i) and S(i)| = |S(i)|
-                }
-                emit(p, uint32_t(r0 + r), dv);
-            }
-        }
-        wave_sync();
-    }
-
-    __device__ void emit(int64_t p, uint32_t j, Item v) {
-        if constexpr (!kVal) {
-            if (a.pack_rr) {  // one staged word: column and packed value
-                reinterpret_cast<uint32_t*>(a.c_ci)[p] = j * a.pack_rr + uint32_t(v);
+    // one output: slot p, sorted key k of the column's first product, its
+    // terms' count and (plus-times) sum; len_i: the row's entries (Jaccard)
+    __device__ void emit(int64_t p, Key k, uint32_t cnt, double sum, uint32_t len_i) const {
+        if constexpr (SR == kCount) {
+            if (a.pack_rr) {  // one staged word: column and count
+                a.c_ci[p] = int32_t(uint32_t(k) * a.pack_rr + cnt);
                 return;
             }
+            a.c_ci[p] = int32_t(uint32_t(k));
+            static_cast<Out*>(a.c_val)[p] = Out(cnt);
+        } else if constexpr (kVal) {
+            a.c_ci[p] = int32_t(column_of(k));
+            static_cast<Out*>(a.c_val)[p] = Out(sum);
+        } else if constexpr (WIDE) {
+            a.c_ci[p] = int32_t(column_of(k));
+            static_cast<Out*>(a.c_val)[p] = jaccard(int32_t(cnt), len_i, int64_t(uint32_t(k)));
+        } else {  // the packed word holds one term already
+            a.c_ci[p] = int32_t(uint32_t(k) + (cnt - 1u) * a.pack_r2);
         }
-        a.c_ci[p] = int32_t(j);
-        Out ov;
+    }
+
+    // ---- rows of up to 64 products, 64 / S of them side by side
+
+    struct Group {  // one register of products, its loads in flight
+        uint32_t info, key;
+        bool live;
+        In va, vb;
+    };
+
+    template <int S>
+    __device__ Group fetch(uint32_t g, uint32_t end, uint32_t ebase) const {
+        Group f;
+        const uint32_t idx = g + uint32_t(lane / S), o = uint32_t(lane % S);
+        f.info = L.ord[min(idx, end - 1u)];
+        const uint32_t p = (f.info >> 11) & 0x3ffu, slot = (f.info & 0x7ffu) + o;
+        f.live = idx < end && o < p;
+        const uint32_t d = f.live ? L.d[slot] : kNoRun;
+        // the run that holds this product starts at the nearest marked lane
+        // (a row's first product always starts one)
+        const int src = 63 - __clzll((long long)(__ballot(d != kNoRun) & upto));
+        const uint32_t pos = uint32_t(__shfl(int(d), src, kWave)) + slot;
+        f.key = 0;
+        f.va = f.vb = In(0);
+        if (f.live) {
+            f.key = a.cx.key[pos];
+            if constexpr (kVal) {
+                f.va = static_cast<const In*>(a.val)[ebase + L.x[slot - uint32_t(lane - src)]];
+                f.vb = static_cast<const In*>(a.cx.val)[pos];
+            }
+        }
+        return f;
+    }
+
+    template <int S>
+    __device__ void finish(const Group& f) const {
+        const uint32_t o = uint32_t(lane % S);
+        const uint32_t p = (f.info >> 11) & 0x3ffu, row = f.info >> 21;
+        Key k = f.live ? sort_key(f.key, o) : kDead;
+        k = wsort::sort_segments<S>(k, sides);
+        double v = 0.0;
         if constexpr (kVal)
-            ov = Out(v);
-        else if constexpr (SR == kCount)
-            ov = v;
+            v = __shfl(double(f.va) * double(f.vb), int((uint32_t(lane) & ~uint32_t(S - 1)) | (index_of(k) & uint32_t(S - 1))),
+                       kWave);
+        // (the row's products fill its first p lanes before and after the sort)
+        const uint32_t j = column_of(k);
+        const uint32_t prev = wsort::from_lane_before(j, 0u);  // (with every lane active)
+        const bool same = f.live && o > 0 && prev == j;
+        const int64_t out = L.out[row];
+        const uint32_t len_i = SR == kJaccard && WIDE ? L.len[row] : 0u;
+        if (__ballot(same) == 0) {
+            if (f.live) emit(out + o, k, 1u, v, len_i);
+            if (f.live && o == 0) L.cnt[row] = uint16_t(p);
+            return;
+        }
+        const bool head = f.live && !same;
+        const uint64_t seg = S == 64 ? ~uint64_t(0) : ((uint64_t(1) << (S & 63)) - 1) << (lane & ~(S - 1));
+        const uint64_t hm = __ballot(head) & seg;
+        const uint32_t rank = uint32_t(__popcll(hm & upto)) - 1u;  // (heads)
+        const uint64_t above = (hm >> lane) >> 1;
+        const uint32_t cnt = above ? uint32_t(__ffsll((long long)above)) : p - o;
+        if constexpr (kVal) {
+            const uint32_t most = wave_reduce_max(head ? cnt : 1u);
+            const double first = v;
+            for (uint32_t c = 1; c < most; ++c) {
+                const double w = __shfl_down(first, c, kWave);
+                if (head && c < cnt) v += w;
+            }
+        }
+        if (head) emit(out + rank, k, cnt, v, len_i);
+        if (f.live && o == 0) L.cnt[row] = uint16_t(__popcll(hm));
+    }
+
+    template <int S>
+    __device__ void short_rows(uint32_t begin, uint32_t end, uint32_t ebase) const {
+        if (begin >= end) return;
+        constexpr uint32_t kSide = kWave / S;
+        Group f = fetch<S>(begin, end, ebase);
+        for (uint32_t g = begin; g < end; g += kSide) {
+            Group n = f;
+            if (g + kSide < end) n = fetch<S>(g + kSide, end, ebase);  // (in flight during the sort)
+            finish<S>(f);
+            f = n;
+        }
+    }
+
+    // Key word and (plus-times) factors of product o of a row whose slots
+    // start at s0, every lane of one register; dc and sc carry the last run
+    // begun before this register (its word and slot).
+    __device__ Group fetch_at(uint32_t s0, uint32_t o, uint32_t p, uint32_t ebase, uint32_t& dc, uint32_t& sc,
+                              uint32_t& pos, uint32_t& x) const {
+        Group f;
+        f.info = 0;
+        f.live = o < p;
+        const uint32_t slot = s0 + o;
+        const uint32_t d = f.live ? L.d[slot] : kNoRun;
+        const uint64_t marks = __ballot(d != kNoRun), lm = marks & upto;
+        const int src = 63 - __clzll((long long)lm);
+        const uint32_t dd = uint32_t(__shfl(int(d), src, kWave));
+        pos = (lm ? dd : dc) + slot;
+        x = 0;
+        f.key = 0;
+        f.va = f.vb = In(0);
+        if (f.live) {
+            f.key = a.cx.key[pos];
+            if constexpr (kVal) x = L.x[lm ? slot - uint32_t(lane - src) : sc];
+        }
+        if (marks) {
+            const int last = 63 - __clzll((long long)marks);
+            dc = uint32_t(__builtin_amdgcn_readlane(int(d), last));
+            sc = slot - uint32_t(lane) + uint32_t(last);
+        }
+        return f;
+    }
+
+    // ---- rows of 65 to 128 products, one at a time in two registers
+
+    __device__ void pair_rows(uint32_t begin, uint32_t end, uint32_t ebase) const {
+        for (uint32_t g = begin; g < end; ++g) pair_row(uint32_t(__builtin_amdgcn_readfirstlane(int(L.ord[g]))), ebase);
+    }
+
+    __device__ void pair_row(uint32_t info, uint32_t ebase) const {
+        const uint32_t s0 = info & 0x7ffu, p = (info >> 11) & 0x3ffu, row = info >> 21;
+        const uint32_t o1 = uint32_t(kWave + lane);
+        Key k[2];
+        double t[2] = {0.0, 0.0};
+        {
+            uint32_t dc = 0, sc = 0, pos[2], x[2];
+            Group f[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) f[u] = fetch_at(s0, uint32_t(u * kWave + lane), p, ebase, dc, sc, pos[u], x[u]);
+            if constexpr (kVal) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (f[u].live) {
+                        f[u].va = static_cast<const In*>(a.val)[ebase + x[u]];
+                        f[u].vb = static_cast<const In*>(a.cx.val)[pos[u]];
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                k[u] = f[u].live ? sort_key(f[u].key, uint32_t(u * kWave + lane)) : kDead;
+                if constexpr (kVal) t[u] = double(f[u].va) * double(f[u].vb);
+            }
+        }
+        wsort::sort_regs<2>(k, sides);
+        double v[2] = {0.0, 0.0};
+        if constexpr (kVal) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t o = index_of(k[u]);
+                const double lo = __shfl(t[0], int(o & 63u), kWave), hi = __shfl(t[1], int(o & 63u), kWave);
+                v[u] = (o & 64u) ? hi : lo;
+            }
+        }
+        const int64_t out = L.out[row];
+        const uint32_t len_i = SR == kJaccard && WIDE ? L.len[row] : 0u;
+        const uint32_t j0 = column_of(k[0]), j1 = column_of(k[1]);
+        const uint32_t prev0 = wsort::from_lane_before(j0, 0u);
+        const uint32_t prev1 = wsort::from_lane_before(j1, uint32_t(__builtin_amdgcn_readlane(int(j0), kWave - 1)));
+        const bool same0 = lane > 0 && prev0 == j0, same1 = o1 < p && prev1 == j1;
+        if ((__ballot(same0) | __ballot(same1)) == 0) {
+            emit(out + lane, k[0], 1u, v[0], len_i);
+            if (o1 < p) emit(out + o1, k[1], 1u, v[1], len_i);
+            if (lane == 0) L.cnt[row] = uint16_t(p);
+            return;
+        }
+        const bool head0 = !same0, head1 = o1 < p && !same1;
+        const uint64_t hm0 = __ballot(head0), hm1 = __ballot(head1);
+        // every head's terms: up to the next head or the row's end
+        const uint64_t up0 = (hm0 >> lane) >> 1, up1 = (hm1 >> lane) >> 1;
+        const uint32_t next = hm1 ? uint32_t(kWave) + uint32_t(__ffsll((long long)hm1)) - 1u : p;
+        const uint32_t cnt0 = up0 ? uint32_t(__ffsll((long long)up0)) : next - uint32_t(lane);
+        const uint32_t cnt1 = up1 ? uint32_t(__ffsll((long long)up1)) : p - o1;
+        if constexpr (kVal) {
+            // terms of a column in product order: the sorted products moved
+            // down one lane at a time
+            const uint32_t most = wave_reduce_max(max(head0 ? cnt0 : 1u, head1 ? cnt1 : 1u));
+            double w0 = v[0], w1 = v[1];
+            for (uint32_t c = 1; c < most; ++c) {
+                const double first1 = __shfl(w1, 0, kWave);
+                w0 = __shfl_down(w0, 1, kWave);
+                w1 = __shfl_down(w1, 1, kWave);
+                if (lane == kWave - 1) w0 = first1;
+                if (head0 && c < cnt0) v[0] += w0;
+                if (head1 && c < cnt1) v[1] += w1;
+            }
+        }
+        const uint32_t n0 = uint32_t(__popcll(hm0));
+        if (head0) emit(out + __popcll(hm0 & upto) - 1, k[0], cnt0, v[0], len_i);
+        if (head1) emit(out + n0 + uint32_t(__popcll(hm1 & upto)) - 1, k[1], cnt1, v[1], len_i);
+        if (lane == 0) L.cnt[row] = uint16_t(n0 + uint32_t(__popcll(hm1)));
+    }
+
+    // ---- rows of more than 128 products, one at a time: 64 products sorted
+    // in a register at a time, merged in LDS (few registers, rolled loops)
+
+    __device__ void long_rows(uint32_t begin, uint32_t end, uint32_t ebase) const {
+        for (uint32_t g = begin; g < end; ++g) {
+            wave_sync();
+            long_row(uint32_t(__builtin_amdgcn_readfirstlane(int(L.ord[g]))), ebase);
+        }
+    }
+
+    // value of product o of the row (its position and entry kept at its slot)
+    __device__ double term(uint32_t slot, uint32_t ebase) const {
+        return double(static_cast<const In*>(a.val)[ebase + L.x[slot]]) *
+               double(static_cast<const In*>(a.cx.val)[L.d[slot]]);
+    }
+
+    __device__ void long_row(uint32_t info, uint32_t ebase) const {
+        const uint32_t s0 = info & 0x7ffu, p = (info >> 11) & 0x3ffu, row = info >> 21;
+        Key* K;
+        if constexpr (WaveLds<kVal, Key>::kOwnKeys)
+            K = L.key;
         else
-            ov = __int_as_float(v);
-        static_cast<Out*>(a.c_val)[p] = ov;
+            K = L.d + s0;
+        uint32_t dc = 0, sc = 0;
+#pragma unroll 1
+        for (uint32_t o = uint32_t(lane); o < ((p + 63u) & ~63u); o += kWave) {
+            uint32_t pos, x;
+            const Group f = fetch_at(s0, o, p, ebase, dc, sc, pos, x);
+            Key k = f.live ? sort_key(f.key, o) : kDead;
+            k = wsort::sort64(k, sides);
+            if (f.live) {
+                K[o] = k;
+                if constexpr (kVal) {
+                    L.d[s0 + o] = pos;
+                    // (a run reaching into the next registers is looked up
+                    // at its slot again: its first slot keeps its entry)
+                    L.x[s0 + o] = uint16_t(x);
+                }
+            }
+        }
+        // blocks of B sorted keys merged in pairs: mirror-image exchanges
+        // across the pair, then half-cleaners; every block ascends, so the
+        // keys past the row's end stay virtual
+#pragma unroll 1
+        for (uint32_t B = kWave; B < p; B <<= 1) {
+            wave_sync();
+#pragma unroll 1
+            for (uint32_t q = uint32_t(lane); 2 * (q & ~(B - 1)) < p; q += kWave) {
+                // (q counts the lower blocks' elements: element e of pair b)
+                const uint32_t b = 2 * (q & ~(B - 1)), e = q & (B - 1);
+                const uint32_t i = b + e, j = b + 2 * B - 1 - e;
+                if (j < p) {
+                    const Key u = K[i], w = K[j];
+                    if (w < u) {
+                        K[i] = w;
+                        K[j] = u;
+                    }
+                }
+            }
+#pragma unroll 1
+            for (uint32_t h = B >> 1; h >= uint32_t(kWave); h >>= 1) {
+                wave_sync();
+#pragma unroll 1
+                for (uint32_t q = uint32_t(lane); 2 * (q & ~(h - 1)) < p; q += kWave) {
+                    const uint32_t i = 2 * (q & ~(h - 1)) + (q & (h - 1)), j = i + h;
+                    if (j < p) {
+                        const Key u = K[i], w = K[j];
+                        if (w < u) {
+                            K[i] = w;
+                            K[j] = u;
+                        }
+                    }
+                }
+            }
+            wave_sync();
+#pragma unroll 1
+            for (uint32_t o = uint32_t(lane); o < ((p + 63u) & ~63u); o += kWave) {
+                const Key k = wsort::merge64(o < p ? K[o] : kDead, sides);
+                if (o < p) K[o] = k;
+            }
+        }
+        wave_sync();
+        const int64_t out = L.out[row];
+        const uint32_t len_i = SR == kJaccard && WIDE ? L.len[row] : 0u;
+        uint32_t heads = 0;
+#pragma unroll 1
+        for (uint32_t o = uint32_t(lane); o < ((p + 63u) & ~63u); o += kWave) {
+            const Key k = o < p ? K[o] : kDead;
+            const uint32_t j = column_of(k);
+            const bool head = o < p && !(o > 0 && column_of(K[o - 1]) == j);
+            const uint64_t hm = __ballot(head);
+            if (head) {
+                double v = 0.0;
+                if constexpr (kVal) v = term(s0 + index_of(k), ebase);
+                uint32_t cnt = 1;  // terms in product order
+                for (; o + cnt < p; ++cnt) {
+                    const Key n = K[o + cnt];
+                    if (column_of(n) != j) break;
+                    if constexpr (kVal) v += term(s0 + index_of(n), ebase);
+                }
+                emit(out + heads + uint32_t(__popcll(hm & upto)) - 1, k, cnt, v, len_i);
+            }
+            heads += uint32_t(__popcll(hm));
+        }
+        if (lane == 0) L.cnt[row] = uint16_t(heads);
+    }
+
+    // Entries [eb, eb + ne) of the batch: their runs marked at their first
+    // product slots (nprod slots).
+    __device__ void mark_runs(uint32_t eb, int ne, int nprod) const {
+        for (int q = 4 * lane; q < nprod; q += 4 * kWave)
+            *reinterpret_cast<uint4*>(L.d + q) = make_uint4(kNoRun, kNoRun, kNoRun, kNoRun);
+        wave_sync();
+        constexpr int kU = 4;  // run words per lane in flight
+        uint32_t carry = 0;
+        for (int b = 0; b < ne; b += kU * kWave) {
+            uint32_t w[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int q = b + u * kWave + lane;
+                w[u] = q < ne ? a.run.r4[eb + q] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int q = b + u * kWave + lane;
+                if (b + u * kWave >= ne) break;
+                const uint2 r = q < ne ? run_from(a.run, w[u], int64_t(eb) + q) : make_uint2(0u, 0u);
+                const uint32_t len = r.y - r.x;
+                const uint32_t inc = wsort::inclusive_sum(len);
+                const uint32_t slot = carry + inc - len;
+                if (len) {
+                    L.d[slot] = r.x - slot;
+                    if constexpr (kVal) L.x[slot] = uint16_t(q);
+                }
+                carry += uint32_t(__builtin_amdgcn_readlane(int(inc), kWave - 1));
+            }
+        }
+        wave_sync();
     }
 
     // A chunk's row pointers, product counts and staging slots (lane = row),
     // loaded in one round, ahead of the chunk.
     struct Head {
-        int64_t rpv = 0, ubv = 0;
+        int64_t ubv = 0;
         uint64_t pr = 0;
+        uint32_t rpv = 0, rpn = 0;  // the row's entries
     };
     __device__ Head head(int64_t c) const {
         const int R = a.rows_per_chunk;
         const int64_t rs = c * R;
         const int nr = int(min(int64_t(R), a.m - rs));
         Head h;
-        if (lane <= nr) h.rpv = a.rp[rs + lane];
         if (lane < nr) {
+            h.rpv = uint32_t(a.rp[rs + lane]);  // (entries of A are below 2^31)
+            h.rpn = uint32_t(a.rp[rs + lane + 1]);
             h.pr = a.prod[rs + lane];
             h.ubv = a.ubp[rs + lane];
         }
         return h;
     }
 
+    // Sum of the squares of every light row's entries (lane = row): eight
+    // lanes per row, two groups of eight rows at a time, the first 32 entries
+    // of each in one round of loads.
+    __device__ double diagonals(uint32_t rpv, int nr) const {
+        double mine = 0.0;
+        const uint32_t sub = uint32_t(lane) & 7u;
+        constexpr int kU = 4;
+        for (int g = 0; g < nr; g += 16) {
+            double t[2];
+            In v[2][kU];
+            uint32_t s[2], e[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int row = min(g + 8 * h + (lane >> 3), kFR - 1);
+                s[h] = uint32_t(__shfl(int(rpv), row, kWave)) + sub;
+                e[h] = s[h] - sub + (g + 8 * h + (lane >> 3) < nr ? uint32_t(L.len[row]) : 0u);
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+                    v[h][u] = s[h] + 8u * u < e[h] ? static_cast<const In*>(a.val)[s[h] + 8u * u] : In(0);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                t[h] = 0.0;
+#pragma unroll
+                for (int u = 0; u < kU; ++u) t[h] += double(v[h][u]) * double(v[h][u]);
+                for (uint32_t q = s[h] + 8u * kU; q < e[h]; q += 8u) {
+                    const double w = double(static_cast<const In*>(a.val)[q]);
+                    t[h] += w * w;
+                }
+                t[h] = wsort::sum8(t[h]);
+                const double got = __shfl(t[h], int(8u * sub), kWave);
+                if ((lane >> 3) == (g >> 3) + h) mine = got;
+            }
+        }
+        return mine;
+    }
+
     __device__ void run(int64_t c, const Head& h) {
         const int R = a.rows_per_chunk;
         r0 = c * R;
         const int nr = int(min(int64_t(R), a.m - r0));
-        const int64_t rpv = h.rpv, ubv = h.ubv;
-        const uint64_t pr = h.pr;
-        if (lane <= nr) L.rp[lane] = rpv;
-        wave_sync();
-        int64_t len = 0;
-        bool light = false;
-        const int64_t rpn = __shfl_down(rpv, 1, kWave);  // row pointer after this lane's row
-        if (lane < nr) {
-            len = rpn - rpv;
-            light = pr <= uint64_t(kFP) && len <= kFE;
-            L.rprod[lane] = light ? uint16_t(pr) : 0;
-            // light rows are written at their upper-bound slots (products + diagonal)
-            L.rcnt[lane] = ubv;
-        }
+        const uint32_t len = h.rpn - h.rpv;
+        const bool light = lane < nr && h.pr <= uint64_t(kFP) && len <= uint32_t(kFE);
+        const uint32_t p = light ? uint32_t(h.pr) : 0u;
+        L.out[lane] = h.ubv;
+        L.cnt[lane] = 0;
+        L.len[lane] = light ? uint16_t(len) : uint16_t(0);
+        const uint32_t pinc = wsort::inclusive_sum(p), pexc = pinc - p;
         // batches of consecutive light rows, cut greedily: a batch opened at
-        // row ra takes the following light rows while its entries and products
-        // fit the LDS budget; every lane tests its own row against the prefix
-        // sums at ra, and the batch ends at the first row that fails.  Lane k
-        // keeps batch k's rows (ra | rb << 8).
-        const uint64_t lightmask = __ballot(lane < nr && light);
-        const uint32_t mypr = (lane < nr && light) ? uint32_t(pr) : 0u;
-        const uint32_t pinc = wave_inclusive_scan(mypr);
-        const uint32_t pexc = pinc - mypr;
-        int nbatch = 0;
-        uint32_t mybatch = 0;
+        // row ra takes the following light rows while its products fit
+        const uint64_t lightmask = __ballot(light);
         for (uint64_t rest = lightmask; rest;) {
             const int ra = __ffsll((unsigned long long)rest) - 1;
-            const int64_t ea = int64_t(uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(rpv)), ra))) |
-                                       (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(uint64_t(rpv) >> 32)), ra))) << 32));
             const uint32_t pa = uint32_t(__builtin_amdgcn_readlane(int(pexc), ra));
-            const bool ok = lane >= ra && lane < nr && light && rpn - ea <= kFE && pinc - pa <= uint32_t(kFP);
-            const uint64_t okm = __ballot(ok) >> ra;
-            const int rb = ra + __ffsll((unsigned long long)~okm) - 1;
-            if (lane == nbatch) mybatch = uint32_t(ra) | (uint32_t(rb) << 8);
-            ++nbatch;
-            rest = lightmask & (~uint64_t(0) << rb);
+            const uint64_t okm = __ballot(lane >= ra && light && pinc - pa <= uint32_t(kCap)) >> ra;
+            const int rb = ~okm ? ra + __ffsll((unsigned long long)~okm) - 1 : kWave;
+            rest = rb < kWave ? lightmask & (~uint64_t(0) << rb) : 0;
+            const uint32_t nprod = uint32_t(__builtin_amdgcn_readlane(int(pinc), rb - 1)) - pa;
+            if (nprod == 0) continue;
+            const uint32_t eb = uint32_t(__builtin_amdgcn_readlane(int(h.rpv), ra));
+            const uint32_t ee = uint32_t(__builtin_amdgcn_readlane(int(h.rpn), rb - 1));
+            mark_runs(eb, int(ee - eb), int(nprod));
+            // rows by size class
+            const uint32_t q = lane >= ra && lane < rb ? p : 0u;
+            const uint32_t info = (pexc - pa) | (p << 11) | (uint32_t(lane) << 21);
+            constexpr uint32_t kMost[6] = {8, 16, 32, 64, 128, kFP};
+            uint32_t at[7];
+            at[0] = 0;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                const bool in = q > (k ? kMost[k ? k - 1 : 0] : 0u) && q <= kMost[k];
+                const uint64_t m = __ballot(in);
+                if (in) L.ord[at[k] + uint32_t(__popcll(m & upto)) - 1u] = info;
+                at[k + 1] = at[k] + uint32_t(__popcll(m));
+            }
+            wave_sync();
+            short_rows<8>(at[0], at[1], eb);
+            short_rows<16>(at[1], at[2], eb);
+            short_rows<32>(at[2], at[3], eb);
+            short_rows<64>(at[3], at[4], eb);
+            pair_rows(at[4], at[5], eb);
+            long_rows(at[5], at[6], eb);
+            wave_sync();
         }
         wave_sync();
-        int64_t cnt = 0;  // exact length of this lane's row
-        if (lane < nr) cnt = light ? ((LOWER && len > 0) ? 1 : 0) : a.heavy_nnz[r0 + lane];
-        uint32_t rn[kRunRegs];
-        uint32_t bk = nbatch > 0 ? uint32_t(__builtin_amdgcn_readlane(int(mybatch), 0)) : 0u;
-        if (nbatch > 0) fetch_runs(int(bk & 0xffu), int(bk >> 8), rn);
-        for (int k = 0; k < nbatch; ++k) {
-            const int ra = int(bk & 0xffu), rb = int(bk >> 8);
-            const bool more = k + 1 < nbatch;
-            const uint32_t bn = more ? uint32_t(__builtin_amdgcn_readlane(int(mybatch), k + 1)) : 0u;
-            const int P = batch(ra, rb, rn, more ? int(bn & 0xffu) : -1, more ? int(bn >> 8) : 0);
-            bk = bn;
-            if (lane >= ra && lane < rb)
-                cnt += int64_t(L.ucnt[L.rbb[lane] + L.rnb[lane]] - L.ucnt[L.rbb[lane]]);
-            write(ra, rb, P);
+        double dv = 0.0;
+        if constexpr (LOWER && kVal) dv = diagonals(h.rpv, nr);
+        if (lane < nr) {
+            // exact lengths; diagonals (lower triangle) end their rows
+            int64_t cnt = light ? int64_t(L.cnt[lane]) : a.heavy_nnz[r0 + lane];
+            if (LOWER && light && len > 0) {
+                const int64_t at = h.ubv + cnt;
+                const uint32_t i = uint32_t(r0 + lane);
+                if constexpr (kVal) {
+                    a.c_ci[at] = int32_t(i);
+                    static_cast<Out*>(a.c_val)[at] = Out(dv);
+                } else if constexpr (SR == kCount) {  // |S(i) and S(i)| = |S(i)|
+                    emit(at, Key(i), len, 0.0, len);
+                } else if constexpr (WIDE) {
+                    emit(at, (uint64_t(i) << 32) | len, len, 0.0, len);
+                } else {
+                    emit(at, i * a.pack_rr + a.pack_r2 + len, len, 0.0, len);
+                }
+                ++cnt;
+            }
+            a.row_cnt[r0 + lane] = cnt;
         }
-        if (lane < nr) a.row_cnt[r0 + lane] = cnt;
+        wave_sync();
     }
 };
 
-template <int SR, bool LOWER>
-// (plus-times: at most 168 VGPRs, three wavefronts per SIMD)
-__global__ __launch_bounds__(kWave* kWavesF) __attribute__((amdgpu_waves_per_eu(SR == kF64 || SR == kF32 ? 3 : 1)))
-void fused_kernel(FusedArgs a) {
-    using Item = typename ItemOf<SR>::T;
-    __shared__ WaveLds<Item> lds[kWavesF];
-    WaveLds<Item>& L = lds[threadIdx.x / kWave];
-    Chunk<SR, LOWER> ch(a, L);
-    // Persistent wavefronts.  With few chunks per launched wavefront the
-    // chunks are dealt out in turn (c, c + stride, ...).  With many, the
-    // wavefronts take runs of consecutive chunks from a counter, so that
-    // every wavefront the device holds keeps busy however many of the
-    // launched ones are resident at once and however the chunks' costs vary:
-    // a run is a quarter of the chunks left per launched wavefront (as last
-    // seen), at least one, so the runs shrink towards the end.  The next
-    // chunk is taken and its head loaded while the current chunk runs.
+// Persistent wavefronts.  With few chunks per launched wavefront the chunks
+// are dealt out in turn (c, c + stride, ...).  With many, the wavefronts take
+// runs of consecutive chunks from a counter, so that every wavefront the
+// device holds keeps busy however many of the launched ones are resident at
+// once and however the chunks' costs vary: a run is a quarter of the chunks
+// left per launched wavefront (as last seen), at least one, so the runs
+// shrink towards the end.  The next chunk is taken and its head loaded while
+// the current chunk runs.
+template <int SR, bool LOWER, bool WIDE>
+__device__ void all_chunks(const FusedArgs& a) {
+    using C = Chunk<SR, LOWER, WIDE>;
+    __shared__ WaveLds<C::kVal, typename C::Key> lds[kWavesF];
+    C ch(a, lds[threadIdx.x / kWave]);
     const int lane = lane_id();
     if (blockIdx.x == 0 && threadIdx.x == 0) a.row_cnt[a.m] = 0;  // (the scan's last input)
     const int64_t nwaves = int64_t(gridDim.x) * kWavesF;
@@ -899,6 +657,16 @@ void fused_kernel(FusedArgs a) {
     }
 }
 
+// (Jaccard off the diagonal has no packed words)
+template <int SR, bool LOWER>
+__global__ __launch_bounds__(kWave* kWavesF) void fused_kernel(FusedArgs a) {
+    all_chunks<SR, LOWER, SR == kJaccard && !LOWER>(a);
+}
+template <int SR, bool LOWER>
+__global__ __launch_bounds__(kWave* kWavesF) void fused_wide(FusedArgs a) {
+    all_chunks<SR, LOWER, true>(a);
+}
+
 // Workgroups resident on the whole device at once (at least one).
 template <typename K>
 int resident_groups(K kernel) {
@@ -910,16 +678,28 @@ int resident_groups(K kernel) {
     return g > 0 ? g : 1;
 }
 
+template <int SR, bool LOWER>
+void launch(const FusedArgs& a, bool wide, int grid, hipStream_t s) {
+    if constexpr (SR != kCount && !(SR == kJaccard && !LOWER)) {
+        if (wide) {
+            static const int res = resident_groups(fused_wide<SR, LOWER>);
+            fused_wide<SR, LOWER><<<grid < res ? grid : res, kWave * kWavesF, 0, s>>>(a);
+            return;
+        }
+    }
+    static const int res = resident_groups(fused_kernel<SR, LOWER>);
+    fused_kernel<SR, LOWER><<<grid < res ? grid : res, kWave * kWavesF, 0, s>>>(a);
+}
+
 template <int SR>
 void launch(const FusedArgs& a, int grid, hipStream_t s) {
-    if (grid <= 0) return;
-    if (a.lower) {
-        static const int res = resident_groups(fused_kernel<SR, true>);
-        fused_kernel<SR, true><<<grid < res ? grid : res, kWave * kWavesF, 0, s>>>(a);
-    } else {
-        static const int res = resident_groups(fused_kernel<SR, false>);
-        fused_kernel<SR, false><<<grid < res ? grid : res, kWave * kWavesF, 0, s>>>(a);
-    }
+    // 64-bit sort keys where a column and a product index, or a Jaccard
+    // word, do not fit 32 bits
+    const bool wide = SR == kJaccard ? a.pack_rr == 0 : a.m_right > (int64_t(1) << (32 - kOrdBits));
+    if (a.lower)
+        launch<SR, true>(a, wide, grid, s);
+    else
+        launch<SR, false>(a, wide, grid, s);
 }
 
 __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restrict__ rp,
