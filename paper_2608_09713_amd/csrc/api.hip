@@ -352,9 +352,12 @@ void validate(const DevCsr& A, bool upper_forbidden, Arena& ar, Ctl* ctl, hipStr
 // ccount (zeroed, B.n entries, with no directory only): the entries of every
 // column, written when the local sort builds the index (*counted is then set).
 // vsrc (N entries): the entry of B behind every position of the index.
+// entries: the index keeps {key, entry of B} instead of keys and values
+// (index_keeps_entries; vsrc is then not written).
 ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ctl, hipStream_t s,
                      const RunTab* run = nullptr, bool need_dir = true, uint32_t* ccount = nullptr, bool* counted = nullptr,
-                     uint32_t* vsrc = nullptr, uint32_t* hist1 = nullptr, const int64_t* trow1 = nullptr) {
+                     uint32_t* vsrc = nullptr, uint32_t* hist1 = nullptr, const int64_t* trow1 = nullptr,
+                   bool entries = false) {
     ColIndex cx;
     cx.n = B.n;
     cx.m = B.m;
@@ -380,11 +383,14 @@ ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ct
     const int vb_out = csc_value_bytes(sr);
 
     cx.gptr = runs_given ? nullptr : ar.get_t<uint32_t>(cx.ngroups + 1);
-    cx.key = ar.get_t<uint32_t>(N > 0 ? N : 1);
+    if (entries)
+        cx.ke = ar.get_t<uint2>(N);
+    else
+        cx.key = ar.get_t<uint32_t>(N > 0 ? N : 1);
     // with every partner run given, Jaccard keys carry the row lengths
     // (the row field's spare bits) and no value array is kept
     if (sr == kJaccard && runs_given) cx.lenbits = 32 - cx.rowbits;
-    cx.val = vb_out && cx.lenbits == 0 ? ar.get(size_t(N > 0 ? N : 1) * vb_out) : nullptr;
+    cx.val = vb_out && cx.lenbits == 0 && !entries ? ar.get(size_t(N > 0 ? N : 1) * vb_out) : nullptr;
 
     if (N > 0) {
         // records (column, row, entry index) sorted by column; values are
@@ -423,6 +429,7 @@ ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ct
             pk.ccount = ccount;
             pk.vsrc = vsrc;  // (ctl->nkept is zero: ctl is zeroed at the call's start)
             pk.carried = carried;
+            pk.ke = cx.ke;
         }
         const int which = radix_sort_csr(B.ci, B.rp, B.m, cx.rowbits, lenbits, ka, kb, ra, rb, ea, eb, N, nbits_n, tmp,
                                          s, runs_given ? &pk : nullptr, hist1, trow1);
@@ -460,18 +467,21 @@ spsyrk_status finish(spsyrk_status st) {
 
 // Rows per wavefront chunk of the light-row kernel (SPSYRK_ROWS_PER_CHUNK
 // overrides it for tuning); a chunk splits into as many LDS batches as needed.
-// A matrix of fewer rows than the device's wavefronts hold in chunks of
-// kFusedRows takes shorter chunks (down to 8 rows), so that more wavefronts
-// share it: tiny_uniform_f64 (4096 rows) 28 -> 17 us.
+// Long chunks fill the wavefront registers that hold rows of one size class;
+// short ones keep the last round of chunks short, where the wavefronts take
+// only a few each: 64 rows from eight chunks per wavefront on (jaccard_large,
+// 2^23 rows: 1.47 ms against 1.64 with 32 rows), else down to 16 (kmer_i32,
+// 2^20 rows: 0.376 ms against 0.414 with 64), and 8 where 16 rows would leave
+// wavefronts without any (tiny_uniform_f64).
 int rows_per_chunk(int64_t m) {
     if (const char* e = std::getenv("SPSYRK_ROWS_PER_CHUNK")) {
         const int v = std::atoi(e);
         if (v >= 1 && v <= kFusedRows) return v;
     }
-    constexpr int64_t kWaves = 3072;  // wavefronts of the light kernel resident on the device
+    constexpr int64_t kWaves = 6144;  // wavefronts of the light kernel resident on the device
     int r = kFusedRows;
-    while (r > 8 && m < int64_t(r) * kWaves) r /= 2;
-    return r;
+    while (r > 16 && m < int64_t(r) * 8 * kWaves) r /= 2;
+    return m < int64_t(r) * kWaves ? 8 : r;
 }
 
 constexpr int64_t kDenseColumns = int64_t(1) << 28;  // dense column starts: at most 1 GiB
@@ -487,7 +497,7 @@ struct LowerPlan {
     int64_t* rp = nullptr;  // copies of the pattern
     int32_t* ci = nullptr;
     ColIndex cx;
-    uint32_t* vsrc = nullptr;  // entry of A behind every position of the index (nnz)
+    uint32_t* vsrc = nullptr;  // entry of A behind every position of the index (nnz; null with cx.ke)
     RunTab run;
     uint32_t* rend = nullptr;  // run ends of the heavy rows' entries (nnz, with cursor)
     unsigned long long* prod = nullptr;
@@ -502,16 +512,29 @@ struct LowerPlan {
     int64_t nchunks = 0;
 };
 
+// Whether the column index of B in lower mode keeps entries in place of the
+// values: plus-times with the local sort (which writes the index) and at most
+// one entry per column on average, where a column's entries are seldom
+// partners (at uniform columns half as many products as entries).  Gathering
+// every entry's value in sorted order then costs more than reading each
+// product's: one random read at about 53 G/s each.  (offdiag_f64's A_i, 12.6 M
+// entries and 4.7 M products: the gather alone takes 0.24 ms.)
+bool index_keeps_entries(const DevCsr& B, int sr) {
+    if ((sr != kF64 && sr != kF32) || B.nnz <= 0 || B.nnz > B.n) return false;
+    return local_bits(B.nnz, bit_width_u64(B.n > 1 ? uint64_t(B.n - 1) : 0)) > 0;
+}
+
 // The buffers build_index takes for the column index of B in lower mode
 // (every partner run given), allocated ahead with Arena::reserve: the keys,
 // two buffers each of sorted keys, rows and entries, the values (none for
-// Jaccard, whose keys carry the lengths) and the sort's workspace.
-void reserve_index(const DevCsr& B, int sr, Arena& ar) {
+// Jaccard, whose keys carry the lengths) or entries beside the keys, and the
+// sort's workspace.
+void reserve_index(const DevCsr& B, int sr, Arena& ar, bool entries) {
     const int64_t N = B.nnz;
     if (N <= 0) return;
     const int nbits = bit_width_u64(B.n > 1 ? uint64_t(B.n - 1) : 0);
-    ar.reserve(size_t(N) * sizeof(uint32_t), 7);
-    const int vb = csc_value_bytes(sr);
+    ar.reserve(size_t(N) * sizeof(uint32_t), entries ? 6 : 7);
+    const int vb = entries ? int(sizeof(uint2)) : csc_value_bytes(sr);
     if (vb && sr != kJaccard) ar.reserve(size_t(N) * size_t(vb));
     ar.reserve(radix_csr_tmp_bytes(N, nbits));
 }
@@ -554,16 +577,17 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
     if (lower) {
         HIPCHK(hipMemsetAsync(run.r4, 0, size_t(L.nnz) * sizeof(uint32_t), s));
         if (run.radix == 1) HIPCHK(hipMemsetAsync(run.r8, 0, size_t(L.nnz) * sizeof(uint2), s));
+        const bool entries = index_keeps_entries(L, sr);
         uint32_t* vsrc = nullptr;
-        if (plan) {
+        if (plan && !entries) {
             vsrc = ar.get_t<uint32_t>(L.nnz);
             HIPCHK(hipMemsetAsync(vsrc, 0, size_t(L.nnz) * sizeof(uint32_t), s));
             plan->vsrc = vsrc;
         }
-        reserve_index(L, sr, ar);
+        reserve_index(L, sr, ar, entries);
         checked();
         Phase ph(SPSYRK_PHASE_COLINDEX, s);
-        cx = build_index(L, true, sr, ar, ctl, s, &run, true, nullptr, nullptr, vsrc, hist1, vrows);
+        cx = build_index(L, true, sr, ar, ctl, s, &run, true, nullptr, nullptr, vsrc, hist1, vrows, entries);
         if (hist1) ar.release(hist1);
     } else {
         checked();
@@ -606,6 +630,18 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
     ar.release(ptmp);
     const int64_t nheavy = h.heavy_count;
     const int64_t light_cap = int64_t(h.light_cap);
+    if (cx.ke && (nheavy > 0 || int64_t(h.products) > L.nnz)) {
+        // more products than entries after all (or heavy rows, which walk
+        // keys and values many times): every value gathered once
+        const int vb = csc_value_bytes(sr);
+        cx.key = ar.get_t<uint32_t>(L.nnz);
+        cx.val = ar.get(size_t(L.nnz) * size_t(vb));
+        if (plan) plan->vsrc = ar.get_t<uint32_t>(L.nnz);
+        split_index(cx.ke, L.nnz, L.v, vb, cx.key, cx.val, plan ? plan->vsrc : nullptr, s);
+        check_launch();
+        ar.release(cx.ke);
+        cx.ke = nullptr;
+    }
     HeavyArgs ha;
     int64_t* heavy_nnz = nullptr;
     if (nheavy > 1) {
@@ -743,9 +779,10 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         plan->run.radix = run.radix;
         plan->run.inv = run.inv;
         plan->prod = static_cast<unsigned long long*>(ar.keep(prod));
-        ar.keep(cx.key);
+        if (cx.ke) ar.keep(cx.ke);
+        if (cx.key) ar.keep(cx.key);
         if (cx.val) ar.keep(cx.val);
-        ar.keep(plan->vsrc);
+        if (plan->vsrc) ar.keep(plan->vsrc);
         plan->heavy_rows = static_cast<int32_t*>(ar.keep(heavy_rows));
         plan->nheavy = nheavy;
         if (nheavy > 0) {
@@ -1244,7 +1281,7 @@ void lower_execute(const LowerPlan& P, const void* vals, Arena& ar, hipStream_t 
     }
     HIPCHK(hipMemcpyAsync(c_rp, P.c_rp, size_t(m + 1) * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
     const int vb = (P.sr == kF64) ? 8 : (P.sr == kF32 ? 4 : 0);
-    if (vb) {
+    if (vb && !P.cx.ke) {  // (an index that keeps entries needs no values)
         gather_values(P.cx.val, vals, P.vsrc, P.nnz, vb, s);
         check_launch();
     }
@@ -1676,7 +1713,7 @@ spsyrk_status spsyrk_lower_plan(const spsyrk_csr* A, spsyrk_semiring sr, const s
         }
         for (void* q : {static_cast<void*>(lp.rp), static_cast<void*>(lp.ci), static_cast<void*>(lp.run.r8),
                         static_cast<void*>(lp.run.r4), static_cast<void*>(lp.rend),
-                        static_cast<void*>(lp.prod), static_cast<void*>(lp.cx.key), lp.cx.val,
+                        static_cast<void*>(lp.prod), static_cast<void*>(lp.cx.ke), static_cast<void*>(lp.cx.key), lp.cx.val,
                         static_cast<void*>(lp.vsrc), static_cast<void*>(lp.heavy_rows),
                         static_cast<void*>(lp.heavy_nnz), static_cast<void*>(lp.cursor),
                         static_cast<void*>(lp.ctl), static_cast<void*>(lp.c_rp)})

@@ -57,6 +57,9 @@ struct ColIndex {
     int64_t nkept = 0;      // entries kept (device-side value is authoritative until synced)
     uint32_t* key = nullptr;
     void* val = nullptr;    // double / float values of B, or int32 row lengths of B (Jaccard)
+    // non-null (lower mode, plus-times): {key, entry of B} per position instead
+    // of key and val, the values then read from B's by entry
+    uint2* ke = nullptr;
     uint32_t* gptr = nullptr;  // null when every entry's partner run is given (no lookups)
     // > 0 (Jaccard with every partner run given): each key also carries its
     // row's length above the row bits, saturated at 2^lenbits - 1 (the full
@@ -168,6 +171,7 @@ struct LocalPack {
     int64_t* kept = nullptr;
     uint32_t* ccount = nullptr;  // non-null (zeroed, one per column): entries of every column
     uint32_t* vsrc = nullptr;    // non-null: the entry index of every written position
+    uint2* ke = nullptr;         // non-null: {key, entry index} per position, in place of key and val
     // 4 or 8 (with vals_b, and no run table and no vsrc): the record passes
     // carry each entry's value in place of its index (the third record
     // buffers then hold values of that size), so the local sort reads values
@@ -285,6 +289,10 @@ void column_starts(const int32_t* ci, int64_t nnz, int64_t n, uint32_t* cptr, vo
 void rebase_rows(const int64_t* rp, int64_t r0, int64_t m, int64_t* out, hipStream_t s);
 // dst[p] = src[idx[p]] for p < n, elements of vb (4 or 8) bytes.
 void gather_values(void* dst, const void* src, const uint32_t* idx, int64_t n, int vb, hipStream_t s);
+// The column index ke of n positions as separate arrays: key, val (values of
+// vb bytes gathered from src by entry) and, if not null, vsrc (the entries).
+void split_index(const uint2* ke, int64_t n, const void* src, int vb, uint32_t* key, void* val, uint32_t* vsrc,
+                 hipStream_t s);
 // ci[p] += off for p < nnz.
 void shift_columns(int32_t* ci, int64_t nnz, int32_t off, hipStream_t s);
 // Off-diagonal partner runs: run[e] = {cptr[ci[e]], cptr[ci[e] + 1]}.

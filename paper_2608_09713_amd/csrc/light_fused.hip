@@ -2,7 +2,7 @@
 //
 // Work unit: a chunk of R consecutive rows per wavefront.  Each wavefront
 // works alone in its own slice of LDS (no workgroup barriers), in batches of
-// consecutive light rows of at most kCap products:
+// consecutive light rows of at most 1024 (with values 768) products:
 //
 //   1. the batch's entries, 64 at a time: the partner run of every entry
 //      (written by the column-index build), a prefix sum of the run lengths,
@@ -36,15 +36,16 @@ namespace {
 constexpr int kFE = kFusedEntries;   // entries of a light row
 constexpr int kFP = kFusedProducts;  // products of a light row
 constexpr int kFR = kFusedRows;      // rows per chunk (upper limit: one per lane)
-constexpr int kCap = 1024;           // product slots per batch
+// product slots per batch
+constexpr int slots(bool val) { return val ? 768 : 1024; }
 constexpr int kWavesF = 2;           // wavefronts per workgroup
 constexpr int kDealtBelow = 16;      // chunks per launched wavefront below which chunks are dealt out
 constexpr int kOrdBits = 9;          // product index bits of a 32-bit plus-times key (column above them)
-constexpr uint32_t kNoRun = 0x80000000u;  // a slot where no run starts (starts are below 2^31, slots below kCap)
+constexpr uint32_t kNoRun = 0x80000000u;  // a slot where no run starts (starts are below 2^31, slots below 2^11)
 static_assert(kFR <= kWave, "one row per lane");
-static_assert(kFP <= kCap, "a row fits a batch");
+static_assert(kFP <= slots(true) && kFP <= slots(false), "a row fits a batch");
 static_assert(kFP <= (1 << kOrdBits), "a product index must fit kOrdBits");
-static_assert(kCap <= (1 << 11) && kFP <= (1 << 10) && kFR <= (1 << 6), "fields of a listed row");
+static_assert(slots(false) <= (1 << 11) && slots(true) <= (1 << 11) && kFP <= (1 << 10) && kFR <= (1 << 6), "fields of a listed row");
 static_assert(kFR * kFE <= (1 << 16), "an entry's index in its batch must fit 16 bits");
 
 __device__ inline void wave_sync() {
@@ -53,10 +54,12 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// (5 KiB: 32 wavefronts per compute unit; with values 9 or 11 KiB: 17 or 14)
+// (5 KiB; with values 7.5 KiB, 64-bit keys 9.5: 20 and 16 wavefronts per
+// compute unit)
 template <bool VAL, typename Key>
 struct WaveLds {
     // a long row's keys; without values 32-bit keys take the row's slots of d
+    static constexpr int kCap = slots(VAL);
     static constexpr bool kOwnKeys = VAL || sizeof(Key) > 4;
     Key key[kOwnKeys ? kFP : 1];
     alignas(16) uint32_t d[kCap];  // start of the run that begins at the slot, less the slot; else kNoRun
@@ -78,19 +81,28 @@ struct Chunk {
     using Out = typename Tr::Out;
     using Key = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
     static constexpr bool kVal = (SR == kF64 || SR == kF32);
+    static constexpr int kCap = slots(kVal);
     static constexpr Key kDead = ~Key(0);  // sorts behind every product of its row
 
     const FusedArgs& a;
     WaveLds<kVal, Key>& L;
-    const int lane;
-    const wsort::Sides sides;
-    const uint64_t upto;  // lanes up to this one
+    const int lane0;
     uint32_t rowmask;
     uint32_t lenmax;  // saturated length in a key (Jaccard keys carrying lengths)
     int64_t r0 = 0;
 
-    __device__ Chunk(const FusedArgs& a_, WaveLds<kVal, Key>& L_)
-        : a(a_), L(L_), lane(lane_id()), sides(lane), upto((uint64_t(2) << lane) - 1) {
+    // The lane number, as a value the compiler does not know: what a passage
+    // derives from it (masks, sides, addresses) is formed there again instead
+    // of being held in registers through all the others (25 of them: one
+    // wavefront per SIMD).
+    __device__ int fresh_lane() const {
+        int l = lane0;
+        asm volatile("" : "+v"(l));
+        return l;
+    }
+    __device__ static uint64_t lanes_upto(int lane) { return (uint64_t(2) << lane) - 1; }
+
+    __device__ Chunk(const FusedArgs& a_, WaveLds<kVal, Key>& L_) : a(a_), L(L_), lane0(lane_id()) {
         rowmask = a.cx.rowbits >= 32 ? 0xffffffffu : ((1u << a.cx.rowbits) - 1u);
         lenmax = a.cx.lenbits > 0 ? ((a.cx.lenbits >= 32 ? 0xffffffffu : (1u << a.cx.lenbits) - 1u)) : 0u;
     }
@@ -149,12 +161,32 @@ struct Chunk {
 
     struct Group {  // one register of products, its loads in flight
         uint32_t info, key;
+        uint32_t src;  // (plus-times) the partner's value: its place in right_values()
         bool live;
-        In va, vb;
+        In va;         // the entry's value
     };
 
+    // The partners' values: by position in the column index, or, where the
+    // index keeps entries instead (lower mode), by entry of A.
+    __device__ const In* right_values() const {
+        return static_cast<const In*>(LOWER && a.cx.ke ? a.val : a.cx.val);
+    }
+    // key word of a position, and (plus-times) where the partner's value is
+    __device__ void partner(uint32_t pos, uint32_t& key, uint32_t& src) const {
+        if constexpr (kVal && LOWER) {
+            if (a.cx.ke) {
+                const uint2 q = a.cx.ke[pos];
+                key = q.x;
+                src = q.y;
+                return;
+            }
+        }
+        key = a.cx.key[pos];
+        src = pos;
+    }
+
     template <int S>
-    __device__ Group fetch(uint32_t g, uint32_t end, uint32_t ebase) const {
+    __device__ Group fetch(int lane, uint32_t g, uint32_t end, uint32_t ebase) const {
         Group f;
         const uint32_t idx = g + uint32_t(lane / S), o = uint32_t(lane % S);
         f.info = L.ord[min(idx, end - 1u)];
@@ -163,29 +195,28 @@ struct Chunk {
         const uint32_t d = f.live ? L.d[slot] : kNoRun;
         // the run that holds this product starts at the nearest marked lane
         // (a row's first product always starts one)
-        const int src = 63 - __clzll((long long)(__ballot(d != kNoRun) & upto));
+        const int src = 63 - __clzll((long long)(__ballot(d != kNoRun) & lanes_upto(lane)));
         const uint32_t pos = uint32_t(__shfl(int(d), src, kWave)) + slot;
-        f.key = 0;
-        f.va = f.vb = In(0);
+        f.key = f.src = 0;
+        f.va = In(0);
         if (f.live) {
-            f.key = a.cx.key[pos];
-            if constexpr (kVal) {
-                f.va = static_cast<const In*>(a.val)[ebase + L.x[slot - uint32_t(lane - src)]];
-                f.vb = static_cast<const In*>(a.cx.val)[pos];
-            }
+            partner(pos, f.key, f.src);
+            if constexpr (kVal) f.va = static_cast<const In*>(a.val)[ebase + L.x[slot - uint32_t(lane - src)]];
         }
         return f;
     }
 
     template <int S>
-    __device__ void finish(const Group& f) const {
+    __device__ void finish(int lane, const wsort::Sides& sides, const Group& f) const {
         const uint32_t o = uint32_t(lane % S);
         const uint32_t p = (f.info >> 11) & 0x3ffu, row = f.info >> 21;
+        In vb = In(0);
+        if constexpr (kVal) vb = f.live ? right_values()[f.src] : In(0);  // (in flight during the sort)
         Key k = f.live ? sort_key(f.key, o) : kDead;
         k = wsort::sort_segments<S>(k, sides);
         double v = 0.0;
         if constexpr (kVal)
-            v = __shfl(double(f.va) * double(f.vb), int((uint32_t(lane) & ~uint32_t(S - 1)) | (index_of(k) & uint32_t(S - 1))),
+            v = __shfl(double(f.va) * double(vb), int((uint32_t(lane) & ~uint32_t(S - 1)) | (index_of(k) & uint32_t(S - 1))),
                        kWave);
         // (the row's products fill its first p lanes before and after the sort)
         const uint32_t j = column_of(k);
@@ -201,7 +232,7 @@ struct Chunk {
         const bool head = f.live && !same;
         const uint64_t seg = S == 64 ? ~uint64_t(0) : ((uint64_t(1) << (S & 63)) - 1) << (lane & ~(S - 1));
         const uint64_t hm = __ballot(head) & seg;
-        const uint32_t rank = uint32_t(__popcll(hm & upto)) - 1u;  // (heads)
+        const uint32_t rank = uint32_t(__popcll(hm & lanes_upto(lane))) - 1u;  // (heads)
         const uint64_t above = (hm >> lane) >> 1;
         const uint32_t cnt = above ? uint32_t(__ffsll((long long)above)) : p - o;
         if constexpr (kVal) {
@@ -220,11 +251,13 @@ struct Chunk {
     __device__ void short_rows(uint32_t begin, uint32_t end, uint32_t ebase) const {
         if (begin >= end) return;
         constexpr uint32_t kSide = kWave / S;
-        Group f = fetch<S>(begin, end, ebase);
+        const int lane = fresh_lane();
+        const wsort::Sides sides(lane);
+        Group f = fetch<S>(lane, begin, end, ebase);
         for (uint32_t g = begin; g < end; g += kSide) {
             Group n = f;
-            if (g + kSide < end) n = fetch<S>(g + kSide, end, ebase);  // (in flight during the sort)
-            finish<S>(f);
+            if (g + kSide < end) n = fetch<S>(lane, g + kSide, end, ebase);  // (in flight during the sort)
+            finish<S>(lane, sides, f);
             f = n;
         }
     }
@@ -232,22 +265,22 @@ struct Chunk {
     // Key word and (plus-times) factors of product o of a row whose slots
     // start at s0, every lane of one register; dc and sc carry the last run
     // begun before this register (its word and slot).
-    __device__ Group fetch_at(uint32_t s0, uint32_t o, uint32_t p, uint32_t ebase, uint32_t& dc, uint32_t& sc,
-                              uint32_t& pos, uint32_t& x) const {
+    __device__ Group fetch_at(int lane, uint32_t s0, uint32_t o, uint32_t p, uint32_t ebase, uint32_t& dc, uint32_t& sc,
+                              uint32_t& x) const {
         Group f;
         f.info = 0;
         f.live = o < p;
         const uint32_t slot = s0 + o;
         const uint32_t d = f.live ? L.d[slot] : kNoRun;
-        const uint64_t marks = __ballot(d != kNoRun), lm = marks & upto;
+        const uint64_t marks = __ballot(d != kNoRun), lm = marks & lanes_upto(lane);
         const int src = 63 - __clzll((long long)lm);
         const uint32_t dd = uint32_t(__shfl(int(d), src, kWave));
-        pos = (lm ? dd : dc) + slot;
+        const uint32_t pos = (lm ? dd : dc) + slot;
         x = 0;
-        f.key = 0;
-        f.va = f.vb = In(0);
+        f.key = f.src = 0;
+        f.va = In(0);
         if (f.live) {
-            f.key = a.cx.key[pos];
+            partner(pos, f.key, f.src);
             if constexpr (kVal) x = L.x[lm ? slot - uint32_t(lane - src) : sc];
         }
         if (marks) {
@@ -261,31 +294,36 @@ struct Chunk {
     // ---- rows of 65 to 128 products, one at a time in two registers
 
     __device__ void pair_rows(uint32_t begin, uint32_t end, uint32_t ebase) const {
-        for (uint32_t g = begin; g < end; ++g) pair_row(uint32_t(__builtin_amdgcn_readfirstlane(int(L.ord[g]))), ebase);
+        if (begin >= end) return;
+        const int lane = fresh_lane();
+        const wsort::Sides sides(lane);
+        for (uint32_t g = begin; g < end; ++g)
+            pair_row(lane, sides, uint32_t(__builtin_amdgcn_readfirstlane(int(L.ord[g]))), ebase);
     }
 
-    __device__ void pair_row(uint32_t info, uint32_t ebase) const {
+    __device__ void pair_row(int lane, const wsort::Sides& sides, uint32_t info, uint32_t ebase) const {
         const uint32_t s0 = info & 0x7ffu, p = (info >> 11) & 0x3ffu, row = info >> 21;
         const uint32_t o1 = uint32_t(kWave + lane);
         Key k[2];
         double t[2] = {0.0, 0.0};
         {
-            uint32_t dc = 0, sc = 0, pos[2], x[2];
+            uint32_t dc = 0, sc = 0, x[2];
             Group f[2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) f[u] = fetch_at(s0, uint32_t(u * kWave + lane), p, ebase, dc, sc, pos[u], x[u]);
+            for (int u = 0; u < 2; ++u) f[u] = fetch_at(lane, s0, uint32_t(u * kWave + lane), p, ebase, dc, sc, x[u]);
+            In vb[2] = {In(0), In(0)};
             if constexpr (kVal) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
                     if (f[u].live) {
                         f[u].va = static_cast<const In*>(a.val)[ebase + x[u]];
-                        f[u].vb = static_cast<const In*>(a.cx.val)[pos[u]];
+                        vb[u] = right_values()[f[u].src];
                     }
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 k[u] = f[u].live ? sort_key(f[u].key, uint32_t(u * kWave + lane)) : kDead;
-                if constexpr (kVal) t[u] = double(f[u].va) * double(f[u].vb);
+                if constexpr (kVal) t[u] = double(f[u].va) * double(vb[u]);
             }
         }
         wsort::sort_regs<2>(k, sides);
@@ -332,8 +370,8 @@ struct Chunk {
             }
         }
         const uint32_t n0 = uint32_t(__popcll(hm0));
-        if (head0) emit(out + __popcll(hm0 & upto) - 1, k[0], cnt0, v[0], len_i);
-        if (head1) emit(out + n0 + uint32_t(__popcll(hm1 & upto)) - 1, k[1], cnt1, v[1], len_i);
+        if (head0) emit(out + __popcll(hm0 & lanes_upto(lane)) - 1, k[0], cnt0, v[0], len_i);
+        if (head1) emit(out + n0 + uint32_t(__popcll(hm1 & lanes_upto(lane))) - 1, k[1], cnt1, v[1], len_i);
         if (lane == 0) L.cnt[row] = uint16_t(n0 + uint32_t(__popcll(hm1)));
     }
 
@@ -341,19 +379,22 @@ struct Chunk {
     // in a register at a time, merged in LDS (few registers, rolled loops)
 
     __device__ void long_rows(uint32_t begin, uint32_t end, uint32_t ebase) const {
+        if (begin >= end) return;
+        const int lane = fresh_lane();
+        const wsort::Sides sides(lane);
         for (uint32_t g = begin; g < end; ++g) {
             wave_sync();
-            long_row(uint32_t(__builtin_amdgcn_readfirstlane(int(L.ord[g]))), ebase);
+            long_row(lane, sides, uint32_t(__builtin_amdgcn_readfirstlane(int(L.ord[g]))), ebase);
         }
     }
 
-    // value of product o of the row (its position and entry kept at its slot)
+    // value of a product (its entry and its partner's place kept at its slot)
     __device__ double term(uint32_t slot, uint32_t ebase) const {
         return double(static_cast<const In*>(a.val)[ebase + L.x[slot]]) *
-               double(static_cast<const In*>(a.cx.val)[L.d[slot]]);
+               double(right_values()[L.d[slot]]);
     }
 
-    __device__ void long_row(uint32_t info, uint32_t ebase) const {
+    __device__ void long_row(int lane, const wsort::Sides& sides, uint32_t info, uint32_t ebase) const {
         const uint32_t s0 = info & 0x7ffu, p = (info >> 11) & 0x3ffu, row = info >> 21;
         Key* K;
         if constexpr (WaveLds<kVal, Key>::kOwnKeys)
@@ -363,14 +404,14 @@ struct Chunk {
         uint32_t dc = 0, sc = 0;
 #pragma unroll 1
         for (uint32_t o = uint32_t(lane); o < ((p + 63u) & ~63u); o += kWave) {
-            uint32_t pos, x;
-            const Group f = fetch_at(s0, o, p, ebase, dc, sc, pos, x);
+            uint32_t x;
+            const Group f = fetch_at(lane, s0, o, p, ebase, dc, sc, x);
             Key k = f.live ? sort_key(f.key, o) : kDead;
             k = wsort::sort64(k, sides);
             if (f.live) {
                 K[o] = k;
                 if constexpr (kVal) {
-                    L.d[s0 + o] = pos;
+                    L.d[s0 + o] = f.src;
                     // (a run reaching into the next registers is looked up
                     // at its slot again: its first slot keeps its entry)
                     L.x[s0 + o] = uint16_t(x);
@@ -437,7 +478,7 @@ struct Chunk {
                     if (column_of(n) != j) break;
                     if constexpr (kVal) v += term(s0 + index_of(n), ebase);
                 }
-                emit(out + heads + uint32_t(__popcll(hm & upto)) - 1, k, cnt, v, len_i);
+                emit(out + heads + uint32_t(__popcll(hm & lanes_upto(lane))) - 1, k, cnt, v, len_i);
             }
             heads += uint32_t(__popcll(hm));
         }
@@ -447,6 +488,7 @@ struct Chunk {
     // Entries [eb, eb + ne) of the batch: their runs marked at their first
     // product slots (nprod slots).
     __device__ void mark_runs(uint32_t eb, int ne, int nprod) const {
+        const int lane = fresh_lane();
         for (int q = 4 * lane; q < nprod; q += 4 * kWave)
             *reinterpret_cast<uint4*>(L.d + q) = make_uint4(kNoRun, kNoRun, kNoRun, kNoRun);
         wave_sync();
@@ -481,10 +523,11 @@ struct Chunk {
     // loaded in one round, ahead of the chunk.
     struct Head {
         int64_t ubv = 0;
-        uint64_t pr = 0;
+        uint32_t pr = 0;  // (over the light rows' limit: kFP + 1)
         uint32_t rpv = 0, rpn = 0;  // the row's entries
     };
     __device__ Head head(int64_t c) const {
+        const int lane = lane0;
         const int R = a.rows_per_chunk;
         const int64_t rs = c * R;
         const int nr = int(min(int64_t(R), a.m - rs));
@@ -492,7 +535,7 @@ struct Chunk {
         if (lane < nr) {
             h.rpv = uint32_t(a.rp[rs + lane]);  // (entries of A are below 2^31)
             h.rpn = uint32_t(a.rp[rs + lane + 1]);
-            h.pr = a.prod[rs + lane];
+            h.pr = uint32_t(min(a.prod[rs + lane], (unsigned long long)(kFP + 1)));
             h.ubv = a.ubp[rs + lane];
         }
         return h;
@@ -502,6 +545,7 @@ struct Chunk {
     // lanes per row, two groups of eight rows at a time, the first 32 entries
     // of each in one round of loads.
     __device__ double diagonals(uint32_t rpv, int nr) const {
+        const int lane = fresh_lane();
         double mine = 0.0;
         const uint32_t sub = uint32_t(lane) & 7u;
         constexpr int kU = 4;
@@ -536,12 +580,13 @@ struct Chunk {
     }
 
     __device__ void run(int64_t c, const Head& h) {
+        const int lane = lane0;
         const int R = a.rows_per_chunk;
         r0 = c * R;
         const int nr = int(min(int64_t(R), a.m - r0));
         const uint32_t len = h.rpn - h.rpv;
-        const bool light = lane < nr && h.pr <= uint64_t(kFP) && len <= uint32_t(kFE);
-        const uint32_t p = light ? uint32_t(h.pr) : 0u;
+        const bool light = lane < nr && h.pr <= uint32_t(kFP) && len <= uint32_t(kFE);
+        const uint32_t p = light ? h.pr : 0u;
         L.out[lane] = h.ubv;
         L.cnt[lane] = 0;
         L.len[lane] = light ? uint16_t(len) : uint16_t(0);
@@ -570,7 +615,7 @@ struct Chunk {
             for (int k = 0; k < 6; ++k) {
                 const bool in = q > (k ? kMost[k ? k - 1 : 0] : 0u) && q <= kMost[k];
                 const uint64_t m = __ballot(in);
-                if (in) L.ord[at[k] + uint32_t(__popcll(m & upto)) - 1u] = info;
+                if (in) L.ord[at[k] + uint32_t(__popcll(m & lanes_upto(lane))) - 1u] = info;
                 at[k + 1] = at[k] + uint32_t(__popcll(m));
             }
             wave_sync();
@@ -658,12 +703,15 @@ __device__ void all_chunks(const FusedArgs& a) {
 }
 
 // (Jaccard off the diagonal has no packed words)
+// (six wavefronts per SIMD, 80 VGPRs; plus-times five, 96)
 template <int SR, bool LOWER>
-__global__ __launch_bounds__(kWave* kWavesF) void fused_kernel(FusedArgs a) {
+__global__ __launch_bounds__(kWave* kWavesF) __attribute__((amdgpu_waves_per_eu(SR == kF64 || SR == kF32 ? 5 : 6)))
+void fused_kernel(FusedArgs a) {
     all_chunks<SR, LOWER, SR == kJaccard && !LOWER>(a);
 }
 template <int SR, bool LOWER>
-__global__ __launch_bounds__(kWave* kWavesF) void fused_wide(FusedArgs a) {
+__global__ __launch_bounds__(kWave* kWavesF) __attribute__((amdgpu_waves_per_eu(4)))
+void fused_wide(FusedArgs a) {
     all_chunks<SR, LOWER, true>(a);
 }
 

@@ -770,8 +770,12 @@ __device__ inline void emit_entry(const LocalPack& pk, int64_t pos, uint32_t fie
                      static_cast<int32_t*>(pk.val) + pos);
         }
     } else {
-        nt_store(row, pk.key + pos);
-        if constexpr (VB != 0) nt_store(v, static_cast<typename ValT<VB>::T*>(pk.val) + pos);
+        if (VB != 0 && pk.ke) {
+            nt_store((uint64_t(ent) << 32) | row, reinterpret_cast<uint64_t*>(pk.ke) + pos);
+        } else {
+            nt_store(row, pk.key + pos);
+            if constexpr (VB != 0) nt_store(v, static_cast<typename ValT<VB>::T*>(pk.val) + pos);
+        }
     }
     if (pk.run && pos > cstart) set_run(pk.run, ent, uint32_t(cstart), uint32_t(pos));
 }
@@ -863,7 +867,7 @@ __device__ inline uint32_t pack_group_lds(const uint32_t* __restrict__ kx, const
             if constexpr (CARRY)
                 vv[k] = ev[k];
             else
-                vv[k] = entry_value<VB>(pk, ev[k]);
+                vv[k] = pk.ke ? 0 : entry_value<VB>(pk, ev[k]);
         }
     const uint32_t hi = kx[b0] & ~lmask;  // the group's high column bits
 #pragma unroll
@@ -917,7 +921,7 @@ __device__ inline uint32_t pack_group_global(uint32_t* __restrict__ kx, uint32_t
                 v = es[b0 + j];
             } else {
                 ent = es[b0 + j];
-                v = entry_value<VB>(pk, ent);
+                v = pk.ke ? 0 : entry_value<VB>(pk, ent);
             }
             emit_entry<VB, JAC>(pk, b0 + j, rs[b0 + j], ent, b0 + cstart, v, last, col);
         }

@@ -362,7 +362,32 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(T* __restrict__ dst, con
         dst[p] = src[idx[p]];
 }
 
+template <typename T>
+__global__ __launch_bounds__(kBlock) void split_index_kernel(const uint2* __restrict__ ke, int64_t n,
+                                                             const T* __restrict__ src, uint32_t* __restrict__ key,
+                                                             T* __restrict__ val, uint32_t* __restrict__ vsrc) {
+    for (int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x; p < n; p += int64_t(gridDim.x) * kBlock) {
+        const uint2 q = ke[p];
+        key[p] = q.x;
+        val[p] = src[q.y];
+        if (vsrc) vsrc[p] = q.y;
+    }
+}
+
 }  // namespace
+
+void split_index(const uint2* ke, int64_t n, const void* src, int vb, uint32_t* key, void* val, uint32_t* vsrc,
+                 hipStream_t s) {
+    if (n <= 0) return;
+    int64_t blocks = (n + kBlock - 1) / kBlock;
+    if (blocks > 65536) blocks = 65536;
+    if (vb == 8)
+        split_index_kernel<<<unsigned(blocks), kBlock, 0, s>>>(ke, n, static_cast<const uint64_t*>(src), key,
+                                                               static_cast<uint64_t*>(val), vsrc);
+    else
+        split_index_kernel<<<unsigned(blocks), kBlock, 0, s>>>(ke, n, static_cast<const uint32_t*>(src), key,
+                                                               static_cast<uint32_t*>(val), vsrc);
+}
 
 void gather_values(void* dst, const void* src, const uint32_t* idx, int64_t n, int vb, hipStream_t s) {
     if (n <= 0) return;
