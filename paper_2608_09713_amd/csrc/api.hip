@@ -219,7 +219,8 @@ struct Ctl {
     unsigned long long heavy_sums[2];  // entries of A and output entries of the heavy rows
     unsigned long long chunk_counter;
     unsigned long long maxlen;  // largest row length of the left operand
-    int64_t pad[1];
+    int32_t dense_count;        // rows of at least kDenseProducts products
+    int32_t pad[1];
 };
 
 struct HostCtl {
@@ -505,6 +506,7 @@ struct LowerPlan {
     int64_t nheavy = 0;
     int64_t* heavy_nnz = nullptr;
     uint32_t* cursor = nullptr;
+    DenseArgs dense;  // (its cells and counts; nrows 0 without such rows)
     Ctl* ctl = nullptr;
     int64_t* c_rp = nullptr;
     int64_t total = 0;
@@ -522,6 +524,17 @@ struct LowerPlan {
 bool index_keeps_entries(const DevCsr& B, int sr) {
     if ((sr != kF64 && sr != kF32) || B.nnz <= 0 || B.nnz > B.n) return false;
     return local_bits(B.nnz, bit_width_u64(B.n > 1 ? uint64_t(B.n - 1) : 0)) > 0;
+}
+
+// Whether the ndense rows of at least kDenseProducts products go by cells
+// (lower mode): their products are to outnumber the entries, which a pass
+// over all of them (the table of column cells) has to pay for, and the cells
+// of a row are to be few (4 M rows: 256 cells).  SPSYRK_DENSE_ROWS=0 (read at
+// every call) turns it off.
+bool use_dense(int64_t ndense, int64_t nnz, int64_t m) {
+    const char* e = std::getenv("SPSYRK_DENSE_ROWS");
+    if (e && e[0] == '0') return false;
+    return ndense > 0 && m <= (int64_t(1) << 22) && ndense * int64_t(kDenseProducts) >= nnz;
 }
 
 // The buffers build_index takes for the column index of B in lower mode
@@ -612,7 +625,7 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         Phase ph(SPSYRK_PHASE_RUNS, s);
         row_products(L.rp, m, L.nnz, run, ptmp, prod, s, vrows);
         classify_rows(L.rp, prod, m, lower, heavy_rows, &ctl->heavy_count, &ctl->light_cap, &ctl->products, ub, s,
-                      &ctl->maxlen);
+                      &ctl->maxlen, lower ? &ctl->dense_count : nullptr);
     }
     check_launch();
     // the row classes go to the host; the scan of the staging slots needs
@@ -651,6 +664,30 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         check_launch();
         ar.release(otmp);
     }
+    // The rows with the most products, the first of the ordered list, go by
+    // cells (dense.hip), where their products outweigh a pass over the
+    // entries for the table of column cells (their count is a lower bound).
+    DenseArgs da;
+    const int64_t ndense = h.dense_count;
+    if (lower && use_dense(ndense, L.nnz, m)) {
+        da.rp = L.rp;
+        da.val = L.v;
+        da.cx = cx;
+        da.run = run;
+        da.sr = sr;
+        da.rows = heavy_rows;
+        da.nrows = int(ndense);
+        da.ncells = dense_cells(m);
+        da.blk_log = dense_block_log(L.nnz, m);
+        const int64_t nblk = dense_blocks(L.nnz, da.blk_log);
+        da.cells = ar.get_t<uint32_t>(nblk * da.ncells);
+        da.count = ar.get_t<uint32_t>(ndense * da.ncells);
+        uint32_t* owner = ar.get_t<uint32_t>(nblk);
+        Phase ph(SPSYRK_PHASE_HEAVY_SYMBOLIC, s);
+        dense_table(da, m, L.nnz, owner, s);
+        check_launch();
+        ar.release(owner);
+    }
     if (nheavy > 0) {
         heavy_nnz = ar.get_t<int64_t>(m);
         ha.m = m;
@@ -664,13 +701,16 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         ha.sr = sr;
         ha.heavy_rows = heavy_rows;
         ha.heavy_count = &ctl->heavy_count;
-        ha.heavy_max = nheavy;
+        ha.heavy_first = da.nrows;
+        ha.heavy_max = nheavy - da.nrows;
         ha.row_nnz = heavy_nnz;
         ha.run = run;
         ha.runs_ready = true;
         ha.cursor = ar.get_t<uint32_t>(L.nnz);
         ha.rend = ar.get_t<uint32_t>(L.nnz);
+        da.row_nnz = heavy_nnz;
         Phase ph(SPSYRK_PHASE_HEAVY_SYMBOLIC, s);
+        dense_symbolic(da, s);
         heavy_symbolic(ha, &ctl->queue, s);
     }
     check_launch();
@@ -762,6 +802,10 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         ha.c_val = c_val;
         {
             Phase ph(SPSYRK_PHASE_HEAVY_NUMERIC, s);
+            da.c_rp = c_rp;
+            da.c_ci = c_ci;
+            da.c_val = c_val;
+            dense_numeric(da, s);
             heavy_numeric(ha, &ctl->queue, s);
         }
         check_launch();
@@ -790,6 +834,11 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
             plan->cursor = static_cast<uint32_t*>(ar.keep(ha.cursor));
             plan->rend = static_cast<uint32_t*>(ar.keep(ha.rend));
         }
+        if (da.nrows > 0) {
+            ar.keep(da.cells);
+            ar.keep(da.count);
+        }
+        plan->dense = da;
         plan->ctl = static_cast<Ctl*>(ar.keep(ctl));
         plan->c_rp = ar.get_t<int64_t>(m + 1, true);
         HIPCHK(hipMemcpyAsync(plan->c_rp, c_rp, size_t(m + 1) * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
@@ -1325,7 +1374,8 @@ void lower_execute(const LowerPlan& P, const void* vals, Arena& ar, hipStream_t 
         ha.sr = P.sr;
         ha.heavy_rows = P.heavy_rows;
         ha.heavy_count = &P.ctl->heavy_count;
-        ha.heavy_max = P.nheavy;
+        ha.heavy_first = P.dense.nrows;
+        ha.heavy_max = P.nheavy - P.dense.nrows;
         ha.row_nnz = P.heavy_nnz;
         ha.run = P.run;
         ha.runs_ready = true;
@@ -1334,7 +1384,17 @@ void lower_execute(const LowerPlan& P, const void* vals, Arena& ar, hipStream_t 
         ha.c_rp = c_rp;
         ha.c_ci = c_ci;
         ha.c_val = c_val;
+        DenseArgs da = P.dense;
+        da.rp = P.rp;
+        da.val = vals;
+        da.cx = P.cx;
+        da.run = P.run;
+        da.rows = P.heavy_rows;
+        da.c_rp = c_rp;
+        da.c_ci = c_ci;
+        da.c_val = c_val;
         Phase ph(SPSYRK_PHASE_HEAVY_NUMERIC, s);
+        dense_numeric(da, s);
         heavy_numeric(ha, &P.ctl->queue, s);
     }
     check_launch();
@@ -1716,6 +1776,7 @@ spsyrk_status spsyrk_lower_plan(const spsyrk_csr* A, spsyrk_semiring sr, const s
                         static_cast<void*>(lp.prod), static_cast<void*>(lp.cx.ke), static_cast<void*>(lp.cx.key), lp.cx.val,
                         static_cast<void*>(lp.vsrc), static_cast<void*>(lp.heavy_rows),
                         static_cast<void*>(lp.heavy_nnz), static_cast<void*>(lp.cursor),
+                        static_cast<void*>(lp.dense.cells), static_cast<void*>(lp.dense.count),
                         static_cast<void*>(lp.ctl), static_cast<void*>(lp.c_rp)})
             if (q) h->bufs.push_back(q);
         made = h;

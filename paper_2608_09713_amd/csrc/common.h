@@ -62,6 +62,10 @@ __host__ __device__ inline int bit_width_u64(uint64_t x) { return x ? 64 - __bui
 
 __device__ inline int lane_id() { return __lane_id(); }
 
+// a value that is the same in every lane, as a scalar: loops and lane reads
+// controlled by it then cost no execution-mask handling
+__device__ inline uint32_t uniform(uint32_t v) { return uint32_t(__builtin_amdgcn_readfirstlane(int(v))); }
+
 // 16 bytes read once: a streamed load that does not displace cached lines
 __device__ inline uint4 nt_load4(const void* p) {
     typedef unsigned int v4 __attribute__((ext_vector_type(4)));

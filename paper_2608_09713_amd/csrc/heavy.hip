@@ -8,64 +8,63 @@
 // position among the row's output entries, so the window's column indices are
 // written straight from the bitmap, in order.  The values are then summed in
 // LDS over the compacted ranks (tiles of kAcc ranks), so the accumulator only
-// spans columns that occur.  Every partner run is sorted by row, so each run
-// is consumed front to back through a per-entry cursor: a short stretch of a
-// run by a group of kGrp lanes, a long one by a whole wavefront, both over
-// contiguous keys.
+// spans columns that occur.
+//
+// Every partner run is sorted by row, so the part of it that falls into a
+// window or a tile is a stretch of consecutive positions: its end is found by
+// binary search, and the stretches of the row's entries, laid end to end, are
+// shared out evenly over the wavefronts (stretches.h).  What bounds a row are
+// its chains of dependent loads (a search is about ten, each a miss in L2)
+// and LDS traffic: marks and values run at about 300 G products/s each.  The
+// rows of 2^17 products and more go to dense.hip in lower mode; together the
+// two numeric passes take 30 ms on R-MAT scale 19 in f32 (57 ms with one
+// workgroup for every row, whose largest rows set its length).
 //
 // The symbolic pass builds the bitmaps only and counts the row's columns; the
 // numeric pass rebuilds them, writes the column indices and the values.
 #include "common.h"
 #include "internal.h"
 #include "lookup.h"
+#include "stretches.h"
 
 namespace spsyrk {
 namespace {
 
 constexpr int kHB = 512;                 // threads per workgroup
 constexpr int kHW = kHB / kWave;         // wavefronts per workgroup
-constexpr int kChunkE = 512;             // entries examined per activity round
-constexpr int kLongU = 2;                // keys per lane per step of a long walk
 constexpr int kHeavyGroups = 1024;       // workgroups of a heavy-row launch
-constexpr int kGrp = 8;                  // lanes per short stretch of a walk
 
 // Output columns per window and ranks per value tile: the symbolic pass
 // holds a 32 KiB bitmap; the numeric pass a 16 KiB bitmap, the rank of every
-// 128 columns' first column (4 KiB) and a 28 KiB value tile, about 52 KiB
-// with the activity lists, so that three workgroups share a compute unit
-// (windows of 2^17 columns measure 2% faster than 2^16 with a rank per word;
-// with twice the LDS only two workgroups fit, and rows wait longer on their
-// walks' latency).
+// 128 columns' first column (4 KiB) and an 18 or 21 KiB value tile, 52 KiB
+// with the stretches and bounds of kHB entries, so that three workgroups
+// share a compute unit.
 template <int SR, bool NUM>
 struct HeavyCfg {
     using Acc = typename SrTraits<SR>::Acc;
     static constexpr int kWin = NUM ? (1 << 17) : (1 << 18);
     static constexpr int kWords = kWin / 32;
-    static constexpr int kAcc = 28672 / int(sizeof(Acc));
+    static constexpr int kAcc = (SR == kF64 ? 18432 : 21504) / int(sizeof(Acc));
+    static constexpr int kHU = NUM && SR != kF32 ? 3 : 2;  // registers of products in flight (3 spill in f32)
 };
 
-// exclusive scan over the kHB threads of a workgroup; *total gets the sum
-__device__ inline uint32_t scan_hb(uint32_t v, uint32_t* wt, uint32_t* total) {
-    const int lane = lane_id();
-    const int w = threadIdx.x / kWave;
-    const uint32_t inc = wave_inclusive_scan(v);
-    if (lane == kWave - 1) wt[w] = inc;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-#pragma unroll
-    for (int q = 0; q < kHW; ++q) {
-        const uint32_t t = wt[q];
-        if (q < w) off += t;
-        tot += t;
+// first position in [lo, hi) whose row is at least x (hi if none)
+__device__ inline uint32_t stretch_end(const uint32_t* __restrict__ key, uint32_t rowmask, uint32_t lo, uint32_t hi,
+                                       int64_t x) {
+    if (lo >= hi || int64_t(key[hi - 1] & rowmask) < x) return hi;
+    uint32_t n = hi - 1;  // (the last one is at least x)
+    while (lo < n) {
+        const uint32_t mid = lo + (n - lo) / 2;
+        if (int64_t(key[mid] & rowmask) < x)
+            lo = mid + 1;
+        else
+            n = mid;
     }
-    __syncthreads();
-    *total = tot;
-    return off + inc - v;
+    return lo;
 }
 
 // Three workgroups of the numeric pass share a compute unit by their LDS;
-// that takes six wavefronts per SIMD, i.e. at most 80 VGPRs (with 88, only two
-// workgroups fit and the pass takes about 40% longer).
+// that takes six wavefronts per SIMD, i.e. at most 80 VGPRs.
 template <int SR, bool NUM, bool LOWER>
 __global__ __launch_bounds__(kHB) __attribute__((amdgpu_waves_per_eu(NUM ? 6 : 8)))
 void heavy_kernel(HeavyArgs a, int* queue) {
@@ -76,16 +75,21 @@ void heavy_kernel(HeavyArgs a, int* queue) {
     constexpr int kAcc = HeavyCfg<SR, NUM>::kAcc;
     constexpr int kWin = HeavyCfg<SR, NUM>::kWin;
     constexpr int kWords = HeavyCfg<SR, NUM>::kWords;
+    constexpr int kHU = HeavyCfg<SR, NUM>::kHU;
     constexpr bool kVal = (SR == kF64 || SR == kF32);
+    constexpr int kTiles = (kWin + kAcc - 1) / kAcc;  // value tiles of a window, at most
 
     __shared__ __align__(16) uint32_t bits[kWords];
     __shared__ uint32_t prefw[NUM ? kWords / 4 : 1];  // rank of the first column of each 4 words in the window
     __shared__ Acc acc[NUM ? kAcc : 1];
-    __shared__ int32_t act_short[kChunkE];
-    __shared__ int32_t act_long[kChunkE];
-    __shared__ int nshort_s, nlong_s;
+    // (the symbolic pass and the marks need no values; the numeric pass's are A's)
+    __shared__ Stretches<In, NUM && kVal, kHB, kHU> S;
+    __shared__ int32_t tile_col[NUM ? kTiles + 1 : 1];  // first column of every value tile
+    // rows of up to kHB entries: ends of the entries' stretches in the next
+    // windows, and in the next tiles of a window (boundary-major)
+    __shared__ uint32_t win_end[kHB];
+    __shared__ uint32_t tile_end[NUM ? kHB : 1];
     __shared__ int row_s;
-    __shared__ uint32_t wt[kHW];
     __shared__ double wtd[kHW];
 
     const int tid = threadIdx.x;
@@ -95,10 +99,9 @@ void heavy_kernel(HeavyArgs a, int* queue) {
     const uint32_t rowmask = a.cx.rowbits >= 32 ? 0xffffffffu : ((1u << a.cx.rowbits) - 1u);
     const int nheavy = *a.heavy_count;
 
-    // rank of column j of the current window among the window's columns
-    auto rank_of = [&](int64_t B0, uint32_t j) -> uint32_t {
+    // rank of column B0 + x among the window's columns
+    auto rank_of = [&](uint32_t x) -> uint32_t {
         if constexpr (!NUM) return 0u;  // (ranks exist in the numeric pass only)
-        const uint32_t x = uint32_t(int64_t(j) - B0);
         const uint4 q = reinterpret_cast<const uint4*>(bits)[x >> 7];
         const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
         const uint32_t k = (x >> 5) & 3u, mk = (1u << (x & 31)) - 1u;
@@ -108,141 +111,29 @@ void heavy_kernel(HeavyArgs a, int* queue) {
         return r;
     };
 
-    // Walk the partner runs of entries [c0, c1) from their cursors through
-    // the partners below column B1 (and, for values, of rank below T0 + tl):
-    // mark them in the bitmap, or add their terms to the value tile.  Short
-    // stretches (under a wavefront of partners) are walked by groups of kGrp
-    // lanes, long ones by whole wavefronts.  The cursors move if advance is set.
-    // Called by all threads.
-    auto walk = [&](int64_t c0, int64_t c1, int64_t B0, int64_t B1, bool value, uint32_t T0, uint32_t tl,
-                    bool advance) {
-        if (tid == 0) {
-            nshort_s = 0;
-            nlong_s = 0;
-        }
-        __syncthreads();
-        const uint32_t rlim = T0 + tl;
-        for (int64_t e = c0 + tid; e < c1; e += kHB) {
-            const uint32_t c = a.cursor[e];
-            const uint32_t hi = a.rend[e];
-            if (c >= hi) continue;
-            const uint32_t j = key[c] & rowmask;
-            if (int64_t(j) >= B1 || (value && rank_of(B0, j) >= rlim)) continue;
-            bool lng = c + uint32_t(kWave) <= hi;
-            if (lng) {
-                const uint32_t jl = key[c + kWave - 1] & rowmask;
-                lng = int64_t(jl) < B1 && !(value && rank_of(B0, jl) >= rlim);
-            }
-            if (lng)
-                act_long[atomicAdd(&nlong_s, 1)] = int32_t(e - c0);
-            else
-                act_short[atomicAdd(&nshort_s, 1)] = int32_t(e - c0);
-        }
-        __syncthreads();
-        const int nshort = nshort_s, nlong = nlong_s;
-        // short stretches: a group of kGrp lanes each, kGrp consecutive keys
-        // per step (the keys in range form a prefix of the stretch)
-        {
-            const int gl = lane % kGrp;
-            for (int q = tid / kGrp; q < nshort; q += kHB / kGrp) {
-                const int64_t e = c0 + act_short[q];
-                uint32_t c = a.cursor[e];
-                const uint32_t hi = a.rend[e];
-                double av = 0.0;
-                if constexpr (kVal) av = value ? double(static_cast<const In*>(a.val)[e]) : 0.0;
-                while (c < hi) {
-                    const uint32_t p = c + uint32_t(gl);
-                    const uint32_t jj = p < hi ? (key[p] & rowmask) : 0xffffffffu;
-                    bool in = false;
-                    if (int64_t(jj) < B1) {
-                        const uint32_t x = uint32_t(int64_t(jj) - B0);
-                        if (value) {
-                            const uint32_t rk = rank_of(B0, jj);
-                            in = rk >= T0 && rk < rlim;
-                            if (in) {
-                                if constexpr (NUM) {
-                                    if constexpr (kVal)
-                                        atomicAdd(&acc[rk - T0], av * double(static_cast<const In*>(a.cx.val)[p]));
-                                    else
-                                        atomicAdd(&acc[rk - T0], 1);
-                                }
-                            }
-                        } else {
-                            in = true;
-                            atomicOr(&bits[x >> 5], 1u << (x & 31));
-                        }
-                    }
-                    const uint64_t bal = __ballot(in);
-                    const uint32_t took = uint32_t(__popcll((bal >> (lane - gl)) & ((uint64_t(1) << kGrp) - 1)));
-                    c += took;
-                    if (took < uint32_t(kGrp)) break;
-                }
-                if (advance && gl == 0) a.cursor[e] = c;
-            }
-        }
-        // long stretches: a wavefront each, kLongU keys per lane per step
-        for (int q = w; q < nlong; q += kHW) {
-            const int64_t e = c0 + act_long[q];
-            uint32_t c = a.cursor[e];
-            const uint32_t hi = a.rend[e];
-            double av = 0.0;
-            if constexpr (kVal) av = value ? double(static_cast<const In*>(a.val)[e]) : 0.0;
-            while (c < hi) {
-                uint32_t jj[kLongU];
-#pragma unroll
-                for (int u = 0; u < kLongU; ++u) {
-                    const uint32_t p = c + uint32_t(u * kWave) + lane;
-                    jj[u] = p < hi ? (key[p] & rowmask) : 0xffffffffu;
-                }
-                uint32_t took = 0;
-                bool full = true;
-#pragma unroll
-                for (int u = 0; u < kLongU; ++u) {
-                    const uint32_t p = c + uint32_t(u * kWave) + lane;
-                    bool in = false;
-                    if (full && int64_t(jj[u]) < B1) {
-                        const uint32_t x = uint32_t(int64_t(jj[u]) - B0);
-                        if (value) {
-                            const uint32_t rk = rank_of(B0, jj[u]);
-                            in = rk >= T0 && rk < rlim;
-                            if (in) {
-                                if constexpr (NUM) {
-                                    if constexpr (kVal)
-                                        atomicAdd(&acc[rk - T0], av * double(static_cast<const In*>(a.cx.val)[p]));
-                                    else
-                                        atomicAdd(&acc[rk - T0], 1);
-                                }
-                            }
-                        } else {
-                            in = true;
-                            atomicOr(&bits[x >> 5], 1u << (x & 31));
-                        }
-                    }
-                    const uint32_t t = uint32_t(__popcll(__ballot(in)));
-                    took += t;
-                    full = full && t == uint32_t(kWave);
-                }
-                c += took;
-                if (!full) break;
-            }
-            if (advance && lane == 0) a.cursor[e] = c;
-        }
-        __syncthreads();
-    };
-
+    int next_row = -1;  // (thread 0)
+    if (tid == 0) {
+        const int h = a.heavy_first + atomicAdd(queue, 1);
+        next_row = h < nheavy ? a.heavy_rows[h] : -1;
+    }
     while (true) {
-        if (tid == 0) {
-            const int h = atomicAdd(queue, 1);
-            row_s = h < nheavy ? a.heavy_rows[h] : -1;
-        }
+        if (tid == 0) row_s = next_row;
         __syncthreads();
-        const int i = row_s;
+        const int i = int(uniform(uint32_t(row_s)));
         __syncthreads();
         if (i < 0) break;
+        if (tid == 0) next_row = a.heavy_first + atomicAdd(queue, 1);  // (the next row's place, used at this row's end)
         const int64_t e0 = a.rp[i], e1 = a.rp[i + 1];
         const int64_t E = e1 - e0;
+        // Rows of up to kHB entries keep an entry per thread: the start of its
+        // stretch stays in a register, and the idle threads search the ends in several windows or tiles at once (a
+        // search is a chain of about ten loads, each of them a miss in L2).
+        // Longer rows go through the entries kHB at a time, with the starts
+        // and the windows' ends in memory.
+        const bool small = E <= kHB;
+        uint32_t start = 0;  // (small rows) the stretch's start
 
-        // partner runs and cursors
+        // partner runs, and every entry's next position
         uint64_t prod_local = 0;
         for (int64_t e = e0 + tid; e < e1; e += kHB) {
             uint2 rr;
@@ -255,40 +146,90 @@ void heavy_kernel(HeavyArgs a, int* queue) {
             } else {
                 rr = run_of(a.run, e);
             }
-            a.cursor[e] = rr.x;
-            a.rend[e] = rr.y;
+            if (small) {
+                start = rr.x;
+            } else {
+                a.cursor[e] = rr.x;
+            }
         }
         if constexpr (!NUM) {
             const uint64_t tot = wave_reduce_sum(prod_local);
             if (lane == 0 && tot && a.products) atomicAdd(a.products, (unsigned long long)tot);
         }
-        __threadfence_block();
+        const int per_group = small ? kHB / int(E) : 1;  // boundaries searched at once
+        if (!NUM && !a.runs_ready) __threadfence_block();
         __syncthreads();
 
         const int64_t jmax = LOWER ? int64_t(i) : a.m_right;
+        const int64_t nwin = (jmax + kWin - 1) / kWin;
         int64_t count = 0;                          // symbolic: distinct columns so far
         int64_t outp = NUM ? a.c_rp[i] : 0;         // numeric: first output slot of the window
-        for (int64_t B0 = 0; B0 < jmax; B0 += kWin) {
+        for (int64_t k = 0; k < nwin; ++k) {
+            const int64_t B0 = k * kWin;
             const int64_t B1 = min(jmax, B0 + int64_t(kWin));
             const int nw = int((B1 - B0 + 31) >> 5);
             for (int x = tid; x < nw; x += kHB) bits[x] = 0;
-            __syncthreads();
+            // (each entry of a long row is one thread's from here on: its own
+            // writes to the cursor and the window's end are the ones it reads)
+            const int kg = small ? int(k % per_group) : 0;  // the window in its group
+            if (small && kg == 0 && k + 1 < nwin) {
+                // ends at the next per_group window ends, the last one left
+                // out: thread tid searches boundary tid / E for entry tid % E
+                const int eg = tid / int(E), ee = tid - eg * int(E);
+                if (eg < per_group && k + 1 + eg < nwin) {
+                    const uint2 r = run_of(a.run, e0 + ee);
+                    win_end[tid] = stretch_end(key, rowmask, r.x, r.y, (k + 1 + eg) * kWin);
+                }
+                __syncthreads();
+            }
 
-            // mark the window's columns; the numeric pass walks the runs again
-            // for the values, so only the symbolic pass moves the cursors here
-            for (int64_t c0 = e0; c0 < e1; c0 += kChunkE)
-                walk(c0, min(e1, c0 + int64_t(kChunkE)), B0, B1, false, 0u, 0u, !NUM);
+            // mark the window's columns; the numeric pass keeps the starts
+            // for the values and notes where the window's stretch ends
+            uint32_t wend = 0;
+            auto mark = [&](uint32_t t, uint32_t te, const uint32_t(&pos)[kHU], const In(&)[kHU]) {
+                uint32_t j[kHU];
+#pragma unroll
+                for (int u = 0; u < kHU; ++u) j[u] = t + uint32_t(u * kWave) + lane < te ? key[pos[u]] & rowmask : 0u;
+#pragma unroll
+                for (int u = 0; u < kHU; ++u) {
+                    if (t + uint32_t(u * kWave) + lane < te) {
+                        const uint32_t x = uint32_t(int64_t(j[u]) - B0);
+                        atomicOr(&bits[x >> 5], 1u << (x & 31));
+                    }
+                }
+            };
+            for (int64_t c0 = e0; c0 < e1; c0 += kHB) {  // (once for a small row)
+                const int64_t e = c0 + tid;
+                uint32_t lo = start, hi = wend;
+                if (small) {
+                    if (tid < E) hi = wend = k + 1 < nwin ? win_end[kg * int(E) + tid] : run_of(a.run, e).y;
+                } else {
+                    lo = hi = 0;
+                    if (e < e1) {
+                        lo = a.cursor[e];
+                        hi = run_of(a.run, e).y;
+                        if (B1 < jmax) hi = stretch_end(key, rowmask, lo, hi, B1);
+                        if constexpr (NUM)
+                            a.rend[e] = hi;
+                        else
+                            a.cursor[e] = hi;
+                    }
+                }
+                S.products(lo, hi, In(0), mark);
+            }
 
             // ranks: every thread owns a contiguous stretch of words
             constexpr int kPer = (kWords + kHB - 1) / kHB;
             const int wlo = min(nw, tid * kPer), whi = min(nw, wlo + kPer);
             uint32_t s = 0;
+#pragma unroll 4
             for (int x = wlo; x < whi; ++x) s += uint32_t(__popc(bits[x]));
             uint32_t Nw;
-            uint32_t off = scan_hb(s, wt, &Nw);
+            uint32_t off = S.scan(s, &Nw);
+            Nw = uniform(Nw);
             if constexpr (!NUM) {
                 count += Nw;
-                __syncthreads();
+                start = wend;
             } else {
                 for (int x = wlo; x < whi; ++x) {
                     if ((x & 3) == 0) prefw[x >> 2] = off;
@@ -298,22 +239,74 @@ void heavy_kernel(HeavyArgs a, int* queue) {
                         const int t = __ffs(b) - 1;
                         b &= b - 1;
                         SPSYRK_CHECK(outp + off < a.c_rp[i + 1], kDbgHeavyOut);
-                        a.c_ci[outp + off] = int32_t(B0 + 32 * x + t);
+                        const int32_t j = int32_t(B0 + 32 * x + t);
+                        a.c_ci[outp + off] = j;
+                        if (off % uint32_t(kAcc) == 0) tile_col[off / uint32_t(kAcc)] = j;
                         ++off;
                     }
                 }
                 // (the barrier orders these writes for the workgroup's reads below)
                 __syncthreads();
 
-                // values over the compacted ranks, kAcc ranks at a time; an
-                // entry joins a value tile only if its next partner's rank
-                // falls inside it
-                for (uint32_t T0 = 0; T0 < Nw; T0 += uint32_t(kAcc)) {
+                // values over the compacted ranks, kAcc ranks at a time
+                const int ntile = int((Nw + uint32_t(kAcc) - 1) / uint32_t(kAcc));
+                for (int q = 0; q < ntile; ++q) {
+                    const uint32_t T0 = uint32_t(q) * uint32_t(kAcc);
                     const uint32_t tl = min(Nw - T0, uint32_t(kAcc));
                     for (uint32_t x = tid; x < tl; x += kHB) acc[x] = Acc(0);
-                    __syncthreads();
-                    for (int64_t c0 = e0; c0 < e1; c0 += kChunkE)
-                        walk(c0, min(e1, c0 + int64_t(kChunkE)), B0, B1, true, T0, tl, true);
+                    const bool last = q + 1 == ntile;
+                    auto add = [&](uint32_t t, uint32_t te, const uint32_t(&pos)[kHU], const In(&av)[kHU]) {
+                        uint32_t j[kHU];
+                        In bv[kHU];
+#pragma unroll
+                        for (int u = 0; u < kHU; ++u) {
+                            const bool in = t + uint32_t(u * kWave) + lane < te;
+                            j[u] = in ? key[pos[u]] & rowmask : 0u;
+                            bv[u] = In(0);
+                            if constexpr (kVal) bv[u] = in ? static_cast<const In*>(a.cx.val)[pos[u]] : In(0);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kHU; ++u) {
+                            if (t + uint32_t(u * kWave) + lane < te) {
+                                const uint32_t rk = rank_of(uint32_t(int64_t(j[u]) - B0)) - T0;
+                                SPSYRK_CHECK(rk < tl, kDbgHeavyOut);
+                                if constexpr (kVal)
+                                    atomicAdd(&acc[rk], double(av[u]) * double(bv[u]));
+                                else
+                                    atomicAdd(&acc[rk], 1);
+                            }
+                        }
+                    };
+                    const int qg = small ? q % per_group : 0;
+                    if (small && qg == 0 && !last) {
+                        const int eg = tid / int(E), ee = tid - eg * int(E);
+                        if (eg < per_group && q + 1 + eg < ntile) {
+                            const uint2 r = run_of(a.run, e0 + ee);
+                            tile_end[tid] = stretch_end(key, rowmask, r.x, k + 1 < nwin ? win_end[kg * int(E) + ee] : r.y,
+                                                        int64_t(tile_col[q + 1 + eg]));
+                        }
+                        __syncthreads();
+                    }
+                    for (int64_t c0 = e0; c0 < e1; c0 += kHB) {
+                        const int64_t e = c0 + tid;
+                        uint32_t lo = start, hi = wend;
+                        In val = In(0);
+                        if constexpr (kVal)
+                            if (e < e1) val = static_cast<const In*>(a.val)[e];
+                        if (small) {
+                            if (!last && tid < E) hi = tile_end[qg * int(E) + tid];
+                            start = hi;
+                        } else {
+                            lo = hi = 0;
+                            if (e < e1) {
+                                lo = a.cursor[e];
+                                hi = a.rend[e];
+                                if (!last) hi = stretch_end(key, rowmask, lo, hi, int64_t(tile_col[q + 1]));
+                                a.cursor[e] = hi;
+                            }
+                        }
+                        S.products(lo, hi, val, add);
+                    }
                     for (uint32_t x = tid; x < tl; x += kHB) {
                         const int64_t p = outp + T0 + x;
                         SPSYRK_CHECK(p < a.c_rp[i + 1], kDbgHeavyOut);
@@ -336,6 +329,7 @@ void heavy_kernel(HeavyArgs a, int* queue) {
         if constexpr (NUM) {
             if (tid == 0) SPSYRK_CHECK(outp + (LOWER ? 1 : 0) == a.c_rp[i + 1], kDbgHeavyCount);
         }
+        if (tid == 0) next_row = next_row < nheavy ? a.heavy_rows[next_row] : -1;
         // diagonal (lower triangle only; a heavy row is never empty)
         if constexpr (!NUM) {
             if (tid == 0) {

@@ -275,10 +275,11 @@ void light_fused(const FusedArgs& a, hipStream_t s);
 // the sum of prod over all rows into the two counters
 // and ub[i] = products + diagonal for light rows, 0 for heavy rows (and ub[m]
 // = 0); maxlen
-// (optional, zeroed): the largest row length
+// (optional, zeroed): the largest row length; dense_count (optional, zeroed):
+// the rows of at least kDenseProducts products
 void classify_rows(const int64_t* rp, const unsigned long long* prod, int64_t m, bool lower, int32_t* heavy_rows,
                    int32_t* heavy_count, unsigned long long* light_cap, unsigned long long* prod_sum, int64_t* ub,
-                   hipStream_t s, unsigned long long* maxlen = nullptr);
+                   hipStream_t s, unsigned long long* maxlen = nullptr, int32_t* dense_count = nullptr);
 
 // ---- runs.hip
 // Dense column starts of a CSR matrix's column-sorted copy: cptr[c] =
@@ -344,7 +345,8 @@ struct HeavyArgs {
     int sr = kF64;
     const int32_t* heavy_rows = nullptr;
     const int32_t* heavy_count = nullptr;
-    int64_t heavy_max = 0;              // upper bound of heavy rows (grid sizing)
+    int64_t heavy_max = 0;              // upper bound of the rows taken (grid sizing)
+    int heavy_first = 0;                // rows of the list left out (they go to dense.hip)
     // per-entry run bounds (sized nnz of the left operand), written by the symbolic pass
     RunTab run;                         // partner run {first, end} of every entry (r8 only
                                         // when the symbolic pass writes it)
@@ -361,6 +363,38 @@ struct HeavyArgs {
 // queue: one device int of scratch (work counter)
 void heavy_symbolic(const HeavyArgs& a, int* queue, hipStream_t s);
 void heavy_numeric(const HeavyArgs& a, int* queue, hipStream_t s);
+
+// ---- dense.hip
+// The rows with the most products (lower mode), by cells of output columns.
+// A row is dense from kDenseProducts products on; ncells = dense_cells(m).
+constexpr unsigned long long kDenseProducts = 1ull << 17;
+struct DenseArgs {
+    const int64_t* rp = nullptr;       // A
+    const void* val = nullptr;
+    ColIndex cx;
+    RunTab run;                        // partner run of every entry
+    int sr = kF64;
+    const int32_t* rows = nullptr;     // the rows
+    int nrows = 0;
+    int ncells = 0;
+    int blk_log = 5;                   // dense_block_log
+    uint32_t* cells = nullptr;         // [dense_blocks * ncells] cell starts of the long columns
+    uint32_t* count = nullptr;         // [nrows * ncells] columns, then first outputs, of every unit
+    int64_t* row_nnz = nullptr;        // [m] (symbolic)
+    const int64_t* c_rp = nullptr;
+    int32_t* c_ci = nullptr;
+    void* c_val = nullptr;
+};
+int dense_cells(int64_t m);
+// log2 of the positions per block of the table of long columns, for an index
+// of `positions` entries over m rows (a table of at most 64 MB), and its blocks
+int dense_block_log(int64_t positions, int64_t m);
+int64_t dense_blocks(int64_t positions, int blk_log);
+// fills a.cells (owner: dense_blocks words of scratch)
+void dense_table(const DenseArgs& a, int64_t m, int64_t nnz, uint32_t* owner, hipStream_t s);
+// row lengths and first outputs; then columns and values
+void dense_symbolic(const DenseArgs& a, hipStream_t s);
+void dense_numeric(const DenseArgs& a, hipStream_t s);
 
 // ---- accumulate.hip
 // Row-wise union of two lower parts P and T (m rows, canonical), in work items

@@ -755,7 +755,7 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
                                                           bool lower, int32_t* __restrict__ heavy_rows,
                                                           int32_t* heavy_count, unsigned long long* light_cap,
                                                           unsigned long long* prod_sum, int64_t* __restrict__ ub,
-                                                          unsigned long long* maxlen) {
+                                                          unsigned long long* maxlen, int32_t* dense_count) {
     __shared__ unsigned long long wt[kWavesPerBlock][3];
     unsigned long long cap = 0, ps = 0, ml = 0;
     for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < m; i += int64_t(gridDim.x) * kBlock) {
@@ -769,6 +769,7 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
             cap += u;
         } else {
             heavy_rows[atomicAdd(heavy_count, 1)] = int32_t(i);
+            if (dense_count && pr >= kDenseProducts) atomicAdd(dense_count, 1);
         }
         ub[i] = u;
     }
@@ -799,12 +800,12 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
 
 void classify_rows(const int64_t* rp, const unsigned long long* prod, int64_t m, bool lower, int32_t* heavy_rows,
                    int32_t* heavy_count, unsigned long long* light_cap, unsigned long long* prod_sum, int64_t* ub,
-                   hipStream_t s, unsigned long long* maxlen) {
+                   hipStream_t s, unsigned long long* maxlen, int32_t* dense_count) {
     if (m <= 0) return;
     int64_t grid = (m + kBlock - 1) / kBlock;
     if (grid > 1024) grid = 1024;
     classify_kernel<<<unsigned(grid), kBlock, 0, s>>>(rp, prod, m, lower, heavy_rows, heavy_count, light_cap,
-                                                      prod_sum, ub, maxlen);
+                                                      prod_sum, ub, maxlen, dense_count);
 }
 
 void light_fused(const FusedArgs& a, hipStream_t s) {

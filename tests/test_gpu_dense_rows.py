@@ -1,0 +1,83 @@
+"""Rows of 2^17 products and more, which go by cells of 2^13 output columns
+(the heavy rows' units of work otherwise being whole rows), against the
+oracle: rows on both sides of a cell's edge, columns on both sides of the
+length from which the table of cells holds them, more than 1024 entries in a
+row, and the same product with the path switched off."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2608_09713_amd as sp
+from paper_2608_09713_amd.workloads import CSR
+from tests.parity import compare_full, compare_rows
+
+pytestmark = pytest.mark.gpu
+
+VDT = {"f64": np.float64, "f32": np.float32, "count": None, "jaccard": None}
+
+
+def _matrix(seed, m, hubs, share, tail, long_rows):
+    """Hub columns held by a share of all rows, a few sparse entries per row,
+    columns of 30 to 36 and 60 to 70 entries, and long rows of 1500 entries."""
+    rng = np.random.default_rng(seed)
+    rows, cols = [], []
+    for h in range(hubs):
+        r = np.flatnonzero(rng.random(m) < share)
+        rows.append(r)
+        cols.append(np.full(len(r), h))
+    rows.append(np.repeat(np.arange(m), tail))
+    cols.append(rng.integers(hubs, hubs + 4 * m, m * tail))
+    c = hubs + 4 * m
+    for ln in list(range(30, 37)) + list(range(60, 71)):
+        r = np.sort(rng.choice(m, ln, replace=False))
+        r[-1] = m - 1
+        rows.append(r)
+        cols.append(np.full(ln, c))
+        c += 1
+    for r in long_rows:
+        rows.append(np.full(1500, r))
+        cols.append(hubs + rng.choice(4 * m, 1500, replace=False))
+    rows, cols = np.concatenate(rows), np.concatenate(cols)
+    key = np.unique(rows.astype(np.int64) * (c + 7) + cols)
+    rows, cols = key // (c + 7), key % (c + 7)
+    rp = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(np.bincount(rows, minlength=m), out=rp[1:])
+    return CSR(m, c + 7, rp, cols.astype(np.int32), rng.standard_normal(len(cols)))
+
+
+@pytest.mark.parametrize("semiring", ["f64", "f32", "count", "jaccard"])
+@pytest.mark.parametrize("m", [16384, 16385, 25000])
+def test_dense_rows(semiring, m, monkeypatch):
+    A = _matrix(m, m, 24, 0.6, 3, [m - 1, m - 2, 16000])
+    A = A.with_values(None if VDT[semiring] is None else A.values.astype(VDT[semiring]))
+    dA = sp.DeviceCSR.from_host(A, "cuda:0")
+    print(f"[{semiring}] m={m} nnz={A.nnz}", flush=True)
+    rows = np.unique(np.concatenate([np.arange(0, m, 997), [16000, 16382, 16383, m - 2, m - 1],
+                                     np.arange(16384, min(m, 16390))]))
+    ref = oracle.lower(A, semiring, rows=rows)
+    C = sp.lower(dA, semiring)
+    assert sp.stats()["heavy_rows"] > 0 and sp.stats()["products"] > 1 << 27
+    compare_rows(C, ref, rows, semiring, "lower")
+    monkeypatch.setenv("SPSYRK_DENSE_ROWS", "0")
+    D = sp.lower(dA, semiring)
+    monkeypatch.delenv("SPSYRK_DENSE_ROWS")
+    assert C.row_ptr.equal(D.row_ptr) and C.col_idx.equal(D.col_idx)
+    if VDT[semiring] is None:
+        assert C.values.equal(D.values)
+    plan, C1 = sp.lower_plan(dA, semiring)
+    compare_rows(C1, ref, rows, semiring, "plan")
+    if VDT[semiring] is None:
+        got, B = plan.execute(None), A
+    else:
+        B = A.with_values((A.values * 2 - 1).astype(VDT[semiring]))
+        got = plan.execute(sp.DeviceCSR.from_host(B, "cuda:0").values)
+    compare_rows(got, oracle.lower(B, semiring, rows=rows), rows, semiring, "execute")
+    plan.close()
+
+
+def test_dense_rows_full():
+    """Every row of a small matrix whose upper rows are dense."""
+    A = _matrix(3, 9000, 40, 0.7, 2, [8999])
+    C = sp.lower(sp.DeviceCSR.from_host(A, "cuda:0"), "f64")
+    assert sp.stats()["heavy_rows"] > 0
+    compare_full(C, oracle.lower(A, "f64"), "f64", "lower")
