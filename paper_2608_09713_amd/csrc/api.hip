@@ -82,11 +82,23 @@ class Arena {
     bool touched() const { return touched_; }
     ~Arena() { release_all(); }
 
+    // One block for the call's workspace: gets that fit come out of it, so
+    // that a call on a small matrix asks the caller's allocator for it and
+    // the outputs only (25 allocations through a Python callback cost a small
+    // call more host time than its launches).  Not for calls that keep
+    // workspace past their end (keep).  Called before the first get.
+    void use_block(size_t bytes) {
+        block_bytes_ = round(bytes);
+        block_ = static_cast<char*>(raw(block_bytes_));
+        touched_ = true;
+    }
+
     // Allocate count blocks of the given size ahead of the gets that will
     // take them (any later get of that size takes one), so that those gets
     // cost the host nothing at a point where the device waits on it.
     void reserve(size_t bytes, int count = 1) {
         bytes = round(bytes);
+        if (block_ && bytes * size_t(count) <= block_bytes_ - used_) return;  // (the block serves them as fast)
         for (int i = 0; i < count; ++i) reserved_.push_back({raw(bytes), bytes});
     }
 
@@ -100,6 +112,19 @@ class Arena {
                 (output ? outputs_ : work_).push_back(p);
                 return p;
             }
+        if (block_ && !output) {
+            for (auto& q : pieces_)  // a released piece of about the size (later work on the stream follows its use)
+                if (q.free && q.bytes >= bytes && q.bytes <= 2 * bytes) {
+                    q.free = false;
+                    return q.p;
+                }
+            if (bytes <= block_bytes_ - used_) {
+                void* p = block_ + used_;
+                used_ += bytes;
+                pieces_.push_back({p, bytes, false});
+                return p;
+            }
+        }
         void* p = raw(bytes);
         (output ? outputs_ : work_).push_back(p);
         return p;
@@ -109,6 +134,11 @@ class Arena {
         return static_cast<T*>(get(size_t(count) * sizeof(T), output));
     }
     void release(void* p) {
+        for (auto& q : pieces_)
+            if (q.p == p) {
+                q.free = true;
+                return;
+            }
         for (auto& q : work_)
             if (q == p) {
                 free_one(q);
@@ -140,6 +170,9 @@ class Arena {
             if (p) free_one(p);
         for (auto& r : reserved_)
             if (r.p) free_one(r.p);
+        if (block_) free_one(block_);
+        block_ = nullptr;
+        pieces_.clear();
         work_.clear();
         outputs_.clear();
         reserved_.clear();
@@ -175,8 +208,30 @@ class Arena {
     hipStream_t s_;
     std::vector<void*> work_, outputs_;
     std::vector<Reserved> reserved_;
+    struct Piece {
+        void* p;
+        size_t bytes;
+        bool free;
+    };
+    char* block_ = nullptr;
+    size_t block_bytes_ = 0, used_ = 0;
+    std::vector<Piece> pieces_;
     bool touched_ = false;
 };
+
+// Workspace block of a call (Arena::use_block) that needs about `bytes` of it
+// for its larger buffers: the whole of it up to 64 MB, else a block for the
+// small ones (those over the block's rest are allocated one by one, and
+// released as soon as they are spent).
+size_t work_block(size_t bytes) {
+    constexpr size_t kMost = size_t(64) << 20, kSmall = size_t(1) << 20;
+    return bytes <= kMost ? bytes + kSmall : kSmall;
+}
+// dense column starts that come out of the block too
+size_t work_columns(int64_t ncols) { return ncols < (int64_t(1) << 22) ? size_t(ncols) * 4 + 4096 : 0; }
+// the same for a product with `nnz` entries of both operands in all, m rows
+size_t product_block(int64_t nnz, int64_t m) { return work_block(size_t(nnz) * 80 + size_t(m) * 48); }
+
 
 // ---- phase timing: event pairs recorded on the call's stream
 struct PhaseMark {
@@ -1526,6 +1581,7 @@ spsyrk_status spsyrk_lower(const spsyrk_csr* A, spsyrk_semiring sr, const spsyrk
         check_semiring(int(sr));
         check_input(A, int(sr), true, "A");
         const DevCsr d = dev(A);
+        ar.use_block(product_block(d.nnz, d.m));
         syrk(d, d, true, int(sr), ar, s, C);
     });
 }
@@ -1540,6 +1596,7 @@ spsyrk_status spsyrk_offdiag(const spsyrk_csr* Ai, const spsyrk_csr* Aj, spsyrk_
             set_detail("Ai has %lld columns, Aj has %lld", (long long)Ai->ncols, (long long)Aj->ncols);
             throw Fail{SPSYRK_ERR_INVALID_ARG};
         }
+        ar.use_block(product_block(Ai->nnz + Aj->nnz, Ai->nrows) + size_t(work_columns(Aj->ncols)));
         syrk(dev(Ai), dev(Aj), false, int(sr), ar, s, C);
     });
 }
@@ -1559,6 +1616,7 @@ spsyrk_status spsyrk_offdiag_half(const spsyrk_csr* Ai, const spsyrk_csr* Aj, sp
             set_detail("unknown half %d", int(half));
             throw Fail{SPSYRK_ERR_INVALID_ARG};
         }
+        ar.use_block(product_block(Ai->nnz + Aj->nnz, Ai->nrows) + size_t(work_columns(Aj->ncols)));
         offdiag_half(dev(Ai), dev(Aj), int(half), int(sr), ar, s, C);
     });
 }
@@ -1586,6 +1644,7 @@ spsyrk_status spsyrk_symm(const spsyrk_csr* C_lower, spsyrk_semiring sr, int64_t
             throw Fail{SPSYRK_ERR_INVALID_ARG};
         }
         const DevCsr c = dev(C_lower);
+        ar.use_block(work_block(size_t(m) * size_t(k) * 8 + size_t(c.nnz) / 64));
         {
             Ctl* ctl = ar.get_t<Ctl>(1);
             zero_ctl(ctl, s);
@@ -1674,6 +1733,7 @@ spsyrk_status spsyrk_lower_accumulate(const spsyrk_csr* C_prev, const spsyrk_csr
         }
         const int64_t m = A_s->nrows;
         const DevCsr P = dev(C_prev);
+        ar.use_block(product_block(A_s->nnz + P.nnz / 16, 2 * m));
         {
             Ctl* ctl = ar.get_t<Ctl>(1);
             zero_ctl(ctl, s);
@@ -1837,6 +1897,7 @@ spsyrk_status spsyrk_mirror(const spsyrk_csr* C_lower, spsyrk_semiring sr, const
                        (long long)C_lower->ncols);
             throw Fail{SPSYRK_ERR_INVALID_ARG};
         }
+        ar.use_block(work_block(size_t(C_lower->nnz) * 26 + size_t(C_lower->nrows) * 40));
         mirror(dev(C_lower), int(sr), ar, s, C_full);
     });
 }
