@@ -35,7 +35,10 @@ __global__ __launch_bounds__(kBlock) void pack(const uint32_t* __restrict__ scol
                                                bool drop_last, int gs, int rowbits, int lenbits, int64_t ngroups,
                                                const int64_t* __restrict__ nkept, const int64_t* __restrict__ rp_b,
                                                uint32_t* __restrict__ key, void* __restrict__ val,
-                                               uint32_t* __restrict__ gptr, uint32_t* __restrict__ vsrc) {
+                                               uint32_t* __restrict__ gptr, uint32_t* __restrict__ vsrc,
+                                               const uint32_t* __restrict__ ncols, int64_t* __restrict__ kept_out) {
+    // (without a directory, which reads it, the kept count is written here)
+    if (kept_out && blockIdx.x == 0 && threadIdx.x == 0) *kept_out = drop_last ? n - int64_t(*ncols) : n;
     __shared__ int64_t colstart[kPTile];
     __shared__ uint32_t excl[kPTile];  // column starts before each position
     __shared__ int64_t wt[kWavesPerBlock];
@@ -200,10 +203,11 @@ void build_colindex(const uint32_t* scol, const uint32_t* srow, const uint32_t* 
     tile_starts<<<np, kBlock, 0, s>>>(scol, n, tbase);
     scan_u32(tbase, tbase, ntp, ncols, scan_tmp, s);
     // the number of distinct columns fixes the kept count and the directory's end
-    kept_count<<<1, 1, 0, s>>>(n, ncols, drop_last, d_nkept);
+    if (cx.gptr) kept_count<<<1, 1, 0, s>>>(n, ncols, drop_last, d_nkept);
 #define SPSYRK_PACK(VBv, JACv)                                                                                    \
     pack<VBv, JACv><<<np, kBlock, 0, s>>>(scol, srow, sent, vals_b, run, n, tbase, drop_last, cx.gs, cx.rowbits,  \
-                                          lenbits, cx.ngroups, d_nkept, rp_b, cx.key, cx.val, cx.gptr, vsrc)
+                                          lenbits, cx.ngroups, d_nkept, rp_b, cx.key, cx.val, cx.gptr, vsrc, \
+                                          ncols, cx.gptr ? nullptr : d_nkept)
     if (sr == kJaccard)
         SPSYRK_PACK(0, true);
     else if (vbytes_in == 8)

@@ -1023,18 +1023,25 @@ int digit_plan(int nbits, int (&width)[8]) {
 
 }  // namespace
 
+constexpr int64_t kFewRecords = int64_t(1) << 16;
+
 // Local-sort plan of a CSR column sort: the high h = nbits - L bits by passes,
 // the low L (1..kLBits) bits inside groups of equal high bits, about 2048
-// records per group on average.  Used for wide keys over many entries
+// records per group on average.  Used for wide keys over many entries, and
+// for few entries, where it takes five launches instead of nine and the
+// passes are all latency (there with about 512 records per group, so that
+// more workgroups share them; a hub column's group is at most the whole
+// matrix).
 // (SPSYRK_LOCAL_SORT=1 forces it wherever it applies, =0 turns it off; read
 // at every call).  Returns L, or 0 for passes over all bits.
 int local_bits(int64_t n, int nbits) {
     const char* e = std::getenv("SPSYRK_LOCAL_SORT");
     const bool force = e && e[0] == '1';
     if (e && e[0] == '0') return 0;
-    if (!force && (nbits < 22 || n < (int64_t(1) << 20))) return 0;
+    const bool few = n <= kFewRecords;
+    if (!force && !few && (nbits < 22 || n < (int64_t(1) << 20))) return 0;
     int h = nbits - kLBits;
-    const int hg = bit_width_u64(uint64_t(n / 2048));  // groups of about 2048 records
+    const int hg = bit_width_u64(uint64_t(n / (few && !force ? 512 : 2048)));  // groups of about that many records
     if (hg > h) h = hg;
     if (h < 1) h = 1;
     const int L = nbits - h;

@@ -1,6 +1,8 @@
-// Device-wide exclusive prefix sums (three launches: tile reduce, scan of
-// tile sums in one workgroup, tile scan with carry-in; one launch for arrays
-// of at most four tiles).
+// Device-wide exclusive prefix sums.  A launch costs a call about 5 us, so
+// arrays of up to kBlockItems values take one workgroup and one launch,
+// longer ones two: the tiles' sums, then every tile's scan, its workgroup
+// adding up the sums before it by itself (at most kOwnSums, 16 KB from L2).
+// Past that many tiles a third launch scans the sums in one workgroup.
 #include "common.h"
 #include "internal.h"
 
@@ -61,63 +63,99 @@ __global__ __launch_bounds__(kBlock) void scan_sums(T* __restrict__ sums, int64_
 }
 
 // Exclusive scan of the tile at base (kTile values of in, zero past n) into
-// out, starting from carry; returns the tile's sum.  The tile is read whole
-// into LDS before any of it is written, so in may equal out.
+// out, starting from carry.  The tile is read whole into LDS before any of it
+// is written, so in may equal out.  The LDS rows of kItems values are padded
+// by one, so that the threads' runs of kItems do not start in one bank.
 template <typename T>
 __device__ inline T scan_tile(const T* __restrict__ in, T* __restrict__ out, int64_t n, int64_t base, T carry,
                               T* buf, T* wt) {
     // coalesced loads into LDS, then a blocked arrangement: thread t holds
     // kItems consecutive elements
+    auto at = [](int x) { return x + x / kItems; };
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
         const int64_t i = base + int64_t(k) * kBlock + threadIdx.x;
-        buf[k * kBlock + threadIdx.x] = i < n ? in[i] : T(0);
+        buf[at(k * kBlock + int(threadIdx.x))] = i < n ? in[i] : T(0);
     }
     __syncthreads();
     T v[kItems];
     T s = 0;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-        v[k] = buf[threadIdx.x * kItems + k];
+        v[k] = buf[at(threadIdx.x * kItems + k)];
         s += v[k];
     }
     T tot;
     T off = block_exclusive_scan(s, wt, &tot) + carry;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-        buf[threadIdx.x * kItems + k] = off;
+        buf[at(threadIdx.x * kItems + k)] = off;
         off += v[k];
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
         const int64_t i = base + int64_t(k) * kBlock + threadIdx.x;
-        if (i < n) out[i] = buf[k * kBlock + threadIdx.x];
+        if (i < n) out[i] = buf[at(k * kBlock + int(threadIdx.x))];
     }
-    __syncthreads();  // (buf is reused by the next tile)
     return tot;
 }
 
-template <typename T>
+// SUMS: sums holds the tiles' sums (not scanned); the last tile writes
+// *total.  Otherwise sums is their exclusive scan.
+template <typename T, bool SUMS>
 __global__ __launch_bounds__(kBlock) void tile_scan(const T* __restrict__ in, T* __restrict__ out, int64_t n,
-                                                    const T* __restrict__ sums) {
+                                                    const T* __restrict__ sums, T* __restrict__ total) {
     __shared__ T wt[kWavesPerBlock];
-    __shared__ T buf[kTile];
-    (void)scan_tile(in, out, n, int64_t(blockIdx.x) * kTile, sums[blockIdx.x], buf, wt);
+    __shared__ T wb[kWavesPerBlock];
+    __shared__ T buf[kTile + kTile / kItems];
+    T before = 0;
+    if constexpr (SUMS) {
+        for (int64_t q = threadIdx.x; q < int64_t(blockIdx.x); q += kBlock) before += sums[q];
+        before = wave_reduce_sum(before);
+        if (lane_id() == 0) wb[threadIdx.x / kWave] = before;
+        __syncthreads();
+        before = 0;
+        for (int w = 0; w < kWavesPerBlock; ++w) before += wb[w];
+    } else {
+        before = sums[blockIdx.x];
+    }
+    const T tot = scan_tile(in, out, n, int64_t(blockIdx.x) * kTile, before, buf, wt);
+    if (SUMS && total && blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) *total = before + tot;
 }
 
-// up to kOneBlockTiles tiles scanned by one workgroup, tile after tile with
-// the carry (one launch instead of three for short arrays); total -> *total
-constexpr int64_t kOneBlockTiles = 4;
+// short arrays: one workgroup of 1024 threads, kShort values each in
+// registers, all loaded at once (one launch; total -> *total)
+constexpr int kOneBlock = 1024;
+constexpr int kShort = 8;
+constexpr int64_t kBlockItems = 2 * kOneBlock * kShort;
 template <typename T>
-__global__ __launch_bounds__(kBlock) void scan_one_block(const T* __restrict__ in, T* __restrict__ out, int64_t n,
-                                                         T* __restrict__ total) {
-    __shared__ T wt[kWavesPerBlock];
-    __shared__ T buf[kTile];
+__global__ __launch_bounds__(kOneBlock) void scan_one_block(const T* __restrict__ in, T* __restrict__ out, int64_t n,
+                                                            T* __restrict__ total) {
+    __shared__ T wt[kOneBlock / kWave];
     T carry = 0;
-    for (int64_t base = 0; base < n; base += kTile) carry += scan_tile(in, out, n, base, carry, buf, wt);
+    for (int64_t base = 0; base < n; base += kOneBlock * kShort) {
+        const int64_t i0 = base + int64_t(threadIdx.x) * kShort;
+        T v[kShort];
+        T s = 0;
+#pragma unroll
+        for (int k = 0; k < kShort; ++k) v[k] = i0 + k < n ? in[i0 + k] : T(0);
+#pragma unroll
+        for (int k = 0; k < kShort; ++k) s += v[k];
+        T tot;
+        // (its barriers also order these loads before the stores: in may be out)
+        T off = block_exclusive_scan<T, kOneBlock>(s, wt, &tot) + carry;
+#pragma unroll
+        for (int k = 0; k < kShort; ++k) {
+            if (i0 + k < n) out[i0 + k] = off;
+            off += v[k];
+        }
+        carry += tot;
+    }
     if (total && threadIdx.x == 0) *total = carry;
 }
+
+constexpr int64_t kOwnSums = 2048;
 
 template <typename T>
 void scan_impl(const T* in, T* out, int64_t n, T* total, void* tmp, hipStream_t s) {
@@ -127,13 +165,17 @@ void scan_impl(const T* in, T* out, int64_t n, T* total, void* tmp, hipStream_t 
         if (total) (void)hipMemsetAsync(total, 0, sizeof(T), s);
         return;
     }
-    if (nb <= kOneBlockTiles) {
-        scan_one_block<T><<<1, kBlock, 0, s>>>(in, out, n, total);
+    if (n <= kBlockItems) {
+        scan_one_block<T><<<1, kOneBlock, 0, s>>>(in, out, n, total);
         return;
     }
     tile_reduce<T><<<dim3(unsigned(nb)), dim3(kBlock), 0, s>>>(in, n, sums);
+    if (nb <= kOwnSums) {
+        tile_scan<T, true><<<dim3(unsigned(nb)), dim3(kBlock), 0, s>>>(in, out, n, sums, total);
+        return;
+    }
     scan_sums<T><<<1, kBlock, 0, s>>>(sums, nb, total);
-    tile_scan<T><<<dim3(unsigned(nb)), dim3(kBlock), 0, s>>>(in, out, n, sums);
+    tile_scan<T, false><<<dim3(unsigned(nb)), dim3(kBlock), 0, s>>>(in, out, n, sums, nullptr);
 }
 
 }  // namespace
