@@ -277,6 +277,10 @@ constexpr int kSplitRows = 1 << 14;  // rows per range at most (the LDS accumula
 // threads measure 10% slower, 1024 25% slower; tiles of 2048 entries with
 // three workgroups per compute unit 15% slower: shorter runs per range)
 constexpr int kSplitThreads = 512;
+// threads of a summing workgroup: its 128 KiB accumulator leaves room for one
+// per compute unit, so it has to keep the memory busy alone (2^23 rows: 0.78 ms
+// with 256 threads, 0.47 ms with 1024)
+constexpr int kApplyThreads = 1024;
 
 // Entries [blk * kSub * kTileS, +kSub * kTileS) of workgroup blk: its entries
 // per range of their column, cnt[range * nblk + blk] (every entry, the
@@ -288,19 +292,55 @@ __global__ __launch_bounds__(kBlock) void split_count(const int32_t* __restrict_
     __syncthreads();
     const int64_t e0 = int64_t(blockIdx.x) * kSub * kTileS;
     const int64_t e1 = min(nnz, e0 + int64_t(kSub) * kTileS);
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock) atomicAdd(&h[ci[e] >> bits], 1u);
+    // 16-byte loads, four in flight per thread, where the part is whole and
+    // aligned (2^23 rows: 0.30 ms with one 4-byte load in flight, 0.18 ms so)
+    int64_t e = e0;
+    if ((reinterpret_cast<uintptr_t>(ci) & 15) == 0)
+        for (; e + int64_t(kBlock) * 16 <= e1; e += int64_t(kBlock) * 16) {
+            uint4 q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = nt_load4(ci + e + (u * kBlock + int(threadIdx.x)) * 4);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                atomicAdd(&h[q[u].x >> bits], 1u);
+                atomicAdd(&h[q[u].y >> bits], 1u);
+                atomicAdd(&h[q[u].z >> bits], 1u);
+                atomicAdd(&h[q[u].w >> bits], 1u);
+            }
+        }
+    for (e += threadIdx.x; e < e1; e += kBlock) atomicAdd(&h[ci[e] >> bits], 1u);
     __syncthreads();
     for (int b = threadIdx.x; b < nr; b += kBlock) cnt[int64_t(b) * nblk + blockIdx.x] = h[b];
 }
 
+// N consecutive entries of src from position i on (src + i aligned to 16 bytes)
+template <int N, typename T>
+__device__ inline void load_run(const T* __restrict__ src, int64_t i, T (&out)[N]) {
+    static_assert(N * sizeof(T) % 16 == 0, "whole 16-byte loads");
+    constexpr int kPer = 16 / int(sizeof(T));
+#pragma unroll
+    for (int u = 0; u < N; u += kPer) {
+        const uint4 q = nt_load4(src + i + u);
+        __builtin_memcpy(&out[u], &q, 16);
+    }
+}
+
 // The row pass for one column, kSub tiles of kTileS entries per workgroup,
-// one thread per stretch of kTileS / kBlock entries as in symm_kernel; the
-// row term is added per row stretch.  Each tile's transposed terms are
-// counted per range, placed in LDS range by range, and written out as one
-// contiguous run per range at the range's cursor of this workgroup (boff:
-// exclusive scan of split_count's counts).
+// one thread per stretch of kTileS / kSplitThreads entries as in symm_kernel.
+// Each tile's transposed terms are counted per range, placed in LDS range by
+// range, and written out as one contiguous run per range at the range's
+// cursor of this workgroup (boff: exclusive scan of split_count's counts).
+// The rows' sums are collected in LDS next to the tile's row window and added
+// to the workspace once per row and tile.
+//
+// The random reads of X bound this pass, so they are kept in flight: the next
+// tile's entries are loaded while this tile's records are counted, and its
+// reads of X are issued before this tile's records are placed and written.
+// (2^23 rows, f32, random columns: 5.31 ms with the reads inside the tile and
+// an atomic add per stretch, 4.63 ms so; the reads alone, random 4-byte reads
+// of a 32 MiB table, would take 3.7 ms at the rate they reach by themselves.)
 template <typename V, typename XT>
-__global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __restrict__ rp, int64_t m, int64_t nnz,
+__global__ __launch_bounds__(kSplitThreads, 4) void split_records(const int64_t* __restrict__ rp, int64_t m, int64_t nnz,
                                                         const int32_t* __restrict__ ci, const V* __restrict__ cv,
                                                         const int64_t* __restrict__ trow, const XT* __restrict__ x,
                                                         int64_t ldx, double* __restrict__ w,
@@ -308,8 +348,6 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
                                                         int64_t nblk, uint16_t* __restrict__ rj,
                                                         double* __restrict__ rv) {
     constexpr int kPerG = kTileS / kSplitThreads;  // entries per thread
-    constexpr int kBatch = kPerG < 8 ? kPerG : 8;
-    static_assert(kPerG % kBatch == 0, "whole batches");
     __shared__ int64_t cur[kSymmSplitMax];   // next record of each range for this workgroup
     __shared__ uint32_t th[kSymmSplitMax];   // the tile's records per range, then their LDS start
     __shared__ uint32_t tc[kSymmSplitMax];   // placement cursors inside the tile
@@ -317,7 +355,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
     __shared__ uint16_t sj[kTileS];
     __shared__ uint16_t sb[kTileS];
     __shared__ double sv[kTileS];
-    __shared__ int64_t win[kWinS + 1];
+    __shared__ uint32_t win[kWinS + 1];  // the tile's rows: their first entry in the tile
+    __shared__ double dots[kWinS / 2];   // and the sums of the first of them
     __shared__ int64_t bounds[2];
     for (int b = threadIdx.x; b < nr; b += kSplitThreads) {
         cur[b] = boff[int64_t(b) * nblk + blockIdx.x];
@@ -326,9 +365,33 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
     }
     const uint32_t lmask = (1u << bits) - 1u;
     const int64_t ntiles = (nnz + kTileS - 1) / kTileS;
-    for (int sub = 0; sub < kSub; ++sub) {
-        const int64_t tile = int64_t(blockIdx.x) * kSub + sub;
-        if (tile >= ntiles) break;  // uniform over the workgroup
+    const int64_t tile0 = int64_t(blockIdx.x) * kSub;
+    const int nt = int(min(int64_t(kSub), ntiles - tile0));
+    const bool vec = ((reinterpret_cast<uintptr_t>(ci) | reinterpret_cast<uintptr_t>(cv)) & 15) == 0;
+    // this thread's entries of a tile: a whole aligned stretch with 16-byte
+    // loads, else one by one (column 0 and value 0 past the end)
+    auto entries = [&](int sub, int32_t(&cj)[kPerG], V(&cvv)[kPerG]) {
+        const int64_t a = (tile0 + sub) * kTileS + int64_t(threadIdx.x) * kPerG;
+        if (vec && a + kPerG <= nnz) {
+            load_run(ci, a, cj);
+            load_run(cv, a, cvv);
+        } else {
+#pragma unroll
+            for (int u = 0; u < kPerG; ++u) {
+                const bool in = a + u < nnz;
+                cj[u] = in ? ci[a + u] : 0;
+                cvv[u] = in ? cv[a + u] : V(0);
+            }
+        }
+    };
+    int32_t cj[kPerG];
+    V cvv[kPerG];
+    XT xj[kPerG];
+    entries(0, cj, cvv);
+#pragma unroll
+    for (int u = 0; u < kPerG; ++u) xj[u] = x[int64_t(cj[u]) * ldx];
+    for (int sub = 0; sub < nt; ++sub) {
+        const int64_t tile = tile0 + sub;
         const int64_t e0 = tile * kTileS;
         const int64_t e1 = min(nnz, e0 + kTileS);
         __syncthreads();  // the previous tile is written; counters are reset
@@ -340,9 +403,18 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
         __syncthreads();
         const int64_t rlo = bounds[0], rhi = bounds[1];
         const bool staged = rhi - rlo + 1 <= kWinS;
+        const int64_t nrow = rhi - rlo + 1;
         if (staged)
-            for (int64_t t = threadIdx.x; t <= rhi - rlo + 1 && rlo + t <= m; t += kSplitThreads) win[t] = rp[rlo + t];
+            for (int64_t t = threadIdx.x; t <= nrow && rlo + t <= m; t += kSplitThreads)
+                win[t] = uint32_t(min(max(rp[rlo + t], e0) - e0, int64_t(kTileS)));
+        for (int t = threadIdx.x; t < kWinS / 2; t += kSplitThreads) dots[t] = 0.0;
         __syncthreads();
+        auto add_dot = [&](int64_t r, double d) {
+            if (r - rlo < kWinS / 2)
+                atomicAdd(&dots[r - rlo], d);
+            else
+                atomicAdd(&w[r], d);
+        };
         const int64_t a = e0 + int64_t(threadIdx.x) * kPerG;
         const int64_t b = min(e1, a + kPerG);
         uint32_t rb[kPerG];  // range (high bits) and row in range (low 16 bits) of each term
@@ -353,45 +425,49 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
             tv[u] = 0.0;
         }
         if (a < b) {
-            int64_t r = staged ? rlo + last_leq_s(win, 0, rhi - rlo, a) : last_leq_s(rp, rlo, rhi, a);
-            int64_t rend = staged ? win[r - rlo + 1] : rp[r + 1];
+            int64_t r, rend;
+            if (staged) {
+                const uint32_t at = uint32_t(a - e0);
+                int lo = 0, hi = int(nrow) - 1;
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (win[mid] <= at)
+                        lo = mid;
+                    else
+                        hi = mid - 1;
+                }
+                r = rlo + lo;
+                rend = e0 + win[lo + 1];
+            } else {
+                r = last_leq_s(rp, rlo, rhi, a);
+                rend = rp[r + 1];
+            }
             double xi = double(x[r * ldx]);
             double dot = 0.0;
 #pragma unroll
-            for (int h = 0; h < kPerG; h += kBatch) {
-                const int64_t a0 = a + h;
-                int32_t cj[kBatch];
-                double cvv[kBatch], xj[kBatch];
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const bool in = a0 + u < b;
-                    cj[u] = in ? ci[a0 + u] : 0;
-                    cvv[u] = in ? double(cv[a0 + u]) : 0.0;
-                }
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) xj[u] = a0 + u < b ? double(x[int64_t(cj[u]) * ldx]) : 0.0;
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const int64_t e = a0 + u;
-                    if (e < b) {
-                        if (e >= rend) {
-                            atomicAdd(&w[r], dot);
-                            do {
-                                ++r;
-                                rend = staged && r <= rhi ? win[r - rlo + 1] : rp[r + 1];
-                            } while (rend <= e);
-                            xi = double(x[r * ldx]);
-                            dot = 0.0;
-                        }
-                        const uint32_t j = uint32_t(cj[u]);
-                        dot += cvv[u] * xj[u];
-                        rb[h + u] = ((j >> bits) << 16) | (j & lmask);
-                        tv[h + u] = int64_t(j) != r ? cvv[u] * xi : 0.0;
+            for (int u = 0; u < kPerG; ++u) {
+                const int64_t e = a + u;
+                if (e < b) {
+                    if (e >= rend) {
+                        add_dot(r, dot);
+                        do {
+                            ++r;
+                            rend = staged ? e0 + win[r - rlo + 1] : rp[r + 1];
+                        } while (rend <= e);
+                        xi = double(x[r * ldx]);
+                        dot = 0.0;
                     }
+                    const uint32_t j = uint32_t(cj[u]);
+                    const double v = double(cvv[u]);
+                    dot += v * double(xj[u]);
+                    rb[u] = ((j >> bits) << 16) | (j & lmask);
+                    tv[u] = int64_t(j) != r ? v * xi : 0.0;
                 }
             }
-            atomicAdd(&w[r], dot);
+            add_dot(r, dot);
         }
+        const bool more = sub + 1 < nt;
+        if (more) entries(sub + 1, cj, cvv);
         // the tile's records per range, their LDS places, then their runs
 #pragma unroll
         for (int u = 0; u < kPerG; ++u)
@@ -399,6 +475,10 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
         __syncthreads();
         block_exclusive_scan_array<uint32_t, kSplitThreads>(th, nr, wt);  // th: start of each range's run in LDS
         __syncthreads();
+        if (more) {
+#pragma unroll
+            for (int u = 0; u < kPerG; ++u) xj[u] = x[int64_t(cj[u]) * ldx];
+        }
 #pragma unroll
         for (int u = 0; u < kPerG; ++u) {
             if (rb[u] == 0xffffffffu) continue;
@@ -408,6 +488,8 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
             sb[q] = uint16_t(g);
             sv[q] = tv[u];
         }
+        for (int t = threadIdx.x; t < min(nrow, int64_t(kWinS / 2)); t += kSplitThreads)
+            if (dots[t] != 0.0) atomicAdd(&w[rlo + t], dots[t]);
         __syncthreads();
         const int tn = int(e1 - e0);
         for (int q = threadIdx.x; q < tn; q += kSplitThreads) {
@@ -428,24 +510,24 @@ __global__ __launch_bounds__(kSplitThreads) void split_records(const int64_t* __
 // Range blockIdx.x: its records (every workgroup's run, contiguous in the
 // range-major array) summed in LDS, then added to its rows of the workspace
 // (no other workgroup touches them).
-__global__ __launch_bounds__(kBlock) void split_apply(const int64_t* __restrict__ boff, int nr, int64_t nblk,
+__global__ __launch_bounds__(kApplyThreads) void split_apply(const int64_t* __restrict__ boff, int nr, int64_t nblk,
                                                       int64_t nrec, int bits, int64_t m,
                                                       const uint16_t* __restrict__ rj,
                                                       const double* __restrict__ rv, double* __restrict__ w) {
     __shared__ double acc[kSplitRows];
     const int rg = blockIdx.x;
     const int rows = int(min(int64_t(1) << bits, m - (int64_t(rg) << bits)));
-    for (int t = threadIdx.x; t < rows; t += kBlock) acc[t] = 0.0;
+    for (int t = threadIdx.x; t < rows; t += kApplyThreads) acc[t] = 0.0;
     __syncthreads();
     const int64_t s0 = boff[int64_t(rg) * nblk];
     const int64_t s1 = rg + 1 < nr ? boff[int64_t(rg + 1) * nblk] : nrec;
     constexpr int kU = 4;
-    for (int64_t q0 = s0 + threadIdx.x; q0 < s1; q0 += int64_t(kBlock) * kU) {
+    for (int64_t q0 = s0 + threadIdx.x; q0 < s1; q0 += int64_t(kApplyThreads) * kU) {
         uint32_t jj[kU];
         double vv[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int64_t q = q0 + int64_t(u) * kBlock;
+            const int64_t q = q0 + int64_t(u) * kApplyThreads;
             jj[u] = q < s1 ? rj[q] : 0u;
             vv[u] = q < s1 ? rv[q] : 0.0;
         }
@@ -455,7 +537,7 @@ __global__ __launch_bounds__(kBlock) void split_apply(const int64_t* __restrict_
     }
     __syncthreads();
     double* __restrict__ wr = w + (int64_t(rg) << bits);
-    for (int t = threadIdx.x; t < rows; t += kBlock) wr[t] += acc[t];
+    for (int t = threadIdx.x; t < rows; t += kApplyThreads) wr[t] += acc[t];
 }
 
 __global__ __launch_bounds__(kBlock) void zero_f64(double* __restrict__ p, int64_t n) {
@@ -592,7 +674,7 @@ void launch_split(const DevCsr& C, const XT* x, int64_t ldx, double* w, const in
     scan_i64(boff, boff, int64_t(L.nr) * L.nblk, nullptr, tmp + L.stmp, s);
     split_records<V, XT><<<unsigned(L.nblk), kSplitThreads, 0, s>>>(C.rp, C.m, C.nnz, C.ci, static_cast<const V*>(C.v), trow,
                                                              x, ldx, w, boff, L.bits, L.nr, L.nblk, rj, rv);
-    split_apply<<<unsigned(L.nr), kBlock, 0, s>>>(boff, L.nr, L.nblk, C.nnz, L.bits, C.m, rj, rv, w);
+    split_apply<<<unsigned(L.nr), kApplyThreads, 0, s>>>(boff, L.nr, L.nblk, C.nnz, L.bits, C.m, rj, rv, w);
 }
 
 template <typename V, typename XT, int BITS>
