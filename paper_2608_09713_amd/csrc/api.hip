@@ -1148,6 +1148,26 @@ std::vector<Slab> plan_slabs(const MirrorArgs& ma, int64_t cap, int64_t wcap, Ar
     return out;
 }
 
+// Slabs of w columns each, when no count can pass the record cap and they are
+// few: what plan_slabs gives there, without reading every entry.
+std::vector<Slab> even_slabs(const MirrorArgs& ma, int64_t w, Arena& ar, hipStream_t s) {
+    const int ns = int((ma.m + w - 1) / w);
+    unsigned long long* hist = ar.get_t<unsigned long long>(kMirrorEvenSlabs);
+    std::vector<unsigned long long> h(size_t(ns), 0);
+    mirror_even_slab_counts(ma, w, ns, hist, s);
+    check_launch();
+    HIPCHK(hipMemcpyAsync(h.data(), hist, size_t(ns) * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    ar.release(hist);
+    std::vector<Slab> out;
+    int64_t before = 0;
+    for (int k = 0; k < ns; ++k) {
+        out.push_back({k * w, std::min(ma.m, (k + 1) * w), int64_t(h[size_t(k)]), before});
+        before += out.back().nrec;
+    }
+    return out;
+}
+
 void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C) {
     Ctl* ctl = ar.get_t<Ctl>(1);
     zero_ctl(ctl, s);
@@ -1166,10 +1186,11 @@ void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C
     ma.vbytes = vb;
 
     // The strict lower part is transposed in column slabs: records (column,
-    // row, value) extracted row-major, sorted stably by column, each column's
-    // record range read off the sorted keys, which gives the full row lengths
-    // and starts of the slab's rows, and every record placed after the lower
-    // part of its row.  The lower rows are copied once all starts are known.
+    // row, value) in row-major order, sorted stably by column, the last pass
+    // placing every record after the lower part of its row; each column's
+    // record range is read off the passes' histograms (slabs of at most 2^16
+    // columns) or the sorted keys, which gives the full row lengths and starts
+    // of the slab's rows.  The lower rows are copied once all starts are known.
     const int64_t cap = mirror_slab_cap();
     // Slabs of at most 2^16 columns sort in two 8-bit passes instead of
     // three: worth it when the records are many per row (each slab costs a
@@ -1202,15 +1223,19 @@ void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C
             check_launch();
             const Ctl h = read_ctl(ctl, s);
             slabs.push_back({0, m, h.total, 0});
+        } else if (L.nnz <= cap && m > 0 && (m + wcap - 1) / wcap <= kMirrorEvenSlabs) {
+            slabs = even_slabs(ma, wcap, ar, s);
         } else {
             slabs = plan_slabs(ma, cap, wcap, ar, s);
         }
     }
-    int64_t nstrict = 0, rec_max = 0, w_max = 0;
+    auto slab_bits = [](const Slab& sl) { return bit_width_u64(sl.c1 - sl.c0 > 1 ? uint64_t(sl.c1 - sl.c0 - 1) : 0); };
+    int64_t nstrict = 0, rec_max = 0, w_max = 0, first_words = 1;
     for (const Slab& sl : slabs) {
         nstrict += sl.nrec;
         rec_max = std::max(rec_max, sl.nrec);
         w_max = std::max(w_max, sl.c1 - sl.c0);
+        first_words = std::max({first_words, sl.c1 - sl.c0, slab_starts_words(slab_bits(sl))});
     }
     const int64_t total = L.nnz + nstrict;
     int64_t* f_rp = ar.get_t<int64_t>(m + 1, true);
@@ -1218,7 +1243,7 @@ void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C
     void* f_val = vb ? ar.get(size_t(total > 0 ? total : 1) * vb, true) : nullptr;
     HIPCHK(hipMemsetAsync(f_rp, 0, sizeof(int64_t), s));  // m == 0: the only row start
 
-    uint32_t* first = ar.get_t<uint32_t>(w_max > 0 ? w_max : 1);
+    uint32_t* first = ar.get_t<uint32_t>(first_words);
     uint32_t* endc = ar.get_t<uint32_t>(w_max > 0 ? w_max : 1);
     uint32_t* ka = ar.get_t<uint32_t>(rec_max > 0 ? rec_max : 1);
     uint32_t* kb = ar.get_t<uint32_t>(rec_max > 0 ? rec_max : 1);
@@ -1242,15 +1267,9 @@ void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C
                 throw Fail{SPSYRK_ERR_HIP};
             }
         }
-        const uint32_t* skey = ka;
-        const uint32_t* srow = ra;
-        const void* sval = va;
-        const int nbits = bit_width_u64(sl.c1 - sl.c0 > 1 ? uint64_t(sl.c1 - sl.c0 - 1) : 0);
-        // keys of at most 16 bits: the sort reads the records straight from
-        // C_L and its last pass puts them into the full rows; wider keys go
-        // through extracted records, passes and a placement
-        const bool fused = nbits <= 16;
-        if (sl.nrec > 0 && fused) {
+        const uint32_t* skey = nullptr;
+        const int nbits = slab_bits(sl);
+        if (sl.nrec > 0) {
             SlabIo io;
             io.ci = L.ci;
             io.val = vb ? L.v : nullptr;
@@ -1261,31 +1280,22 @@ void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C
             io.f_ci = f_ci;
             io.f_val = f_val;
             // (SPSYRK_SLAB_DIRECT=0, read at every call: the first pass reads
-            // extracted records instead of C_L itself, about 4% slower on
-            // R-MAT's transpose)
+            // extracted records instead of C_L itself: a pass over memory more)
             const char* de = std::getenv("SPSYRK_SLAB_DIRECT");
             const bool direct = !(de && de[0] == '0');
             if (direct)
                 mirror_slab_offsets(row_lo, row_cnt, m, s);
             else
                 mirror_slab_extract(ma, sl.c0, sl.nrec, row_cnt, row_lo, strow, ka, ra, va, s);
-            skey = slab_sort_place(io, vb, sl.nrec, nbits, row_cnt, m, !direct, ka, kb, ra, rb, va, vbb, rtmp, s);
-        } else if (sl.nrec > 0) {
-            mirror_slab_extract(ma, sl.c0, sl.nrec, row_cnt, row_lo, strow, ka, ra, va, s);
-            if (radix_sort(ka, kb, ra, rb, va, vbb, vb, sl.nrec, nbits, rtmp, s)) {
-                skey = kb;
-                srow = rb;
-                sval = vbb;
-            }
+            skey = slab_sort_place(io, vb, sl.nrec, nbits, row_cnt, m, !direct, ka, kb, ra, rb, va, vbb, first, rtmp, s);
         }
         // row_cnt is free again: full lengths of the slab's rows
         mirror_slab_columns(ma, sl.c0, sl.c1, skey, sl.nrec, first, endc, row_cnt, sl.before, f_rp, stmp, s);
-        if (!fused) mirror_slab_place(ma, sl.c0, sl.nrec, skey, srow, sval, first, f_rp, f_ci, f_val, s);
         check_launch();
     }
     {
         Phase ph(SPSYRK_PHASE_MIRROR_COPY, s);
-        mirror_copy_lower(ma, 0, L.nnz, trow, f_rp, f_ci, f_val, s);
+        mirror_copy_lower(ma, trow, f_rp, f_ci, f_val, s);
     }
     check_launch();
     HIPCHK(hipStreamSynchronize(s));

@@ -445,13 +445,17 @@ struct SlabIo {
     int32_t* f_ci = nullptr;          // full rows
     void* f_val = nullptr;
 };
-// Sort of a slab of nrec records with keys of nbits <= 16 bits (one or two
-// passes) into the full rows, the first pass reading C_L through the slab's
-// rows or (extracted) the records already in key_a, row_a, val_a; returns
-// the buffer with the sorted keys.  tmp: radix_tmp_bytes(nrec).
-uint32_t* slab_sort_place(const SlabIo& io, int vbytes, int64_t nrec, int nbits, const int64_t* rec_rp, int64_t m,
-                          bool extracted, uint32_t* key_a, uint32_t* key_b, uint32_t* row_a, uint32_t* row_b,
-                          void* val_a, void* val_b, void* tmp, hipStream_t s);
+// Sort of a slab of nrec > 0 records with keys of nbits bits into the full
+// rows, the first pass reading C_L through the slab's rows or (extracted) the
+// records already in key_a, row_a, val_a.  Keys of at most 16 bits: returns
+// null, starts[k] is the first record of slab column k, up to starts[2^nbits]
+// = nrec (slab_starts_words(nbits) words).  Wider keys: returns the sorted
+// keys, in one of the key buffers.  tmp: radix_tmp_bytes(nrec).
+inline int64_t slab_starts_words(int nbits) { return nbits <= 16 ? (int64_t(1) << nbits) + 1 + 257 : 0; }
+const uint32_t* slab_sort_place(const SlabIo& io, int vbytes, int64_t nrec, int nbits, const int64_t* rec_rp,
+                                int64_t m, bool extracted, uint32_t* key_a, uint32_t* key_b, uint32_t* row_a,
+                                uint32_t* row_b, void* val_a, void* val_b, uint32_t* starts, void* tmp,
+                                hipStream_t s);
 
 // ---- mirror.hip
 struct MirrorArgs {
@@ -469,6 +473,10 @@ constexpr int kMirrorBins = 4096;
 constexpr int64_t kMirrorNarrow = int64_t(1) << 16;
 void mirror_coarse_hist(const MirrorArgs& a, int64_t clo, int cb, int nb, unsigned long long* hist,
                         hipStream_t s);
+// strict-lower entries of columns [k w, (k + 1) w) for k < ns <= kMirrorEvenSlabs
+// (the slabs cover every column; m > 0)
+constexpr int kMirrorEvenSlabs = 64;
+void mirror_even_slab_counts(const MirrorArgs& a, int64_t w, int ns, unsigned long long* hist, hipStream_t s);
 // row of every tile start of the mirror's walks over positions [0, rp[m])
 // (trow: mirror_tile_bytes(rp[m]))
 size_t mirror_tile_bytes(int64_t positions);
@@ -483,21 +491,17 @@ void mirror_slab_counts(const MirrorArgs& a, int64_t c0, int64_t c1, int64_t* ro
 // (trow: mirror_tile_bytes(nrec) of scratch)
 void mirror_slab_extract(const MirrorArgs& a, int64_t c0, int64_t nrec, const int64_t* rec_rp, const int64_t* row_lo,
                          int64_t* trow, uint32_t* rkey, uint32_t* rrow, void* rval, hipStream_t s);
-// from the slab's records sorted by column (keys skey): first[k] / end[k],
-// the record range of slab column k, and the full row starts f_rp[c0..c1]
+// the full row starts f_rp[c0..c1] from the slab's records sorted by column,
+// first[k] and end[k] being the record range of slab column k: read off the
+// sorted keys skey, or with skey null given by first, end[k] being first[k + 1]
 // (fl: w + 1 words of scratch; strict_before: strict-lower entries in the
 // columns before c0; first / end: w words each)
 void mirror_slab_columns(const MirrorArgs& a, int64_t c0, int64_t c1, const uint32_t* skey, int64_t nrec,
                          uint32_t* first, uint32_t* end, int64_t* fl, int64_t strict_before, int64_t* f_rp,
                          void* scan_tmp, hipStream_t s);
-// place sorted records: record s of slab column k goes to
-// f_rp[c0 + k] + lower_len(c0 + k) + (s - first[k])
-void mirror_slab_place(const MirrorArgs& a, int64_t c0, int64_t nrec, const uint32_t* skey, const uint32_t* srow,
-                       const void* sval, const uint32_t* first, const int64_t* f_rp, int32_t* f_ci, void* f_val,
+// lower rows' entries to their places f_rp[row] + offset in row (trow: the
+// table of mirror_tile_rows over the lower rows)
+void mirror_copy_lower(const MirrorArgs& a, const int64_t* trow, const int64_t* f_rp, int32_t* f_ci, void* f_val,
                        hipStream_t s);
-// lower rows' entries [ebeg, eend) to their places f_rp[row] + offset in row
-// (trow: the table of mirror_tile_rows over the lower rows, or null)
-void mirror_copy_lower(const MirrorArgs& a, int64_t ebeg, int64_t eend, const int64_t* trow, const int64_t* f_rp,
-                       int32_t* f_ci, void* f_val, hipStream_t s);
 
 }  // namespace spsyrk

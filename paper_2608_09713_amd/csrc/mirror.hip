@@ -2,8 +2,10 @@
 // part.  Row i of C is row i of C_L followed by column i of the strict lower
 // part in ascending row order.  The lower rows are copied in place; the
 // strict lower part is transposed by a stable sort of (column, row, value)
-// records by column, in column slabs that bound the record buffers, and each
-// sorted record is dropped at its place in the full row.
+// records by column, in column slabs that bound the record buffers, whose last
+// pass drops each record at its place in the full row.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 
@@ -56,20 +58,14 @@ __device__ inline int64_t last_row_leq(const int64_t* rp, int64_t m, int64_t e) 
     return lo;
 }
 
-// Rows of the tile [e0, e1) (tile t of kTileE positions, total positions in
-// all): from the tile table trow (the row of every tile start; the upper
-// bound may then be the row of e1, one past the tile), or by searches.
-__device__ inline RowFinder make_finder(const int64_t* rp, int64_t m, int64_t e0, int64_t e1, int64_t* win,
-                                        int64_t* bounds, const int64_t* trow, int64_t t, int64_t total) {
+// Rows of the tile ending at e1 (tile t of kTileE positions, total positions in
+// all) from the tile table trow (the row of every tile start; the upper bound
+// may be the row of e1, one past the tile).
+__device__ inline RowFinder make_finder(const int64_t* rp, int64_t m, int64_t e1, int64_t* win, int64_t* bounds,
+                                        const int64_t* trow, int64_t t, int64_t total) {
     if (threadIdx.x == 0) {
-        if (trow) {
-            const int64_t lo = trow[t];
-            bounds[0] = lo;
-            bounds[1] = e1 < total ? trow[t + 1] : last_row_leq(rp, m, e1 - 1);
-        } else {
-            bounds[0] = last_row_leq(rp, m, e0);
-            bounds[1] = last_row_leq(rp, m, e1 - 1);
-        }
+        bounds[0] = trow[t];
+        bounds[1] = e1 < total ? trow[t + 1] : last_row_leq(rp, m, e1 - 1);
     }
     __syncthreads();
     RowFinder f{rp, bounds[0], bounds[1], false, win};
@@ -82,31 +78,68 @@ __device__ inline RowFinder make_finder(const int64_t* rp, int64_t m, int64_t e0
     return f;
 }
 
-// Every thread of a strict-lower walk takes kPerC contiguous entries row by
-// row, so the diagonal (the last entry of a row, col == row) is recognised
-// without a search per entry.
+// entries per thread of the copy
 constexpr int kPerC = 16;
 constexpr int kTileC = kBlock * kPerC;
 static_assert(kTileC == kTileE, "one tile table serves the walks and the copies");
 
-// lower rows' entries [ebeg, eend) to their places in the full rows
+// lower rows' entries to their places in the full rows.  A copy, bound by
+// memory: the tile's entries are loaded first, 16 per thread in flight, while
+// the rows are found: every row that starts in the tile marks its first entry,
+// then a running maximum over the tile, so that no entry searches for its row.
+// (60 M entries in rows of about 29, i32: 393 us with a search per entry, 311
+// so; 230 M entries in R-MAT's rows, f32: 920 us, 781 so)
 template <int VB>
 __global__ __launch_bounds__(kBlock) void copy_lower(const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                                                     const void* __restrict__ val, int64_t m, int64_t ebeg,
-                                                     int64_t eend, const int64_t* __restrict__ trow,
+                                                     const void* __restrict__ val, int64_t m, int64_t nnz,
+                                                     const int64_t* __restrict__ trow,
                                                      const int64_t* __restrict__ f_rp, int32_t* __restrict__ f_ci,
                                                      void* __restrict__ f_val) {
-    __shared__ int64_t win[kWin + 1];
+    using V = std::conditional_t<VB == 8, uint64_t, uint32_t>;
+    __shared__ uint32_t mark[kTileE];  // the tile's row (less its first row) starting at the entry, then the entry's row
+    __shared__ uint32_t wt[kWavesPerBlock];
     __shared__ int64_t bounds[2];
-    const int64_t e0 = ebeg + int64_t(blockIdx.x) * kTileE;
-    const int64_t e1 = min(eend, e0 + kTileE);
-    RowFinder f = make_finder(rp, m, e0, e1, win, bounds, trow, blockIdx.x, eend);
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock) {
-        const int64_t r = f.row_of(e);
-        const int64_t p = f_rp[r] + (e - rp[r]);
-        f_ci[p] = ci[e];
-        if constexpr (VB == 8) static_cast<uint64_t*>(f_val)[p] = static_cast<const uint64_t*>(val)[e];
-        if constexpr (VB == 4) static_cast<uint32_t*>(f_val)[p] = static_cast<const uint32_t*>(val)[e];
+    const int64_t e0 = int64_t(blockIdx.x) * kTileE;
+    const int n = int(min(nnz - e0, int64_t(kTileE)));
+    if (threadIdx.x == 0) {
+        bounds[0] = trow[blockIdx.x];
+        bounds[1] = e0 + n < nnz ? trow[blockIdx.x + 1] : last_row_leq(rp, m, nnz - 1);
+    }
+    int32_t c[kPerC];
+    V v[kPerC];
+#pragma unroll
+    for (int u = 0; u < kPerC; ++u) {
+        const int i = u * kBlock + int(threadIdx.x);
+        c[u] = i < n ? __builtin_nontemporal_load(ci + e0 + i) : 0;
+        if constexpr (VB != 0) v[u] = i < n ? __builtin_nontemporal_load(static_cast<const V*>(val) + e0 + i) : V(0);
+        mark[i] = 0;
+    }
+    __syncthreads();
+    const int64_t rlo = bounds[0], rhi = bounds[1];
+    for (int64_t r = rlo + 1 + threadIdx.x; r <= rhi; r += kBlock) {
+        const int64_t a = rp[r];
+        if (a - e0 < n && rp[r + 1] > a) mark[a - e0] = uint32_t(r - rlo);
+    }
+    __syncthreads();
+    uint32_t mine[kPerC], run = 0;
+#pragma unroll
+    for (int u = 0; u < kPerC; ++u) {
+        run = max(run, mark[threadIdx.x * kPerC + u]);
+        mine[u] = run;
+    }
+    uint32_t all;
+    const uint32_t before = block_exclusive_max(run, wt, &all);
+#pragma unroll
+    for (int u = 0; u < kPerC; ++u) mark[threadIdx.x * kPerC + u] = max(before, mine[u]);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPerC; ++u) {
+        const int i = u * kBlock + int(threadIdx.x);
+        if (i >= n) continue;
+        const int64_t r = rlo + mark[i];
+        const int64_t p = e0 + i + (f_rp[r] - rp[r]);
+        f_ci[p] = c[u];
+        if constexpr (VB != 0) static_cast<V*>(f_val)[p] = v[u];
     }
 }
 
@@ -141,6 +174,36 @@ __global__ __launch_bounds__(kBlock) void slab_counts(const int64_t* __restrict_
     lo_out[r] = lo;
 }
 
+// strict-lower entries per slab of w columns, ns <= kMirrorEvenSlabs slabs: every
+// row's entries are ascending, so a search per row and slab boundary counts
+// them (rows of many entries per slab; R-MAT scale 17, 2 slabs: 20 us, where
+// counting every entry by its column takes 207 us)
+__global__ __launch_bounds__(kBlock) void even_slab_counts(const int64_t* __restrict__ rp,
+                                                           const int32_t* __restrict__ ci, int64_t m, int64_t w,
+                                                           int ns, unsigned long long* __restrict__ hist) {
+    __shared__ unsigned long long cnt[kMirrorEvenSlabs];
+    if (threadIdx.x < kMirrorEvenSlabs) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t r = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+    if (r < m) {
+        const int64_t b = rp[r + 1];
+        int64_t lo = rp[r];
+        for (int k = 0; k < ns && lo < b; ++k) {
+            const int64_t c1 = (k + 1) * w;
+            const int64_t hi = c1 < r ? lower_bound_i32(ci, lo, b, c1) : (int64_t(ci[b - 1]) == r ? b - 1 : b);
+            if (hi > lo) atomicAdd(&cnt[k], (unsigned long long)(hi - lo));
+            if (c1 >= r) break;
+            lo = hi;
+        }
+    }
+    __syncthreads();
+    if (int(threadIdx.x) < ns && cnt[threadIdx.x]) atomicAdd(&hist[threadIdx.x], cnt[threadIdx.x]);
+}
+
+__global__ void zero_counts(unsigned long long* __restrict__ p, int n) {
+    if (int(threadIdx.x) < n) p[threadIdx.x] = 0;
+}
+
 __global__ __launch_bounds__(kBlock) void slab_offsets(int64_t* __restrict__ row_lo, const int64_t* __restrict__ rec_rp,
                                                        int64_t m) {
     const int64_t r = int64_t(blockIdx.x) * kBlock + threadIdx.x;
@@ -161,7 +224,7 @@ __global__ __launch_bounds__(kBlock) void slab_extract(const int32_t* __restrict
     __shared__ int64_t bounds[2];
     const int64_t p0 = int64_t(blockIdx.x) * kTileE;
     const int64_t p1 = min(nrec, p0 + kTileE);
-    RowFinder f = make_finder(rec_rp, m, p0, p1, win, bounds, trow, blockIdx.x, nrec);
+    RowFinder f = make_finder(rec_rp, m, p1, win, bounds, trow, blockIdx.x, nrec);
     for (int64_t p = p0 + threadIdx.x; p < p1; p += kBlock) {
         const int64_t r = f.row_of(p);
         const int64_t e = row_lo[r] + (p - rec_rp[r]);
@@ -170,24 +233,6 @@ __global__ __launch_bounds__(kBlock) void slab_extract(const int32_t* __restrict
         if constexpr (VB == 8) static_cast<uint64_t*>(rval)[p] = static_cast<const uint64_t*>(val)[e];
         if constexpr (VB == 4) static_cast<uint32_t*>(rval)[p] = static_cast<const uint32_t*>(val)[e];
     }
-}
-
-template <int VB>
-__global__ __launch_bounds__(kBlock) void slab_place(const int64_t* __restrict__ rp, int64_t c0, int64_t nrec,
-                                                     const uint32_t* __restrict__ skey,
-                                                     const uint32_t* __restrict__ srow, const void* __restrict__ sval,
-                                                     const uint32_t* __restrict__ first,
-                                                     const int64_t* __restrict__ f_rp, int32_t* __restrict__ f_ci,
-                                                     void* __restrict__ f_val) {
-    const int64_t s = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (s >= nrec) return;
-    const uint32_t k = skey[s];
-    const int64_t c = c0 + int64_t(k);
-    const int64_t rank = s - int64_t(first[k]);
-    const int64_t p = f_rp[c] + (rp[c + 1] - rp[c]) + rank;
-    f_ci[p] = int32_t(srow[s]);
-    if constexpr (VB == 8) static_cast<uint64_t*>(f_val)[p] = static_cast<const uint64_t*>(sval)[s];
-    if constexpr (VB == 4) static_cast<uint32_t*>(f_val)[p] = static_cast<const uint32_t*>(sval)[s];
 }
 
 // Strict-lower entries with clo <= col < clo + nb * 2^cb per bucket of 2^cb
@@ -313,17 +358,16 @@ void mirror_tile_rows(const int64_t* rp, int64_t m, int64_t* trow, hipStream_t s
     tile_first_rows(rp, m, kTileE, trow, s);
 }
 
-void mirror_copy_lower(const MirrorArgs& a, int64_t ebeg, int64_t eend, const int64_t* trow, const int64_t* f_rp,
-                       int32_t* f_ci, void* f_val, hipStream_t s) {
-    if (eend <= ebeg) return;
-    const unsigned nb = blocks_for(eend - ebeg, kTileE);
-    if (ebeg != 0) trow = nullptr;  // (the table's tiles start at entry 0)
+void mirror_copy_lower(const MirrorArgs& a, const int64_t* trow, const int64_t* f_rp, int32_t* f_ci, void* f_val,
+                       hipStream_t s) {
+    if (a.nnz <= 0) return;
+    const unsigned nb = blocks_for(a.nnz, kTileE);
     if (a.vbytes == 8 && a.val)
-        copy_lower<8><<<nb, kBlock, 0, s>>>(a.rp, a.ci, a.val, a.m, ebeg, eend, trow, f_rp, f_ci, f_val);
+        copy_lower<8><<<nb, kBlock, 0, s>>>(a.rp, a.ci, a.val, a.m, a.nnz, trow, f_rp, f_ci, f_val);
     else if (a.vbytes == 4 && a.val)
-        copy_lower<4><<<nb, kBlock, 0, s>>>(a.rp, a.ci, a.val, a.m, ebeg, eend, trow, f_rp, f_ci, f_val);
+        copy_lower<4><<<nb, kBlock, 0, s>>>(a.rp, a.ci, a.val, a.m, a.nnz, trow, f_rp, f_ci, f_val);
     else
-        copy_lower<0><<<nb, kBlock, 0, s>>>(a.rp, a.ci, a.val, a.m, ebeg, eend, trow, f_rp, f_ci, f_val);
+        copy_lower<0><<<nb, kBlock, 0, s>>>(a.rp, a.ci, a.val, a.m, a.nnz, trow, f_rp, f_ci, f_val);
 }
 
 void mirror_coarse_hist(const MirrorArgs& a, int64_t clo, int cb, int nb, unsigned long long* hist,
@@ -335,13 +379,22 @@ void mirror_coarse_hist(const MirrorArgs& a, int64_t clo, int cb, int nb, unsign
     coarse_hist<<<unsigned(grid), kBlock, 0, s>>>(a.rp, a.ci, a.m, a.nnz, clo, cb, nb, hist);
 }
 
+void mirror_even_slab_counts(const MirrorArgs& a, int64_t w, int ns, unsigned long long* hist, hipStream_t s) {
+    zero_counts<<<1, kBlock, 0, s>>>(hist, ns);
+    even_slab_counts<<<blocks_for(a.m, kBlock), kBlock, 0, s>>>(a.rp, a.ci, a.m, w, ns, hist);
+}
+
 void mirror_slab_columns(const MirrorArgs& a, int64_t c0, int64_t c1, const uint32_t* skey, int64_t nrec,
                          uint32_t* first, uint32_t* end, int64_t* fl, int64_t strict_before, int64_t* f_rp,
                          void* scan_tmp, hipStream_t s) {
     const int64_t w = c1 - c0;
-    (void)hipMemsetAsync(first, 0, size_t(w) * sizeof(uint32_t), s);
-    (void)hipMemsetAsync(end, 0, size_t(w) * sizeof(uint32_t), s);
-    if (nrec > 0) slab_col_runs<<<blocks_for((nrec + 3) / 4, kBlock), kBlock, 0, s>>>(skey, nrec, first, end);
+    if (nrec <= 0 || skey) {  // columns without records keep an empty run
+        (void)hipMemsetAsync(first, 0, size_t(w) * sizeof(uint32_t), s);
+        (void)hipMemsetAsync(end, 0, size_t(w) * sizeof(uint32_t), s);
+    } else {
+        end = first + 1;
+    }
+    if (nrec > 0 && skey) slab_col_runs<<<blocks_for((nrec + 3) / 4, kBlock), kBlock, 0, s>>>(skey, nrec, first, end);
     slab_full_len<<<blocks_for(w + 1, kBlock), kBlock, 0, s>>>(a.rp, c0, w, first, end, fl);
     scan_i64(fl, f_rp + c0, w + 1, nullptr, scan_tmp, s);
     add_carry<<<blocks_for(w + 1, kBlock), kBlock, 0, s>>>(f_rp + c0, w + 1, a.rp + c0, strict_before);
@@ -368,19 +421,6 @@ void mirror_slab_extract(const MirrorArgs& a, int64_t c0, int64_t nrec, const in
         slab_extract<4><<<nb, kBlock, 0, s>>>(a.ci, a.val, a.m, c0, nrec, rec_rp, row_lo, trow, rkey, rrow, rval);
     else
         slab_extract<0><<<nb, kBlock, 0, s>>>(a.ci, a.val, a.m, c0, nrec, rec_rp, row_lo, trow, rkey, rrow, rval);
-}
-
-void mirror_slab_place(const MirrorArgs& a, int64_t c0, int64_t nrec, const uint32_t* skey, const uint32_t* srow,
-                       const void* sval, const uint32_t* first, const int64_t* f_rp, int32_t* f_ci, void* f_val,
-                       hipStream_t s) {
-    if (nrec <= 0) return;
-    const unsigned nb = blocks_for(nrec, kBlock);
-    if (a.vbytes == 8 && a.val)
-        slab_place<8><<<nb, kBlock, 0, s>>>(a.rp, c0, nrec, skey, srow, sval, first, f_rp, f_ci, f_val);
-    else if (a.vbytes == 4 && a.val)
-        slab_place<4><<<nb, kBlock, 0, s>>>(a.rp, c0, nrec, skey, srow, sval, first, f_rp, f_ci, f_val);
-    else
-        slab_place<0><<<nb, kBlock, 0, s>>>(a.rp, c0, nrec, skey, srow, sval, first, f_rp, f_ci, f_val);
 }
 
 }  // namespace spsyrk

@@ -35,7 +35,9 @@ struct ValT<8> {
     using T = uint64_t;
 };
 
-__global__ __launch_bounds__(kBlock) void radix_hist(const uint32_t* __restrict__ keys, int64_t n, int shift,
+// (KT: the keys' type, 32 bits, or 16 between the passes over a narrow mirror slab)
+template <typename KT>
+__global__ __launch_bounds__(kBlock) void radix_hist(const KT* __restrict__ keys, int64_t n, int shift,
                                                      uint32_t mask, uint32_t* __restrict__ hist, int64_t ntiles) {
     // consecutive tiles on one XCD, so that one L2 gathers their counts'
     // 4-byte writes (hist is digit-major: tile t of digit d at d * ntiles + t)
@@ -51,24 +53,21 @@ __global__ __launch_bounds__(kBlock) void radix_hist(const uint32_t* __restrict_
     __syncthreads();
     const int64_t base = tile * kRTile;
     if (base + kRTile <= n && (reinterpret_cast<uintptr_t>(keys) & 15) == 0) {
-        // whole tile, 16-byte loads (the tile starts at a multiple of 16 bytes)
-        uint4 kv[kRItems / 4];
+        // whole tile, four keys per load (the tile starts at a multiple of 16 bytes)
+        KT kv[kRItems];
 #pragma unroll
         for (int k = 0; k < kRItems / 4; ++k)
-            kv[k] = reinterpret_cast<const uint4*>(keys + base)[k * kBlock + threadIdx.x];
+            __builtin_memcpy(&kv[4 * k],
+                             __builtin_assume_aligned(keys + base + 4 * (k * kBlock + int(threadIdx.x)), 4 * sizeof(KT)),
+                             4 * sizeof(KT));
 #pragma unroll
-        for (int k = 0; k < kRItems / 4; ++k) {
-            atomicAdd(&cnt[w][(kv[k].x >> shift) & mask], 1u);
-            atomicAdd(&cnt[w][(kv[k].y >> shift) & mask], 1u);
-            atomicAdd(&cnt[w][(kv[k].z >> shift) & mask], 1u);
-            atomicAdd(&cnt[w][(kv[k].w >> shift) & mask], 1u);
-        }
+        for (int k = 0; k < kRItems; ++k) atomicAdd(&cnt[w][(uint32_t(kv[k]) >> shift) & mask], 1u);
     } else {
         uint32_t kk[kRItems];
 #pragma unroll
         for (int k = 0; k < kRItems; ++k) {
             const int64_t i = base + int64_t(k) * kBlock + threadIdx.x;
-            kk[k] = i < n ? keys[i] : 0xffffffffu;
+            kk[k] = i < n ? uint32_t(keys[i]) : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kRItems; ++k) {
@@ -84,6 +83,7 @@ __global__ __launch_bounds__(kBlock) void radix_hist(const uint32_t* __restrict_
 }
 
 constexpr int kRowWin = 1024;
+constexpr int kOffWin = 256;  // rows of a slab tile whose offsets are held in LDS
 
 __device__ inline int64_t last_leq_i64(const int64_t* a, int64_t lo, int64_t hi, int64_t x) {
     while (lo < hi) {
@@ -108,23 +108,42 @@ __device__ inline int64_t last_leq_i64(const int64_t* a, int64_t lo, int64_t hi,
 //    C_L: key = column - sl.c0, row = r, value = the
 //    entry's value.
 //  kOutArrays: key, row and value arrays in the pass's order.
-//  kOutPlace (last pass of a mirror slab): keys to key_out; the row and
-//    value of the record at sorted position q to the full rows, at
+//  kOutPlace (last pass of a mirror slab): the row and value of the record
+//    at sorted position q to the full rows, at
 //    sl.before + q + sl.rp[sl.c0 + key + 1] (its column's lower part, then
-//    the strict entries of the column in row order).
+//    the strict entries of the column in row order); kOutPlaceKeys also
+//    writes the keys to key_out, in the pass's order.
+// KI and KO are the types of the keys read (kSrcArrays) and written: 32 bits,
+// or 16 between the two passes over a slab of at most 2^16 columns.
 constexpr int kSrcArrays = 0, kSrcCsr = 1, kSrcSlab = 2;
-constexpr int kOutArrays = 0, kOutPlace = 1;
+constexpr int kOutArrays = 0, kOutPlace = 1, kOutPlaceKeys = 2;
 
 // rowof[i] = the row of record base + i of a tile of a record structure with
 // row pointers rp (rows [rlo, rhi] span the tile, rlo holding its first
 // record): every row that starts inside the tile marks its first record,
 // then a running maximum over the tile.  The rows are walked one by one, not
 // staged, so any number of empty rows may lie between (each row pointer is
-// read by about one tile).  Called by all threads; wt: kWavesPerBlock words.
+// read by about one tile); a tile of few rows compares with their starts
+// instead.  Called by all threads; wt: kWavesPerBlock words.
+constexpr int kMarkFew = 8;  // rows after the first that are told apart by comparisons
 __device__ inline void tile_rows_mark(const int64_t* __restrict__ rp, int64_t rlo, int64_t rhi, int64_t base,
                                       uint32_t* rowof, uint32_t* wt) {
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
+    if (rhi - rlo <= kMarkFew) {  // (uniform) long rows: compare with the few row starts
+        int32_t st[kMarkFew];     // in the tile, the rows' first records
+#pragma unroll
+        for (int k = 0; k < kMarkFew; ++k)
+            st[k] = rlo + 1 + k <= rhi ? int32_t(min(rp[rlo + 1 + k] - base, int64_t(kRTile))) : kRTile;
+        for (int i = threadIdx.x; i < kRTile; i += kBlock) {
+            uint32_t r = uint32_t(rlo);
+#pragma unroll
+            for (int k = 0; k < kMarkFew; ++k) r += i >= st[k] ? 1u : 0u;
+            rowof[i] = r;
+        }
+        __syncthreads();
+        return;
+    }
     for (int i = threadIdx.x; i < kRTile; i += kBlock) rowof[i] = uint32_t(rlo);
     __syncthreads();
     for (int64_t k = rlo + 1 + threadIdx.x; k <= rhi; k += kBlock) {
@@ -164,6 +183,7 @@ __global__ __launch_bounds__(kBlock) void radix_hist_slab(int64_t n, uint32_t ma
     __shared__ uint32_t rowof[kRTile];
     __shared__ uint32_t wt[kWavesPerBlock];
     __shared__ int64_t rb[2];
+    __shared__ int64_t off[kOffWin];  // the tile's rows' offsets from record to entry
     const int64_t per = (ntiles + kXcds - 1) / kXcds;  // (tiles placed as in radix_hist)
     const int64_t tile = int64_t(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
     if (tile >= ntiles) return;
@@ -176,15 +196,19 @@ __global__ __launch_bounds__(kBlock) void radix_hist_slab(int64_t n, uint32_t ma
         rb[1] = base + kRTile < n ? trow[tile + 1] : last_leq_i64(rp, trow[tile], m, n - 1);
     }
     __syncthreads();
-    tile_rows_mark(rp, rb[0], rb[1], base, rowof, wt);
+    const int64_t rlo = rb[0], rhi = rb[1];
+    const bool win = rhi - rlo < kOffWin;
+    if (win)
+        for (int k = threadIdx.x; k <= int(rhi - rlo); k += kBlock) off[k] = rlo + k < m ? sl.row_off[rlo + k] : 0;
+    tile_rows_mark(rp, rlo, rhi, base, rowof, wt);
     uint32_t key[kRItems];
 #pragma unroll
     for (int k = 0; k < kRItems; ++k) {
         const int64_t idx = base + int64_t(k) * kBlock + threadIdx.x;
         key[k] = 0;
         if (idx < n) {
-            const int64_t r = rowof[idx - base];
-            key[k] = uint32_t(int64_t(sl.ci[idx + sl.row_off[r]]) - sl.c0);
+            const uint32_t r = rowof[idx - base];
+            key[k] = uint32_t(int64_t(sl.ci[idx + (win ? off[r - uint32_t(rlo)] : sl.row_off[r])]) - sl.c0);
         }
     }
 #pragma unroll
@@ -197,37 +221,44 @@ __global__ __launch_bounds__(kBlock) void radix_hist_slab(int64_t n, uint32_t ma
     hist[int64_t(threadIdx.x) * ntiles + tile] = t;
 }
 
-template <int VB, int SRC, int OUT = kOutArrays>
-__global__ __launch_bounds__(kBlock) void radix_scatter(const uint32_t* __restrict__ key_in,
-                                                        const uint32_t* __restrict__ row_in,
-                                                        const typename ValT<VB>::T* __restrict__ val_in,
-                                                        uint32_t* __restrict__ key_out, uint32_t* __restrict__ row_out,
-                                                        typename ValT<VB>::T* __restrict__ val_out, int64_t n, int shift,
-                                                        uint32_t mask, const uint32_t* __restrict__ offs,
-                                                        int64_t ntiles, const int64_t* __restrict__ rp, int64_t m,
-                                                        const int64_t* __restrict__ trow, int rowbits, int lenbits,
-                                                        SlabIo sl) {
+// LDS of a scatter tile
+template <int VB, int SRC>
+struct ScatterLds {
+    uint32_t wcnt[kWavesPerBlock][kDigits];
+    uint32_t gofs[kDigits];  // global position of the tile's digit run minus its tile start (modulo 2^32)
+    uint32_t wt[kWavesPerBlock];
+    typename ValT<VB>::T ex[kRTile];  // the tile is reordered through one buffer, a field at a time
+    int64_t rbounds[SRC != kSrcArrays ? 2 : 1];
+    int64_t rwin[SRC == kSrcCsr ? kRowWin + 1 : 1];
+    int64_t off[SRC == kSrcSlab ? kOffWin : 1];  // the tile's rows' offsets from record to entry
+};
+
+// One tile of a scatter; FULL: a whole tile of kRTile records, where no
+// record needs a bounds check.  The instructions, not the memory, bound it
+// (about 130 vector instructions per wavefront and 64 records went to
+// ranking, bounds checks and addresses): the checks are compiled out of whole
+// tiles, the digits are matched with one three-input bit operation per digit
+// bit and half, and a slot's place is found once, from its key, and kept for
+// the key, the row and the value.  (115 M records of R-MAT's mirror, f32, 16-bit
+// keys: from C_L 1050 -> 700 us, into the full rows 565 -> 470; 67 M records
+// of 12 bytes from the column ids 501 -> 453 us.)
+template <int VB, int SRC, int OUT, typename KI, typename KO, bool FULL>
+__device__ void scatter_tile(ScatterLds<VB, SRC>& sh, int64_t tile, const KI* __restrict__ key_in,
+                             const uint32_t* __restrict__ row_in, const typename ValT<VB>::T* __restrict__ val_in,
+                             KO* __restrict__ key_out, uint32_t* __restrict__ row_out,
+                             typename ValT<VB>::T* __restrict__ val_out, int64_t n, int shift, uint32_t mask,
+                             const uint32_t* __restrict__ offs, int64_t ntiles, const int64_t* __restrict__ rp,
+                             int64_t m, const int64_t* __restrict__ trow, int rowbits, int lenbits,
+                             const SlabIo& sl) {
     using V = typename ValT<VB>::T;
     constexpr bool FIRST = SRC != kSrcArrays;  // records derived from a row structure
-    // consecutive tiles on one XCD (workgroups go round-robin over the XCDs),
-    // so the partial lines where their digit runs meet merge in one L2
-    const int64_t per = (ntiles + kXcds - 1) / kXcds;
-    const int64_t tile = int64_t(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-    if (tile >= ntiles) return;
-    __shared__ int64_t rwin[SRC == kSrcCsr ? kRowWin + 1 : 1];
-    __shared__ int64_t rbounds[2];
-    __shared__ uint32_t wcnt[kWavesPerBlock][kDigits];
-    __shared__ int64_t gofs[kDigits];  // global position of the tile's digit run minus its tile start
-    __shared__ uint32_t wt[kWavesPerBlock];
-    // the tile is reordered through one buffer, a field at a time
-    __shared__ V ex[kRTile];
-    __shared__ uint8_t dig[kRTile];
-    __shared__ uint16_t kslot[OUT == kOutPlace ? kRTile : 1];  // key of every slot (keys below 2^16)
-
+    constexpr bool PLACE = OUT != kOutArrays;  // records put into the full rows
     const int w = threadIdx.x / kWave;
     const int lane = lane_id();
     const int64_t base = tile * kRTile;
-    const int64_t segbase = base + int64_t(w) * kSeg;
+    const int tile_n = FULL ? kRTile : int(n - base);
+    const int seg = w * kSeg + lane;  // this lane's first record in the tile; its others follow every kWave
+    auto in = [&](int i) { return FULL || i < tile_n; };
     // the keys (the column ids in the first pass) are read once, with
     // streaming loads so that they do not push the tile's partly written
     // output lines out of L2, and first, so that they arrive while the tile
@@ -235,15 +266,14 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(const uint32_t* __restri
     uint32_t kr[kRItems];
     if constexpr (SRC != kSrcSlab) {
 #pragma unroll
-        for (int k = 0; k < kRItems; ++k) {
-            const int64_t idx = segbase + int64_t(k) * kWave + lane;
-            kr[k] = idx < n ? __builtin_nontemporal_load(key_in + idx) : 0u;
-        }
+        for (int k = 0; k < kRItems; ++k)
+            kr[k] = in(seg + k * kWave) ? uint32_t(__builtin_nontemporal_load(key_in + base + seg + k * kWave)) : 0u;
     }
 #pragma unroll
-    for (int q = 0; q < kWavesPerBlock; ++q) wcnt[q][threadIdx.x] = 0;
+    for (int q = 0; q < kWavesPerBlock; ++q) sh.wcnt[q][threadIdx.x] = 0;
     __syncthreads();
 
+    uint32_t* rowof = reinterpret_cast<uint32_t*>(sh.ex);  // row of every tile position (free until the reordering)
     int64_t rlo = 0, rhi = 0;
     bool rstaged = false;
     if constexpr (FIRST) {
@@ -256,41 +286,31 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(const uint32_t* __restri
             if (lo < 0) lo = last_leq_i64(rp, 0, m, base);
             int64_t hi = base + kRTile < n ? trow[tile + 1] : -1;
             if (hi < 0) hi = last_leq_i64(rp, lo, m, base + kRTile < n ? base + kRTile : n - 1);
-            rbounds[0] = lo;
-            rbounds[1] = hi;
+            sh.rbounds[0] = lo;
+            sh.rbounds[1] = hi;
         }
         __syncthreads();
-        rlo = rbounds[0];
-        rhi = rbounds[1];
+        rlo = sh.rbounds[0];
+        rhi = sh.rbounds[1];
         rstaged = SRC == kSrcCsr && rhi - rlo + 2 <= kRowWin + 1;
-        if constexpr (SRC == kSrcSlab) tile_rows_mark(rp, rlo, rhi, base, reinterpret_cast<uint32_t*>(ex), wt);
+        if constexpr (SRC == kSrcSlab) {
+            if (rhi - rlo < kOffWin)
+                for (int k = threadIdx.x; k <= int(rhi - rlo); k += kBlock) sh.off[k] = rlo + k < m ? sl.row_off[rlo + k] : 0;
+            tile_rows_mark(rp, rlo, rhi, base, rowof, sh.wt);
+        }
         if (rstaged) {
-            for (int64_t k = threadIdx.x; k < rhi - rlo + 2; k += kBlock) rwin[k] = rp[rlo + k];
-            // window row of every tile position (in the exchange buffer, free
-            // until the records are reordered): every non-empty row marks its
+            for (int64_t k = threadIdx.x; k < rhi - rlo + 2; k += kBlock) sh.rwin[k] = rp[rlo + k];
+            // window row of every tile position: every non-empty row marks its
             // first position, then a max-scan over the tile
-            uint32_t* rowof = reinterpret_cast<uint32_t*>(ex);
             for (int i = threadIdx.x; i < kRTile; i += kBlock) rowof[i] = 0;
             __syncthreads();
             for (int64_t k = 1 + threadIdx.x; k <= rhi - rlo; k += kBlock)
-                if (rwin[k] < rwin[k + 1] && rwin[k] - base < kRTile) rowof[rwin[k] - base] = uint32_t(k);
+                if (sh.rwin[k] < sh.rwin[k + 1] && sh.rwin[k] - base < kRTile) rowof[sh.rwin[k] - base] = uint32_t(k);
             __syncthreads();
-            uint32_t run_max = 0;
+            uint32_t run_max = 0, all;
 #pragma unroll
             for (int k = 0; k < kRItems; ++k) run_max = max(run_max, rowof[threadIdx.x * kRItems + k]);
-            // exclusive max over the preceding threads
-            uint32_t inc = run_max;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t u = __shfl_up(inc, d, kWave);
-                if (lane >= d) inc = max(inc, u);
-            }
-            if (lane == kWave - 1) wt[w] = inc;
-            __syncthreads();
-            uint32_t before = 0;
-            for (int q = 0; q < w; ++q) before = max(before, wt[q]);
-            const uint32_t prev = __shfl_up(inc, 1, kWave);
-            if (lane > 0) before = max(before, prev);
+            uint32_t before = block_exclusive_max(run_max, sh.wt, &all);
 #pragma unroll
             for (int k = 0; k < kRItems; ++k) {
                 before = max(before, rowof[threadIdx.x * kRItems + k]);
@@ -300,55 +320,61 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(const uint32_t* __restri
         __syncthreads();
     }
     // keys and tile positions stay in registers; the first pass also keeps
-    // its row fields (computed from the LDS window, which the exchange
-    // buffer overwrites), other passes load rows and values only when they
-    // are exchanged (fewer registers, more workgroups per compute unit), also
-    // with streaming loads
-    uint32_t rr[FIRST ? kRItems : 1], loc[kRItems];
+    // its row fields (found in the buffer that the reordering overwrites)
+    uint32_t rr[kRItems], loc[kRItems];
     const uint64_t lt = lanemask_lt();
-    // record idx of a slab (row r) is entry idx + row_off[r]
-    auto slab_entry = [&](int64_t idx, int64_t r) -> int64_t { return idx + sl.row_off[r]; };
-    // all of the segment's keys in flight at once, then the ranking
     // (a slab's values are loaded with their keys, so that each record's
     // entry is found once)
     V vpre[SRC == kSrcSlab && VB != 0 ? kRItems : 1];
     if constexpr (SRC == kSrcSlab) {
+        const bool win = rhi - rlo < kOffWin;
 #pragma unroll
         for (int k = 0; k < kRItems; ++k) {
-            const int64_t idx = segbase + int64_t(k) * kWave + lane;
-            const int64_t r = idx < n ? int64_t(reinterpret_cast<const uint32_t*>(ex)[idx - base]) : 0;
-            rr[k] = uint32_t(r);
-            const int64_t e = slab_entry(idx, r);
-            kr[k] = idx < n ? uint32_t(int64_t(sl.ci[e]) - sl.c0) : 0u;
-            if constexpr (VB != 0) vpre[k] = idx < n ? static_cast<const V*>(sl.val)[e] : V(0);
+            const int i = seg + k * kWave;
+            rr[k] = 0;
+            kr[k] = 0;
+            if constexpr (VB != 0) vpre[k] = V(0);
+            if (in(i)) {
+                // record p of row r is entry p + row_off[r]
+                const uint32_t r = rowof[i];
+                const int64_t e = base + i + (win ? sh.off[r - uint32_t(rlo)] : sl.row_off[r]);
+                rr[k] = r;
+                kr[k] = uint32_t(int64_t(sl.ci[e]) - sl.c0);
+                if constexpr (VB != 0) vpre[k] = static_cast<const V*>(sl.val)[e];
+            }
         }
     }
 #pragma unroll
     for (int k = 0; k < kRItems; ++k) {
-        const int64_t idx = segbase + int64_t(k) * kWave + lane;
-        const bool valid = idx < n;
-        const uint32_t key = kr[k];
-        const uint32_t d = (key >> shift) & mask;
-        uint64_t peers = __ballot(valid);
+        const bool valid = in(seg + k * kWave);
+        const uint32_t d = (kr[k] >> shift) & mask;
+        // the lanes with this digit: those whose digit bits all agree
+        uint32_t plo = 0xffffffffu, phi = 0xffffffffu;
+        if constexpr (!FULL) {
+            const uint64_t v = __ballot(valid);
+            plo = uint32_t(v);
+            phi = uint32_t(v >> 32);
+        }
 #pragma unroll
         for (int b = 0; b < kRBits; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bal = __ballot(bit);
-            peers &= bit ? bal : ~bal;
+            const uint32_t mine = uint32_t(__builtin_amdgcn_sbfe(int(d), b, 1));  // all ones or zero
+            const uint64_t bal = __ballot(mine != 0);
+            plo &= ~(uint32_t(bal) ^ mine);
+            phi &= ~(uint32_t(bal >> 32) ^ mine);
         }
-        uint32_t cur = 0;
-        if (valid) cur = wcnt[w][d];
-        const uint32_t rank = __popcll(peers & lt);
+        const uint32_t cur = sh.wcnt[w][d];
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
         loc[k] = cur + rank;
-        if (valid && rank == 0) wcnt[w][d] = cur + uint32_t(__popcll(peers));
+        if (valid && rank == 0) sh.wcnt[w][d] = cur + uint32_t(__popc(plo) + __popc(phi));
         if constexpr (SRC == kSrcCsr) {
             uint32_t field = 0;
             if (valid) {
+                const int64_t idx = base + seg + k * kWave;
                 int64_t r, len;
                 if (rstaged) {
-                    const int64_t rl = reinterpret_cast<const uint32_t*>(ex)[idx - base];
+                    const int64_t rl = rowof[seg + k * kWave];
                     r = rlo + rl;
-                    len = rwin[rl + 1] - rwin[rl];
+                    len = sh.rwin[rl + 1] - sh.rwin[rl];
                 } else {
                     r = last_leq_i64(rp, rlo, rhi, idx);
                     len = rp[r + 1] - rp[r];
@@ -362,6 +388,12 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(const uint32_t* __restri
             rr[k] = field;
         }
     }
+    // the rows of a later pass, on their way while the places are found
+    if constexpr (SRC == kSrcArrays) {
+#pragma unroll
+        for (int k = 0; k < kRItems; ++k)
+            rr[k] = in(seg + k * kWave) ? __builtin_nontemporal_load(row_in + base + seg + k * kWave) : 0u;
+    }
     __syncthreads();
     {
         const int d = threadIdx.x;
@@ -369,15 +401,15 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(const uint32_t* __restri
         uint32_t tot = 0;
 #pragma unroll
         for (int q = 0; q < kWavesPerBlock; ++q) {
-            c[q] = wcnt[q][d];
+            c[q] = sh.wcnt[q][d];
             tot += c[q];
         }
         uint32_t all;
-        uint32_t off = block_exclusive_scan(tot, wt, &all);
-        gofs[d] = int64_t(offs[int64_t(d) * ntiles + tile]) - int64_t(off);
+        uint32_t off = block_exclusive_scan(tot, sh.wt, &all);
+        sh.gofs[d] = offs[int64_t(d) * ntiles + tile] - off;
 #pragma unroll
         for (int q = 0; q < kWavesPerBlock; ++q) {
-            wcnt[q][d] = off;
+            sh.wcnt[q][d] = off;
             off += c[q];
         }
     }
@@ -385,70 +417,94 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(const uint32_t* __restri
     // tile positions of the records (registers), then keys, rows and values in turn
 #pragma unroll
     for (int k = 0; k < kRItems; ++k) {
-        const int64_t idx = segbase + int64_t(k) * kWave + lane;
-        if (idx < n) {
-            const uint32_t d = (kr[k] >> shift) & mask;
-            loc[k] += wcnt[w][d];
-            ex[loc[k]] = V(kr[k]);
-            dig[loc[k]] = uint8_t(d);
-            if constexpr (OUT == kOutPlace) kslot[loc[k]] = uint16_t(kr[k]);
+        if (in(seg + k * kWave)) {
+            loc[k] += sh.wcnt[w][(kr[k] >> shift) & mask];
+            sh.ex[loc[k]] = V(kr[k]);
         }
     }
-    __syncthreads();
-    const int tile_n = int(min(int64_t(kRTile), n - base));
-    for (int i = threadIdx.x; i < tile_n; i += kBlock) key_out[gofs[dig[i]] + i] = uint32_t(ex[i]);
-    __syncthreads();
-    if constexpr (FIRST) {
-#pragma unroll
-        for (int k = 0; k < kRItems; ++k)
-            if (segbase + int64_t(k) * kWave + lane < n) ex[loc[k]] = V(rr[k]);
-    } else {
-        uint32_t rv[kRItems];
-#pragma unroll
-        for (int k = 0; k < kRItems; ++k) {
-            const int64_t idx = segbase + int64_t(k) * kWave + lane;
-            rv[k] = idx < n ? __builtin_nontemporal_load(row_in + idx) : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < kRItems; ++k)
-            if (segbase + int64_t(k) * kWave + lane < n) ex[loc[k]] = V(rv[k]);
-    }
-    __syncthreads();
-    // full-row position of the record in slot i (kOutPlace)
-    auto place = [&](int i) -> int64_t {
-        const int64_t q = gofs[dig[i]] + i;
-        return sl.before + q + sl.rp[sl.c0 + int64_t(kslot[i]) + 1];
-    };
-    for (int i = threadIdx.x; i < tile_n; i += kBlock) {
-        if constexpr (OUT == kOutPlace)
-            sl.f_ci[place(i)] = int32_t(ex[i]);
-        else
-            row_out[gofs[dig[i]] + i] = uint32_t(ex[i]);
-    }
+    V vv[VB != 0 ? kRItems : 1];
     if constexpr (VB != 0) {
-        V vv[kRItems];
 #pragma unroll
         for (int k = 0; k < kRItems; ++k) {
-            const int64_t idx = segbase + int64_t(k) * kWave + lane;
+            const int i = seg + k * kWave;
             if constexpr (SRC == kSrcCsr)  // the entry index, or with val_in the entry's value
-                vv[k] = val_in ? (idx < n ? __builtin_nontemporal_load(val_in + idx) : V(0)) : V(idx);
+                vv[k] = val_in ? (in(i) ? __builtin_nontemporal_load(val_in + base + i) : V(0)) : V(base + i);
             else if constexpr (SRC == kSrcSlab)
                 vv[k] = vpre[k];
             else
-                vv[k] = idx < n ? __builtin_nontemporal_load(val_in + idx) : V(0);
+                vv[k] = in(i) ? __builtin_nontemporal_load(val_in + base + i) : V(0);
         }
+    }
+    __syncthreads();
+    // places of this thread's slots: in the sorted order, or (PLACE) in the full rows
+    using P = std::conditional_t<PLACE, int64_t, uint32_t>;
+    P pos[kRItems];
+#pragma unroll
+    for (int k = 0; k < kRItems; ++k) {
+        const int i = k * kBlock + int(threadIdx.x);
+        if (!in(i)) continue;
+        const uint32_t key = uint32_t(sh.ex[i]);
+        const uint32_t q = sh.gofs[(key >> shift) & mask] + uint32_t(i);
+        if constexpr (OUT != kOutPlace) key_out[q] = KO(key);
+        if constexpr (PLACE)
+            pos[k] = sl.before + int64_t(q) + sl.rp[sl.c0 + int64_t(key) + 1];
+        else
+            pos[k] = q;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRItems; ++k)
+        if (in(seg + k * kWave)) sh.ex[loc[k]] = V(rr[k]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRItems; ++k) {
+        const int i = k * kBlock + int(threadIdx.x);
+        if (!in(i)) continue;
+        if constexpr (PLACE)
+            sl.f_ci[pos[k]] = int32_t(sh.ex[i]);
+        else
+            row_out[pos[k]] = uint32_t(sh.ex[i]);
+    }
+    if constexpr (VB != 0) {
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kRItems; ++k)
-            if (segbase + int64_t(k) * kWave + lane < n) ex[loc[k]] = vv[k];
+            if (in(seg + k * kWave)) sh.ex[loc[k]] = vv[k];
         __syncthreads();
-        for (int i = threadIdx.x; i < tile_n; i += kBlock) {
-            if constexpr (OUT == kOutPlace)
-                static_cast<V*>(sl.f_val)[place(i)] = ex[i];
+#pragma unroll
+        for (int k = 0; k < kRItems; ++k) {
+            const int i = k * kBlock + int(threadIdx.x);
+            if (!in(i)) continue;
+            if constexpr (PLACE)
+                static_cast<V*>(sl.f_val)[pos[k]] = sh.ex[i];
             else
-                val_out[gofs[dig[i]] + i] = ex[i];
+                val_out[pos[k]] = sh.ex[i];
         }
     }
+}
+
+template <int VB, int SRC, int OUT, typename KI, typename KO>
+__global__ __launch_bounds__(kBlock) void radix_scatter(const KI* __restrict__ key_in,
+                                                        const uint32_t* __restrict__ row_in,
+                                                        const typename ValT<VB>::T* __restrict__ val_in,
+                                                        KO* __restrict__ key_out, uint32_t* __restrict__ row_out,
+                                                        typename ValT<VB>::T* __restrict__ val_out, int64_t n, int shift,
+                                                        uint32_t mask, const uint32_t* __restrict__ offs,
+                                                        int64_t ntiles, const int64_t* __restrict__ rp, int64_t m,
+                                                        const int64_t* __restrict__ trow, int rowbits, int lenbits,
+                                                        SlabIo sl) {
+    __shared__ ScatterLds<VB, SRC> sh;
+    // consecutive tiles on one XCD (workgroups go round-robin over the XCDs),
+    // so the partial lines where their digit runs meet merge in one L2
+    const int64_t per = (ntiles + kXcds - 1) / kXcds;
+    const int64_t tile = int64_t(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+    if (tile >= ntiles) return;
+    if ((tile + 1) * kRTile <= n)
+        scatter_tile<VB, SRC, OUT, KI, KO, true>(sh, tile, key_in, row_in, val_in, key_out, row_out, val_out, n, shift,
+                                                 mask, offs, ntiles, rp, m, trow, rowbits, lenbits, sl);
+    else
+        scatter_tile<VB, SRC, OUT, KI, KO, false>(sh, tile, key_in, row_in, val_in, key_out, row_out, val_out, n, shift,
+                                                  mask, offs, ntiles, rp, m, trow, rowbits, lenbits, sl);
 }
 
 // ---- local sort of the low key bits inside groups of equal high bits
@@ -533,7 +589,8 @@ __global__ __launch_bounds__(kBlock) void digit_starts(const uint32_t* __restric
 // one workgroup per d1: the d2 counts of tile t1 before first1[d1] (keys:
 // the first pass's output), then the starts of groups (d2, d1) for every d2
 // (hist: the second pass's scanned histogram)
-__global__ __launch_bounds__(kBlock) void group_starts(const uint32_t* __restrict__ key, int64_t n, int L, int w1,
+template <typename KT>
+__global__ __launch_bounds__(kBlock) void group_starts(const KT* __restrict__ key, int64_t n, int L, int w1,
                                                        int w2, const uint32_t* __restrict__ first1,
                                                        const uint32_t* __restrict__ hist, int64_t ntiles,
                                                        uint32_t* __restrict__ gstart) {
@@ -546,7 +603,7 @@ __global__ __launch_bounds__(kBlock) void group_starts(const uint32_t* __restric
     const int64_t t1 = f / kRTile;
     const uint32_t m2 = uint32_t(nd2 - 1);
     if (t1 < ntiles)
-        for (int64_t p = t1 * kRTile + threadIdx.x; p < f; p += kBlock) atomicAdd(&cnt[(key[p] >> (L + w1)) & m2], 1u);
+        for (int64_t p = t1 * kRTile + threadIdx.x; p < f; p += kBlock) atomicAdd(&cnt[(uint32_t(key[p]) >> (L + w1)) & m2], 1u);
     __syncthreads();
     const int d2 = threadIdx.x;
     if (d2 < nd2) {
@@ -992,8 +1049,8 @@ __global__ __launch_bounds__(kBlock) void local_sort_pack_big(uint32_t* __restri
     }
 }
 
-template <int VB, int SRC = kSrcArrays, int OUT = kOutArrays>
-void run_pass(const uint32_t* ki, const uint32_t* ri, const void* vi, uint32_t* ko, uint32_t* ro, void* vo, int64_t n,
+template <int VB, int SRC = kSrcArrays, int OUT = kOutArrays, typename KI = uint32_t, typename KO = uint32_t>
+void run_pass(const KI* ki, const uint32_t* ri, const void* vi, KO* ko, uint32_t* ro, void* vo, int64_t n,
               int shift, uint32_t mask, uint32_t* hist, void* scan_tmp, hipStream_t s, const int64_t* rp = nullptr,
               int64_t m = 0, const int64_t* trow = nullptr, int rowbits = 0, int lenbits = 0,
               const SlabIo& sl = SlabIo(), bool counted = false) {
@@ -1003,9 +1060,9 @@ void run_pass(const uint32_t* ki, const uint32_t* ri, const void* vi, uint32_t* 
     if constexpr (SRC == kSrcSlab)
         radix_hist_slab<<<dim3(grid), dim3(kBlock), 0, s>>>(n, mask, hist, ntiles, rp, m, trow, sl);
     else if (!counted)
-        radix_hist<<<dim3(grid), dim3(kBlock), 0, s>>>(ki, n, shift, mask, hist, ntiles);
+        radix_hist<KI><<<dim3(grid), dim3(kBlock), 0, s>>>(ki, n, shift, mask, hist, ntiles);
     scan_u32(hist, hist, ntiles * kDigits, nullptr, scan_tmp, s);
-    radix_scatter<VB, SRC, OUT><<<dim3(unsigned((ntiles + kXcds - 1) / kXcds * kXcds)), dim3(kBlock), 0, s>>>(
+    radix_scatter<VB, SRC, OUT, KI, KO><<<dim3(grid), dim3(kBlock), 0, s>>>(
         ki, ri, static_cast<const V*>(vi), ko, ro, static_cast<V*>(vo), n, shift, mask, hist, ntiles, rp, m, trow, rowbits,
         lenbits, sl);
 }
@@ -1226,15 +1283,17 @@ int radix_sort(uint32_t* key_a, uint32_t* key_b, uint32_t* row_a, uint32_t* row_
     return cur;
 }
 
-// A mirror slab sorted by (column, row) in one or two passes (keys of at
-// most 16 bits), the last pass putting rows and values into the full rows;
-// the first pass reads its records straight from C_L, or, with extracted,
-// from the record arrays key_a, row_a, val_a.  Returns the buffer with the
-// sorted keys (for the column runs).
-uint32_t* slab_sort_place(const SlabIo& io, int vbytes, int64_t nrec, int nbits, const int64_t* rec_rp, int64_t m,
-                          bool extracted, uint32_t* key_a, uint32_t* key_b, uint32_t* row_a, uint32_t* row_b,
-                          void* val_a, void* val_b, void* tmp, hipStream_t s) {
-    if (nrec <= 0) return key_a;
+// A mirror slab sorted by (column, row), the last pass putting rows and values
+// into the full rows; the first pass reads its records straight from C_L, or,
+// with extracted, from the record arrays key_a, row_a, val_a.  Keys of at most
+// 16 bits (one or two passes) are held in 16 bits between the passes, and the
+// columns' first records are read off the passes' histograms into starts
+// (2^nbits + 1 words, then kDigits + 1 of scratch), returning null; wider keys
+// are written out sorted for the column runs, in the returned buffer.
+const uint32_t* slab_sort_place(const SlabIo& io, int vbytes, int64_t nrec, int nbits, const int64_t* rec_rp,
+                                int64_t m, bool extracted, uint32_t* key_a, uint32_t* key_b, uint32_t* row_a,
+                                uint32_t* row_b, void* val_a, void* val_b, uint32_t* starts, void* tmp,
+                                hipStream_t s) {
     const int64_t ntiles = (nrec + kRTile - 1) / kRTile;
     uint32_t* hist = static_cast<uint32_t*>(tmp);
     const size_t hist_bytes = (size_t(ntiles) * kDigits * sizeof(uint32_t) + 255) & ~size_t(255);
@@ -1244,31 +1303,56 @@ uint32_t* slab_sort_place(const SlabIo& io, int vbytes, int64_t nrec, int nbits,
     if (!extracted) tile_first_rows(rec_rp, m, kRTile, trow, s);
     int width[8];
     const int passes = digit_plan(nbits, width);
-    const uint32_t m0 = (1u << width[0]) - 1u;
-    uint32_t* out = key_b;
+    auto mask = [&](int ps) { return (1u << width[ps]) - 1u; };
+    const uint32_t* none = nullptr;
+    const uint32_t* sorted = nullptr;
+    uint16_t* kh = reinterpret_cast<uint16_t*>(key_b);  // 16-bit keys between two passes
+    uint32_t* first1 = starts + (size_t(1) << nbits) + 1;
     auto go = [&](auto vb) {
         constexpr int VB = decltype(vb)::value;
-        if (extracted) {
-            if (passes == 1) {
-                run_pass<VB, kSrcArrays, kOutPlace>(key_a, row_a, val_a, key_b, nullptr, nullptr, nrec, 0, m0, hist,
+        if (passes == 1) {
+            if (extracted)
+                run_pass<VB, kSrcArrays, kOutPlace>(key_a, row_a, val_a, key_b, nullptr, nullptr, nrec, 0, mask(0), hist,
                                                     scan_tmp, s, nullptr, 0, nullptr, 0, 0, io);
-            } else {
-                run_pass<VB>(key_a, row_a, val_a, key_b, row_b, val_b, nrec, 0, m0, hist, scan_tmp, s);
-                run_pass<VB, kSrcArrays, kOutPlace>(key_b, row_b, val_b, key_a, nullptr, nullptr, nrec, width[0],
-                                                    (1u << width[1]) - 1u, hist, scan_tmp, s, nullptr, 0, nullptr, 0,
-                                                    0, io);
-                out = key_a;
-            }
-        } else if (passes == 1) {
-            run_pass<VB, kSrcSlab, kOutPlace>(nullptr, nullptr, nullptr, key_b, nullptr, nullptr, nrec, 0, m0, hist,
-                                              scan_tmp, s, rec_rp, m, trow, 0, 0, io);
-        } else {
-            run_pass<VB, kSrcSlab>(nullptr, nullptr, nullptr, key_a, row_a, val_a, nrec, 0, m0, hist, scan_tmp, s,
-                                   rec_rp, m, trow, 0, 0, io);
-            run_pass<VB, kSrcArrays, kOutPlace>(key_a, row_a, val_a, key_b, nullptr, nullptr, nrec, width[0],
-                                                (1u << width[1]) - 1u, hist, scan_tmp, s, nullptr, 0, nullptr, 0, 0,
-                                                io);
+            else
+                run_pass<VB, kSrcSlab, kOutPlace>(none, nullptr, nullptr, key_b, nullptr, nullptr, nrec, 0, mask(0),
+                                                  hist, scan_tmp, s, rec_rp, m, trow, 0, 0, io);
+            digit_starts<<<1, kBlock, 0, s>>>(hist, ntiles, 1 << width[0], starts, nrec, nullptr);
+            return;
         }
+        if (passes == 2) {
+            if (extracted)
+                run_pass<VB>(key_a, row_a, val_a, kh, row_b, val_b, nrec, 0, mask(0), hist, scan_tmp, s);
+            else
+                run_pass<VB, kSrcSlab>(none, nullptr, nullptr, kh, row_b, val_b, nrec, 0, mask(0), hist, scan_tmp, s,
+                                       rec_rp, m, trow, 0, 0, io);
+            digit_starts<<<1, kBlock, 0, s>>>(hist, ntiles, 1 << width[0], first1, nrec, nullptr);
+            run_pass<VB, kSrcArrays, kOutPlace>(static_cast<const uint16_t*>(kh), row_b, val_b, kh, nullptr, nullptr,
+                                                nrec, width[0], mask(1), hist, scan_tmp, s, nullptr, 0, nullptr, 0, 0,
+                                                io);
+            group_starts<<<1u << width[0], kBlock, 0, s>>>(static_cast<const uint16_t*>(kh), nrec, 0, width[0], width[1],
+                                                           first1, hist, ntiles, starts);
+            return;
+        }
+        uint32_t *ki = key_a, *ko = key_b, *ri = row_a, *ro = row_b;
+        void *vi = val_a, *vo = val_b;
+        int shift = 0;
+        for (int ps = 0; ps < passes; shift += width[ps], ++ps) {
+            if (ps == passes - 1)
+                run_pass<VB, kSrcArrays, kOutPlaceKeys>(static_cast<const uint32_t*>(ki), ri, vi, ko, nullptr, nullptr,
+                                                        nrec, shift, mask(ps), hist, scan_tmp, s, nullptr, 0, nullptr,
+                                                        0, 0, io);
+            else if (ps == 0 && !extracted)
+                run_pass<VB, kSrcSlab>(none, nullptr, nullptr, ko, ro, vo, nrec, 0, mask(0), hist, scan_tmp, s, rec_rp,
+                                       m, trow, 0, 0, io);
+            else
+                run_pass<VB>(static_cast<const uint32_t*>(ki), ri, vi, ko, ro, vo, nrec, shift, mask(ps), hist, scan_tmp,
+                             s);
+            std::swap(ki, ko);
+            std::swap(ri, ro);
+            std::swap(vi, vo);
+        }
+        sorted = ki;
     };
     if (vbytes == 8)
         go(std::integral_constant<int, 8>());
@@ -1276,7 +1360,7 @@ uint32_t* slab_sort_place(const SlabIo& io, int vbytes, int64_t nrec, int nbits,
         go(std::integral_constant<int, 4>());
     else
         go(std::integral_constant<int, 0>());
-    return out;
+    return sorted;
 }
 
 }  // namespace spsyrk
