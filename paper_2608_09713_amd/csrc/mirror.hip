@@ -87,7 +87,7 @@ static_assert(kTileC == kTileE, "one tile table serves the walks and the copies"
 // memory: the tile's entries are loaded first, 16 per thread in flight, while
 // the rows are found: every row that starts in the tile marks its first entry,
 // then a running maximum over the tile, so that no entry searches for its row.
-// (60 M entries in rows of about 29, i32: 393 us with a search per entry, 311
+// (60 M entries in rows of about 57, i32: 393 us with a search per entry, 311
 // so; 230 M entries in R-MAT's rows, f32: 920 us, 781 so)
 template <int VB>
 __global__ __launch_bounds__(kBlock) void copy_lower(const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,

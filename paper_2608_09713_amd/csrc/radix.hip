@@ -221,6 +221,25 @@ __global__ __launch_bounds__(kBlock) void radix_hist_slab(int64_t n, uint32_t ma
     hist[int64_t(threadIdx.x) * ntiles + tile] = t;
 }
 
+// The lanes of valid lanes' mask (plo, phi) whose value agrees with this
+// lane's d in every one of the bits below w: one ballot and one three-input
+// operation per half and bit.  Called by all lanes.
+__device__ inline void match_lanes(uint32_t d, int w, uint32_t& plo, uint32_t& phi) {
+#pragma unroll
+    for (int b = 0; b < kRBits; ++b) {
+        if (b >= w) break;
+        const uint32_t mine = uint32_t(__builtin_amdgcn_sbfe(int(d), b, 1));  // all ones or zero
+        const uint64_t bal = __ballot(mine != 0);
+        plo &= ~(uint32_t(bal) ^ mine);
+        phi &= ~(uint32_t(bal >> 32) ^ mine);
+    }
+}
+// the lanes of the mask before this one, and all of them
+__device__ inline uint32_t lanes_before(uint32_t plo, uint32_t phi) {
+    return __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+}
+__device__ inline uint32_t lanes_all(uint32_t plo, uint32_t phi) { return uint32_t(__popc(plo) + __popc(phi)); }
+
 // LDS of a scatter tile
 template <int VB, int SRC>
 struct ScatterLds {
@@ -240,7 +259,7 @@ struct ScatterLds {
 // tiles, the digits are matched with one three-input bit operation per digit
 // bit and half, and a slot's place is found once, from its key, and kept for
 // the key, the row and the value.  (115 M records of R-MAT's mirror, f32, 16-bit
-// keys: from C_L 1050 -> 700 us, into the full rows 565 -> 470; 67 M records
+// keys: from C_L 1050 -> 700 us, into the full rows 565 -> 470; 134 M records
 // of 12 bytes from the column ids 501 -> 453 us.)
 template <int VB, int SRC, int OUT, typename KI, typename KO, bool FULL>
 __device__ void scatter_tile(ScatterLds<VB, SRC>& sh, int64_t tile, const KI* __restrict__ key_in,
@@ -322,7 +341,6 @@ __device__ void scatter_tile(ScatterLds<VB, SRC>& sh, int64_t tile, const KI* __
     // keys and tile positions stay in registers; the first pass also keeps
     // its row fields (found in the buffer that the reordering overwrites)
     uint32_t rr[kRItems], loc[kRItems];
-    const uint64_t lt = lanemask_lt();
     // (a slab's values are loaded with their keys, so that each record's
     // entry is found once)
     V vpre[SRC == kSrcSlab && VB != 0 ? kRItems : 1];
@@ -355,17 +373,11 @@ __device__ void scatter_tile(ScatterLds<VB, SRC>& sh, int64_t tile, const KI* __
             plo = uint32_t(v);
             phi = uint32_t(v >> 32);
         }
-#pragma unroll
-        for (int b = 0; b < kRBits; ++b) {
-            const uint32_t mine = uint32_t(__builtin_amdgcn_sbfe(int(d), b, 1));  // all ones or zero
-            const uint64_t bal = __ballot(mine != 0);
-            plo &= ~(uint32_t(bal) ^ mine);
-            phi &= ~(uint32_t(bal >> 32) ^ mine);
-        }
+        match_lanes(d, kRBits, plo, phi);
         const uint32_t cur = sh.wcnt[w][d];
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+        const uint32_t rank = lanes_before(plo, phi);
         loc[k] = cur + rank;
-        if (valid && rank == 0) sh.wcnt[w][d] = cur + uint32_t(__popc(plo) + __popc(phi));
+        if (valid && rank == 0) sh.wcnt[w][d] = cur + lanes_all(plo, phi);
         if constexpr (SRC == kSrcCsr) {
             uint32_t field = 0;
             if (valid) {
@@ -630,7 +642,6 @@ __device__ inline void lds_pass(const uint16_t* dig_in, const uint16_t* idx_in, 
     const int s0 = wv * seg, s1 = min(S, s0 + seg);
     wcnt[wv][lane] = 0;
     __syncthreads();
-    const uint64_t lt = lanemask_lt();
     const int nch = seg / kWave;  // (the same in every wavefront)
     uint32_t loc[kCh];
     uint32_t dd[kCh];
@@ -640,18 +651,15 @@ __device__ inline void lds_pass(const uint16_t* dig_in, const uint16_t* idx_in, 
         const int i = s0 + c * kWave + lane;
         const bool valid = i < s1;
         const uint32_t d = valid ? (uint32_t(dig_in[i]) >> sh) & m : 0u;
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < w; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bal = __ballot(bit);
-            peers &= bit ? bal : ~bal;
-        }
+        const uint64_t live = __ballot(valid);
+        uint32_t plo = uint32_t(live), phi = uint32_t(live >> 32);
+        match_lanes(d, w, plo, phi);
         uint32_t cur = 0;
         if (valid) cur = wcnt[wv][d];
-        const uint32_t rank = __popcll(peers & lt);
+        const uint32_t rank = lanes_before(plo, phi);
         loc[c] = cur + rank;
         dd[c] = d;
-        if (valid && rank == 0) wcnt[wv][d] = cur + uint32_t(__popcll(peers));
+        if (valid && rank == 0) wcnt[wv][d] = cur + lanes_all(plo, phi);
     }
     __syncthreads();
     {
@@ -699,22 +707,18 @@ __device__ inline void group_pass(const uint32_t* ki, const uint32_t* ri, const 
         if (threadIdx.x < (1 << kLDig)) base[threadIdx.x] = off;
     }
     __syncthreads();
-    const uint64_t lt = lanemask_lt();
     for (int64_t t0 = 0; t0 < S; t0 += kBlock) {
         const int64_t i = t0 + threadIdx.x;
         const bool valid = i < S;
         const uint32_t kv = valid ? ki[b0 + i] : 0u;
         const uint32_t d = (kv >> sh) & m;
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < w; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bal = __ballot(bit);
-            peers &= bit ? bal : ~bal;
-        }
-        const uint32_t rank = __popcll(peers & lt);
+        const uint64_t live = __ballot(valid);
+        uint32_t plo = uint32_t(live), phi = uint32_t(live >> 32);
+        match_lanes(d, w, plo, phi);
+        const uint32_t rank = lanes_before(plo, phi);
         wcnt[wv][lane] = 0;
         __syncthreads();
-        if (valid && rank == 0) wcnt[wv][d] = uint32_t(__popcll(peers));
+        if (valid && rank == 0) wcnt[wv][d] = lanes_all(plo, phi);
         __syncthreads();
         uint32_t before = 0;
         for (int q = 0; q < wv; ++q) before += wcnt[q][d];

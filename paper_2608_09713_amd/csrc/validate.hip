@@ -3,13 +3,19 @@
 // One kernel checks both arrays: workgroup b checks the row pointers of rows
 // [b*kTileR, (b+1)*kTileR) and the column ids of entry tile t(b) (tiles of
 // kTileE, the radix passes' tiles, dealt to the XCDs in consecutive runs as
-// the passes deal them), whose digits it can count for the first radix pass.  Every thread walks a contiguous stretch of entries row by
-// row, starting from the row of its first entry (searched in an LDS window of
-// the row pointers).  The rows of the workgroup's first entry and of its end
+// the passes deal them), whose digits it can count for the first radix pass.
+// The tile's rows mark the entries they start at in a bit mask, so that every
+// thread compares a contiguous stretch of entries with their predecessors
+// without knowing their rows; an entry above the diagonal is looked for at
+// each row's last entry of the tile, which is its largest when the tile is in
+// order.  A tile of very many rows, and a tile out of order whose entries
+// above the diagonal are wanted too, is walked row by row, from a search of
+// the row pointers.  The rows of the workgroup's first entry and of its end
 // come from a table written by the rows themselves; a row with out-of-range
 // pointers writes nothing, and a missing or inconsistent entry falls back to
 // a search.  On a malformed row_ptr every access still stays in bounds (the
 // results are then meaningless, but the row check has raised its flag).
+// (134 M entries in rows of 16: walked row by row 148 us, 120 us so.)
 #include "common.h"
 #include "internal.h"
 
@@ -18,7 +24,7 @@ namespace {
 
 constexpr int kTileR = 4096;  // row pointers per workgroup
 constexpr int kTileE = kRadixTile;  // entries per workgroup
-constexpr int kWinV = 2048;   // rows held in LDS
+constexpr int kRowsE = 4 * kTileE;  // rows of a tile that mark their entries
 constexpr int kPerE = kTileE / kBlock;
 
 __device__ inline int64_t find_row(const int64_t* rp, int64_t lo, int64_t hi, int64_t e) {
@@ -51,11 +57,12 @@ __global__ __launch_bounds__(kBlock) void entry_tile_rows(const int64_t* __restr
 __global__ __launch_bounds__(kBlock) void check_csr(const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                                     int64_t m, int64_t n, int64_t nnz, bool upper_forbidden,
                                                     const int64_t* __restrict__ trow, uint32_t* err, FirstHist fh) {
-    __shared__ int64_t win[kWinV + 1];
+    __shared__ uint32_t starts[kTileE / 32 + 1];  // bit i: a row starts at entry i of the tile
     __shared__ int64_t bounds[2];
     __shared__ uint32_t bad_s;
     __shared__ uint32_t cnt[kWavesPerBlock][256];  // (digit counts, with fh.hist)
     if (threadIdx.x == 0) bad_s = 0;
+    for (int x = threadIdx.x; x < kTileE / 32 + 1; x += kBlock) starts[x] = 0;
     if (fh.hist)
         for (int q = 0; q < kWavesPerBlock; ++q) cnt[q][threadIdx.x] = 0;
     __syncthreads();  // (a workgroup with no entries meets no other barrier before its atomics)
@@ -88,21 +95,15 @@ __global__ __launch_bounds__(kBlock) void check_csr(const int64_t* __restrict__ 
         }
         __syncthreads();
         const int64_t rlo = bounds[0], rhi = bounds[1];
-        // (rhi < m always holds for a valid row_ptr; the window reads rp[rhi + 1])
-        const bool staged = rhi >= rlo && rhi < m && rhi - rlo + 2 <= kWinV + 1;
-        if (staged)
-            for (int64_t k = threadIdx.x; k < rhi - rlo + 2; k += kBlock) win[k] = rp[rlo + k];
-        __syncthreads();
-        // every thread walks kPerE contiguous entries, row by row
+        // (rhi < m always holds for a valid row_ptr)
+        bool marked = rhi >= rlo && rhi < m && rhi - rlo < kRowsE;
         const int64_t ea = e0 + int64_t(threadIdx.x) * kPerE;
         const int64_t eb = min(e1, ea + kPerE);
+        // the stretch's column ids, by 16-byte loads when whole and aligned
+        int32_t cc[kPerE];
+        int32_t prev = -1;
         if (ea < eb) {
-            int64_t r = staged ? rlo + find_row(win, 0, rhi - rlo, ea) : find_row(rp, 0, m, ea);
-            int64_t rend = r < m ? (staged ? win[r - rlo + 1] : rp[r + 1]) : nnz;
-            int32_t prev = ea > 0 ? ci[ea - 1] : -1;
-            bool first = staged ? win[r - rlo] == ea : rp[r] == ea;
-            // the stretch's column ids, by 16-byte loads when whole and aligned
-            int32_t cc[kPerE];
+            if (ea > 0) prev = ci[ea - 1];
             if (eb - ea == kPerE && (reinterpret_cast<uintptr_t>(ci + ea) & 15) == 0) {
                 const int4* v4 = reinterpret_cast<const int4*>(ci + ea);
 #pragma unroll
@@ -117,6 +118,36 @@ __global__ __launch_bounds__(kBlock) void check_csr(const int64_t* __restrict__ 
 #pragma unroll
                 for (int u = 0; u < kPerE; ++u) cc[u] = ea + u < eb ? ci[ea + u] : 0;
             }
+        }
+        if (marked) {
+            for (int64_t r = rlo + threadIdx.x; r <= rhi; r += kBlock) {
+                const int64_t a = rp[r], z = rp[r + 1];
+                const int64_t hi = min(z, e1);
+                if (hi <= max(a, e0)) continue;  // no entry in the tile
+                if (a >= e0) atomicOr(&starts[(a - e0) >> 5], 1u << ((a - e0) & 31));
+                if (upper_forbidden && int64_t(ci[hi - 1]) > r) bad |= kErrUpper;
+            }
+            __syncthreads();
+            if (ea < eb) {
+                const int bit = int(threadIdx.x) * kPerE;
+                const uint64_t two = (uint64_t(starts[(bit >> 5) + 1]) << 32) | starts[bit >> 5];
+                const uint32_t first = uint32_t(two >> (bit & 31));
+                const uint32_t lim = uint32_t(min(n, int64_t(1) << 31));  // (a negative id is past it)
+                int32_t before = prev;
+#pragma unroll
+                for (int u = 0; u < kPerE; ++u) {
+                    if (ea + u >= eb) break;
+                    if (uint32_t(cc[u]) >= lim) bad |= kErrColRange;
+                    if (before >= cc[u] && !((first >> u) & 1u)) bad |= kErrColOrder;
+                    before = cc[u];
+                }
+            }
+            if (upper_forbidden && __syncthreads_or(int(bad & kErrColOrder))) marked = false;
+        }
+        if (!marked && ea < eb) {
+            int64_t r = find_row(rp, 0, m, ea);
+            int64_t rend = r < m ? rp[r + 1] : nnz;
+            bool first = rp[r] == ea;
 #pragma unroll
             for (int u = 0; u < kPerE; ++u) {
                 const int64_t e = ea + u;
@@ -126,7 +157,7 @@ __global__ __launch_bounds__(kBlock) void check_csr(const int64_t* __restrict__ 
                     // next non-empty row (a malformed row_ptr ends the walk at row m)
                     while (e >= rend && r < m) {
                         ++r;
-                        rend = r < m ? (staged && r <= rhi ? win[r - rlo + 1] : rp[r + 1]) : nnz;
+                        rend = r < m ? rp[r + 1] : nnz;
                     }
                     first = true;
                 }
@@ -136,6 +167,8 @@ __global__ __launch_bounds__(kBlock) void check_csr(const int64_t* __restrict__ 
                 prev = c;
                 first = false;
             }
+        }
+        if (ea < eb) {
             if (fh.hist) {
 #pragma unroll
                 for (int u = 0; u < kPerE; ++u)
