@@ -339,7 +339,7 @@ typedef struct spsyrk_stats {
     int64_t nnz_out;          /* entries in the result */
     int64_t csc_entries;      /* entries kept in the column index built from the right operand */
     int64_t heavy_rows;       /* rows routed to the dense-tile accumulator */
-    int64_t light_rows;       /* rows handled by the batched ordered-bucket accumulator */
+    int64_t light_rows;       /* rows handled by the light-row kernels */
     int64_t products;         /* multiply-adds formed off the diagonal (lower) or in total (offdiag) */
     int64_t heavy_entries;    /* entries of the left operand in heavy rows */
     int64_t heavy_nnz_out;    /* result entries of heavy rows */

@@ -1,5 +1,5 @@
 """The mirror's column slabs: tiles of few long rows and of many short or empty
-ones, keys of one, two and three digit passes, slabs of equal width at and past
+ones, keys of one to four digit passes, slabs of equal width at and past
 the number counted by row searches; against the oracle, bit for bit."""
 import numpy as np
 import pytest
@@ -24,11 +24,15 @@ def _raw(dev, rp, ci, n, vals=None):
 
 
 def _lower(rng, m, lens):
-    """lower-triangular rows of the given lengths (at most row + 1)"""
-    rows = [np.sort(rng.choice(i + 1, size=min(i + 1, int(n)), replace=False)) for i, n in enumerate(lens)]
+    """lower-triangular rows of about the given lengths (at most row + 1)"""
+    rows = np.flatnonzero(lens)
+    cols = [np.sort(rng.choice(i + 1, size=min(i + 1, int(lens[i])), replace=False)) if 8 * lens[i] > i
+            else np.unique(rng.integers(0, i + 1, int(lens[i]))) for i in rows]
+    n = np.zeros(m, dtype=np.int64)
+    n[rows] = [len(c) for c in cols]
     rp = np.zeros(m + 1, dtype=np.int64)
-    rp[1:] = np.cumsum([len(r) for r in rows])
-    ci = np.concatenate(rows).astype(np.int32)
+    rp[1:] = np.cumsum(n)
+    ci = np.concatenate(cols).astype(np.int32)
     return rp, ci, rng.standard_normal(len(ci))
 
 
@@ -41,6 +45,7 @@ def _lower(rng, m, lens):
     ("short", 66000, 0),   # 17-bit keys: three passes, the keys written out
     ("empty", 70000, 0),   # stretches of empty rows longer than any window
     ("empty", 20000, 16),
+    ("sparse", (1 << 24) + 70, 0),  # 25-bit keys: four passes
 ])
 def test_mirror_slab_shapes(dev, shape, m, bits, monkeypatch):
     monkeypatch.setenv("SPSYRK_MIRROR_NARROW", str(bits))
@@ -49,6 +54,10 @@ def test_mirror_slab_shapes(dev, shape, m, bits, monkeypatch):
         lens = np.where(np.arange(m) % 97 == 5, m, 3)
     elif shape == "short":
         lens = rng.integers(0, 3, size=m)
+    elif shape == "sparse":
+        lens = np.zeros(m, dtype=np.int64)
+        lens[rng.choice(m, 2000, replace=False)] = 50
+        lens[m - 1] = 4000
     else:
         lens = np.where(np.arange(m) % 5000 < 40, 60, 0)
     rp, ci, v = _lower(rng, m, lens)
