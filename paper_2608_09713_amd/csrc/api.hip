@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "common.h"
+#include "dense_layout.h"
 #include "internal.h"
 #include "spsyrk.h"
 
@@ -584,12 +585,12 @@ bool index_keeps_entries(const DevCsr& B, int sr) {
 // Whether the ndense rows of at least kDenseProducts products go by cells
 // (lower mode): their products are to outnumber the entries, which a pass
 // over all of them (the table of column cells) has to pay for, and the cells
-// of a row are to be few (4 M rows: 256 cells).  SPSYRK_DENSE_ROWS=0 (read at
+// of a row are to be few (2^22 rows: 512 cells).  SPSYRK_DENSE_ROWS=0 (read at
 // every call) turns it off.
 bool use_dense(int64_t ndense, int64_t nnz, int64_t m) {
     const char* e = std::getenv("SPSYRK_DENSE_ROWS");
     if (e && e[0] == '0') return false;
-    return ndense > 0 && m <= (int64_t(1) << 22) && ndense * int64_t(kDenseProducts) >= nnz;
+    return ndense > 0 && m <= kDenseMaxRows && ndense * int64_t(kDenseProducts) >= nnz;
 }
 
 // The buffers build_index takes for the column index of B in lower mode

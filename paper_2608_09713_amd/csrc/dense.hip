@@ -21,6 +21,7 @@
 //   * a symbolic pass counts every unit's columns, so each unit knows where
 //     its outputs start.
 #include "common.h"
+#include "dense_layout.h"
 #include "internal.h"
 #include "lookup.h"
 #include "stretches.h"
@@ -28,10 +29,7 @@
 namespace spsyrk {
 namespace {
 
-constexpr int kCellBits = 13;
-constexpr int kCell = 1 << kCellBits;
-constexpr int kSymCells = 16;   // cells per workgroup of the symbolic pass
-constexpr int kDB = 512;       // threads per workgroup
+constexpr int kDB = kDenseThreads;
 constexpr int kDW = kDB / kWave;
 constexpr int kDU = 4;          // registers of products in flight per wavefront
 constexpr uint32_t kNoColumn = 0xffffffffu;
@@ -118,9 +116,8 @@ __device__ inline uint2 cell_stretch(const DenseArgs& a, uint2 r, int64_t i, int
 __global__ __launch_bounds__(kDB) void dense_symbolic_kernel(DenseArgs a) {
     __shared__ uint32_t bits[kSymCells * kCell / 32];
     __shared__ Stretches<float, false, kDB, kDU> S;
-    const int nd = a.nrows;
-    const int d = int(blockIdx.x) % nd;
-    const int64_t g0 = int64_t(int(blockIdx.x) / nd) * kSymCells;
+    const int d = int(blockIdx.x);
+    const int64_t g0 = int64_t(blockIdx.y) * kSymCells;
     const int64_t i = a.rows[d];
     if (g0 * kCell >= i) return;
     const int lane = lane_id();
@@ -191,9 +188,8 @@ __global__ __launch_bounds__(kDB) void dense_numeric_kernel(DenseArgs a) {
     __shared__ uint64_t bits[kCell / 64];
     __shared__ uint32_t first[kCell / 64];
     __shared__ Stretches<In, kVal, kDB, kDU> S;
-    const int nd = a.nrows;
-    const int d = int(blockIdx.x) % nd;
-    const int64_t g = int64_t(int(blockIdx.x) / nd);
+    const int d = int(blockIdx.x);
+    const int64_t g = blockIdx.y;
     const int64_t i = a.rows[d];
     const int64_t B0 = g * kCell;
     if (B0 > i) return;
@@ -295,16 +291,6 @@ __global__ __launch_bounds__(kDB) void dense_numeric_kernel(DenseArgs a) {
 
 }  // namespace
 
-int dense_cells(int64_t m) { return int((m + kCell - 1) >> kCellBits); }
-
-int dense_block_log(int64_t positions, int64_t m) {
-    int b = 4;
-    while (((positions >> b) + 2) * int64_t(dense_cells(m)) > (int64_t(1) << 24)) ++b;
-    return b;
-}
-
-int64_t dense_blocks(int64_t positions, int blk_log) { return (positions >> blk_log) + 2; }
-
 void dense_table(const DenseArgs& a, int64_t m, int64_t nnz, uint32_t* owner, hipStream_t s) {
     fill_u32(owner, dense_blocks(nnz, a.blk_log), kNoColumn, s);
     int64_t grid = (nnz + kBlock - 1) / kBlock;
@@ -319,14 +305,15 @@ void dense_table(const DenseArgs& a, int64_t m, int64_t nnz, uint32_t* owner, hi
 
 void dense_symbolic(const DenseArgs& a, hipStream_t s) {
     if (a.nrows <= 0) return;
-    const unsigned grid = unsigned(a.nrows) * unsigned((a.ncells + kSymCells - 1) / kSymCells);
-    dense_symbolic_kernel<<<grid, kDB, 0, s>>>(a);
+    const DenseGrid g = dense_grid(a.nrows, a.ncells, true);
+    dense_symbolic_kernel<<<dim3(g.x, g.y), kDB, 0, s>>>(a);
     dense_offsets<<<unsigned(a.nrows), kWave, 0, s>>>(a);
 }
 
 void dense_numeric(const DenseArgs& a, hipStream_t s) {
     if (a.nrows <= 0) return;
-    const unsigned grid = unsigned(a.nrows) * unsigned(a.ncells);
+    const DenseGrid g = dense_grid(a.nrows, a.ncells, false);
+    const dim3 grid(g.x, g.y);
     switch (a.sr) {
         case kF64: dense_numeric_kernel<kF64><<<grid, kDB, 0, s>>>(a); break;
         case kF32: dense_numeric_kernel<kF32><<<grid, kDB, 0, s>>>(a); break;

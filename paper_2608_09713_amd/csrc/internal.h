@@ -365,8 +365,9 @@ void heavy_symbolic(const HeavyArgs& a, int* queue, hipStream_t s);
 void heavy_numeric(const HeavyArgs& a, int* queue, hipStream_t s);
 
 // ---- dense.hip
-// The rows with the most products (lower mode), by cells of output columns.
-// A row is dense from kDenseProducts products on; ncells = dense_cells(m).
+// The rows with the most products (lower mode), by cells of output columns
+// (sizes and launches: dense_layout.h).  A row is dense from kDenseProducts
+// products on; ncells = dense_cells(m).
 constexpr unsigned long long kDenseProducts = 1ull << 17;
 struct DenseArgs {
     const int64_t* rp = nullptr;       // A
@@ -377,7 +378,7 @@ struct DenseArgs {
     const int32_t* rows = nullptr;     // the rows
     int nrows = 0;
     int ncells = 0;
-    int blk_log = 5;                   // dense_block_log
+    int blk_log = 0;                   // dense_block_log
     uint32_t* cells = nullptr;         // [dense_blocks * ncells] cell starts of the long columns
     uint32_t* count = nullptr;         // [nrows * ncells] columns, then first outputs, of every unit
     int64_t* row_nnz = nullptr;        // [m] (symbolic)
@@ -385,11 +386,6 @@ struct DenseArgs {
     int32_t* c_ci = nullptr;
     void* c_val = nullptr;
 };
-int dense_cells(int64_t m);
-// log2 of the positions per block of the table of long columns, for an index
-// of `positions` entries over m rows (a table of at most 64 MB), and its blocks
-int dense_block_log(int64_t positions, int64_t m);
-int64_t dense_blocks(int64_t positions, int blk_log);
 // fills a.cells (owner: dense_blocks words of scratch)
 void dense_table(const DenseArgs& a, int64_t m, int64_t nnz, uint32_t* owner, hipStream_t s);
 // row lengths and first outputs; then columns and values

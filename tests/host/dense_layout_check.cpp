@@ -1,0 +1,44 @@
+// Host check of the launches over (row, cell) units of dense.hip: every unit
+// is one workgroup of the grid, and no dimension passes what a launch takes
+// (fewer than 2^32 threads, fewer than 2^16 workgroups in y), for any number
+// of rows and cells the path accepts.
+#include <cstdio>
+#include <initializer_list>
+
+#include "dense_layout.h"
+
+int main() {
+    using namespace spsyrk;
+    long checked = 0;
+    for (int64_t m : {int64_t(1), int64_t(8192), int64_t(8193), int64_t(1) << 19, int64_t(1) << 20, int64_t(1) << 21,
+                      kDenseMaxRows - 1, kDenseMaxRows}) {
+        const int cells = dense_cells(m);
+        if (int64_t(cells) * kCell < m || int64_t(cells - 1) * kCell >= m) return 1;
+        for (int64_t rows : {int64_t(1), int64_t(41454), int64_t(65536), int64_t(131073), m}) {
+            if (rows > m) continue;
+            for (bool symbolic : {false, true}) {
+                const DenseGrid g = dense_grid(rows, cells, symbolic);
+                const int64_t per = symbolic ? kSymCells : 1;
+                if (int64_t(g.x) != rows || int64_t(g.y) * per < cells || (int64_t(g.y) - 1) * per >= cells) {
+                    std::printf("units lost: %lld rows, %d cells\n", (long long)rows, cells);
+                    return 1;
+                }
+                if (int64_t(g.x) * kDenseThreads >= (int64_t(1) << 32) || g.y >= 65536) {
+                    std::printf("launch too large: %lld rows, %d cells\n", (long long)rows, cells);
+                    return 1;
+                }
+                ++checked;
+            }
+        }
+    }
+    // the table of long columns stays within 64 MB and has a block for every column start
+    for (int64_t positions : {int64_t(1), int64_t(1000), int64_t(1) << 24, (int64_t(1) << 31) - 1})
+        for (int64_t m : {int64_t(9000), int64_t(1) << 20, kDenseMaxRows}) {
+            const int b = dense_block_log(positions, m);
+            const int64_t blocks = dense_blocks(positions, b);
+            if (blocks * dense_cells(m) > (int64_t(1) << 24) || ((positions + (int64_t(1) << b) - 1) >> b) >= blocks) return 1;
+            ++checked;
+        }
+    std::printf("ok %ld\n", checked);
+    return 0;
+}

@@ -81,3 +81,32 @@ def test_dense_rows_full():
     C = sp.lower(sp.DeviceCSR.from_host(A, "cuda:0"), "f64")
     assert sp.stats()["heavy_rows"] > 0
     compare_full(C, oracle.lower(A, "f64"), "f64", "lower")
+
+
+def test_more_units_than_one_grid_dimension_holds():
+    """About 10 M (row, cell) units, past the 2^23 workgroups of 512 threads that
+    one grid dimension takes: 2^22 rows (512 cells), the last 24,576 sharing 32
+    hub columns.  Counts one-shot, f64 planned and executed."""
+    m, last, hubs = 1 << 22, 24576, 32
+    rng = np.random.default_rng(8)
+    holds = rng.random((last, hubs)) < 0.9
+    holds[:, 0] = True
+    rp = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(holds.sum(1), out=rp[m - last + 1:])
+    cols = np.nonzero(holds)[1]
+    A = CSR(m, 1000, rp, cols.astype(np.int32), rng.standard_normal(len(cols)))
+    products = (np.cumsum(holds, axis=0) - holds)[holds]  # earlier holders of every entry's column
+    per_row = np.add.reduceat(products, rp[m - last:m] - rp[m - last])
+    assert (per_row >= 1 << 17).sum() * 512 > 1 << 23
+    rows = np.concatenate([[0, m - last - 1, m - last, m - last + 5000], np.arange(m - last + 7000, m, 1999), [m - 1]])
+    print(f"[units] nnz={A.nnz} dense rows={int((per_row >= 1 << 17).sum())}", flush=True)
+    B = A.with_values(None)
+    compare_rows(sp.lower(sp.DeviceCSR.from_host(B, "cuda:0"), "count"), oracle.lower(B, "count", rows=rows), rows,
+                 "count", "lower")
+    plan, C = sp.lower_plan(sp.DeviceCSR.from_host(A, "cuda:0"), "f64")
+    compare_rows(C, oracle.lower(A, "f64", rows=rows), rows, "f64", "plan")
+    del C
+    B = A.with_values(A.values * 3 + 1)
+    compare_rows(plan.execute(sp.DeviceCSR.from_host(B, "cuda:0").values), oracle.lower(B, "f64", rows=rows), rows,
+                 "f64", "execute")
+    plan.close()

@@ -25,3 +25,9 @@ def test_symm_bucket_layout_fits_lds_tables(tmp_path):
     # every forced bucket size at every row count up to 2^24 keeps the number
     # of buckets within the kernels' LDS tables
     assert _run_check("symm_layout_check", tmp_path).startswith("ok")
+
+
+def test_dense_launches_stay_within_what_a_launch_takes(tmp_path):
+    # every (row, cell) unit has a workgroup, no grid dimension reaches 2^32
+    # threads, up to 2^22 rows of 512 cells
+    assert _run_check("dense_layout_check", tmp_path).startswith("ok")
