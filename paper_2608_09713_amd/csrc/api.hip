@@ -443,7 +443,7 @@ ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ct
     if (entries)
         cx.ke = ar.get_t<uint2>(N);
     else
-        cx.key = ar.get_t<uint32_t>(N > 0 ? N : 1);
+        cx.key = ar.get_t<uint32_t>(N + kKeyPad);
     // with every partner run given, Jaccard keys carry the row lengths
     // (the row field's spare bits) and no value array is kept
     if (sr == kJaccard && runs_given) cx.lenbits = 32 - cx.rowbits;
@@ -556,12 +556,12 @@ struct LowerPlan {
     ColIndex cx;
     uint32_t* vsrc = nullptr;  // entry of A behind every position of the index (nnz; null with cx.ke)
     RunTab run;
-    uint32_t* rend = nullptr;  // run ends of the heavy rows' entries (nnz, with cursor)
     unsigned long long* prod = nullptr;
     int32_t* heavy_rows = nullptr;
     int64_t nheavy = 0;
     int64_t* heavy_nnz = nullptr;
-    uint32_t* cursor = nullptr;
+    uint2* cursor = nullptr;        // (these two null without long rows)
+    HeavyStretch* list = nullptr;
     DenseArgs dense;  // (its cells and counts; nrows 0 without such rows)
     Ctl* ctl = nullptr;
     int64_t* c_rp = nullptr;
@@ -602,7 +602,8 @@ void reserve_index(const DevCsr& B, int sr, Arena& ar, bool entries) {
     const int64_t N = B.nnz;
     if (N <= 0) return;
     const int nbits = bit_width_u64(B.n > 1 ? uint64_t(B.n - 1) : 0);
-    ar.reserve(size_t(N) * sizeof(uint32_t), entries ? 6 : 7);
+    ar.reserve(size_t(N) * sizeof(uint32_t), 6);
+    if (!entries) ar.reserve(size_t(N + kKeyPad) * sizeof(uint32_t));
     const int vb = entries ? int(sizeof(uint2)) : csc_value_bytes(sr);
     if (vb && sr != kJaccard) ar.reserve(size_t(N) * size_t(vb));
     ar.reserve(radix_csr_tmp_bytes(N, nbits));
@@ -703,7 +704,7 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         // more products than entries after all (or heavy rows, which walk
         // keys and values many times): every value gathered once
         const int vb = csc_value_bytes(sr);
-        cx.key = ar.get_t<uint32_t>(L.nnz);
+        cx.key = ar.get_t<uint32_t>(L.nnz + kKeyPad);
         cx.val = ar.get(size_t(L.nnz) * size_t(vb));
         if (plan) plan->vsrc = ar.get_t<uint32_t>(L.nnz);
         split_index(cx.ke, L.nnz, L.v, vb, cx.key, cx.val, plan ? plan->vsrc : nullptr, s);
@@ -762,8 +763,10 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         ha.row_nnz = heavy_nnz;
         ha.run = run;
         ha.runs_ready = true;
-        ha.cursor = ar.get_t<uint32_t>(L.nnz);
-        ha.rend = ar.get_t<uint32_t>(L.nnz);
+        if (h.maxlen > uint64_t(kHeavySmall)) {
+            ha.cursor = ar.get_t<uint2>(L.nnz);
+            ha.list = ar.get_t<HeavyStretch>(L.nnz);
+        }
         da.row_nnz = heavy_nnz;
         Phase ph(SPSYRK_PHASE_HEAVY_SYMBOLIC, s);
         dense_symbolic(da, s);
@@ -887,8 +890,10 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         plan->nheavy = nheavy;
         if (nheavy > 0) {
             plan->heavy_nnz = static_cast<int64_t*>(ar.keep(heavy_nnz));
-            plan->cursor = static_cast<uint32_t*>(ar.keep(ha.cursor));
-            plan->rend = static_cast<uint32_t*>(ar.keep(ha.rend));
+            if (ha.cursor) {
+                plan->cursor = static_cast<uint2*>(ar.keep(ha.cursor));
+                plan->list = static_cast<HeavyStretch*>(ar.keep(ha.list));
+            }
         }
         if (da.nrows > 0) {
             ar.keep(da.cells);
@@ -1025,8 +1030,8 @@ void syrk(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar, hipSt
     ha.row_nnz = c_rp;
     if (nheavy > 0) {
         ha.run.r8 = ar.get_t<uint2>(L.nnz);
-        ha.cursor = ar.get_t<uint32_t>(L.nnz);
-        ha.rend = ar.get_t<uint32_t>(L.nnz);
+        ha.cursor = ar.get_t<uint2>(L.nnz);
+        ha.list = ar.get_t<HeavyStretch>(L.nnz);
         {
             Phase ph(SPSYRK_PHASE_HEAVY_SYMBOLIC, s);
             heavy_symbolic(ha, &ctl->queue, s);
@@ -1446,7 +1451,7 @@ void lower_execute(const LowerPlan& P, const void* vals, Arena& ar, hipStream_t 
         ha.run = P.run;
         ha.runs_ready = true;
         ha.cursor = P.cursor;
-        ha.rend = P.rend;
+        ha.list = P.list;
         ha.c_rp = c_rp;
         ha.c_ci = c_ci;
         ha.c_val = c_val;
@@ -1843,7 +1848,7 @@ spsyrk_status spsyrk_lower_plan(const spsyrk_csr* A, spsyrk_semiring sr, const s
             h->has_al = true;
         }
         for (void* q : {static_cast<void*>(lp.rp), static_cast<void*>(lp.ci), static_cast<void*>(lp.run.r8),
-                        static_cast<void*>(lp.run.r4), static_cast<void*>(lp.rend),
+                        static_cast<void*>(lp.run.r4), static_cast<void*>(lp.list),
                         static_cast<void*>(lp.prod), static_cast<void*>(lp.cx.ke), static_cast<void*>(lp.cx.key), lp.cx.val,
                         static_cast<void*>(lp.vsrc), static_cast<void*>(lp.heavy_rows),
                         static_cast<void*>(lp.heavy_nnz), static_cast<void*>(lp.cursor),

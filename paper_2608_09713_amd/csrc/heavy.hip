@@ -30,8 +30,9 @@
 namespace spsyrk {
 namespace {
 
-constexpr int kHB = 512;                 // threads per workgroup
+constexpr int kHB = kHeavySmall;         // threads per workgroup
 constexpr int kHW = kHB / kWave;         // wavefronts per workgroup
+constexpr uint32_t kNoRow = 0xffffffffu;  // (rows are below 2^31)
 constexpr int kHeavyGroups = 1024;       // workgroups of a heavy-row launch
 
 // Output columns per window and ranks per value tile: the symbolic pass
@@ -45,7 +46,9 @@ struct HeavyCfg {
     static constexpr int kWin = NUM ? (1 << 17) : (1 << 18);
     static constexpr int kWords = kWin / 32;
     static constexpr int kAcc = (SR == kF64 ? 18432 : 21504) / int(sizeof(Acc));
-    static constexpr int kHU = NUM && SR != kF32 ? 3 : 2;  // registers of products in flight (3 spill in f32)
+    // registers of products in flight (3 for all: R-MAT in f32 15% slower,
+    // the symbolic pass of long rows 20%)
+    static constexpr int kHU = NUM && SR != kF32 ? 3 : 2;
 };
 
 // first position in [lo, hi) whose row is at least x (hi if none)
@@ -61,6 +64,70 @@ __device__ inline uint32_t stretch_end(const uint32_t* __restrict__ key, uint32_
             n = mid;
     }
     return lo;
+}
+
+// The same for U stretches side by side, hi becoming the position and row the
+// row there (kNoRow at hi); known: every stretch's first row is below x.  Most
+// ends lie near the front of a stretch, so its first rows are read at once,
+// 16 bytes per lane (the keys are padded by kKeyPad words), and searched for
+// only past them.  (1024 rows of 10,000 entries with nine partners each, 2^20
+// columns, f64, whole call: 9.8 ms with searches from a stretch's ends, 8.3 so.)
+template <int U>
+__device__ inline void stretch_ends(const uint32_t* __restrict__ key, uint32_t rowmask, const uint32_t (&lo)[U],
+                                    uint32_t (&hi)[U], uint32_t (&row)[U], int64_t x, bool known) {
+    static_assert(kKeyPad >= 4, "four rows from any position, or the one after it");
+    uint32_t k[U][4], at[U], n[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (lo[u] < hi[u]) __builtin_memcpy(k[u], key + lo[u] + (known ? 1u : 0u), 16);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        at[u] = n[u] = hi[u];
+        row[u] = kNoRow;
+        if (lo[u] >= hi[u]) continue;
+        const uint32_t p = lo[u] + (known ? 1u : 0u);
+        uint32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (p + j < hi[u]) {
+                const uint32_t r = k[u][j] & rowmask;
+                if (int64_t(r) < x)
+                    c = j + 1;
+                else
+                    row[u] = min(row[u], r);  // (rows ascend: the first one)
+            }
+        at[u] = p + c;
+        if (c < 4)
+            n[u] = min(at[u], hi[u]);
+        else if (at[u] < hi[u] && int64_t(key[hi[u] - 1] & rowmask) < x)
+            at[u] = hi[u];
+    }
+    auto left = [&] {
+        bool f = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) f |= at[u] < n[u];
+        return f;
+    };
+    while (left()) {
+        uint32_t m[U], v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            m[u] = at[u] + (n[u] - at[u]) / 2;
+            v[u] = at[u] < n[u] ? key[m[u]] & rowmask : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (at[u] >= n[u]) continue;
+            if (int64_t(v[u]) < x) {
+                at[u] = m[u] + 1;
+            } else {
+                n[u] = m[u];
+                row[u] = v[u];  // (the last such position read is the first one)
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) hi[u] = n[u];
 }
 
 // Three workgroups of the numeric pass share a compute unit by their LDS;
@@ -90,6 +157,7 @@ void heavy_kernel(HeavyArgs a, int* queue) {
     __shared__ uint32_t win_end[kHB];
     __shared__ uint32_t tile_end[NUM ? kHB : 1];
     __shared__ int row_s;
+    __shared__ int listed_s;  // (long rows) entries with a stretch in the window
     __shared__ double wtd[kHW];
 
     const int tid = threadIdx.x;
@@ -128,49 +196,48 @@ void heavy_kernel(HeavyArgs a, int* queue) {
         // Rows of up to kHB entries keep an entry per thread: the start of its
         // stretch stays in a register, and the idle threads search the ends in several windows or tiles at once (a
         // search is a chain of about ten loads, each of them a miss in L2).
-        // Longer rows go through the entries kHB at a time, with the starts
-        // and the windows' ends in memory.
+        // Longer rows go through the entries, two per thread at a time, in
+        // every window.  An entry's next position is kept in memory with the
+        // row there, so that an entry with nothing in the window costs one
+        // streamed read, and the numeric pass lists the entries that have
+        // something: its value tiles go through those alone.  (2048 rows of
+        // 5000 entries, 2^22 columns, f64, whole call: 12.6 ms with every
+        // entry searched for in every window and tile, 8.6 so; one row of
+        // 500,000 entries of one partner, 2^20 columns: 511 ms, 94 so.)
         const bool small = E <= kHB;
         uint32_t start = 0;  // (small rows) the stretch's start
 
-        // partner runs, and every entry's next position
-        uint64_t prod_local = 0;
-        for (int64_t e = e0 + tid; e < e1; e += kHB) {
-            uint2 rr;
-            if (!NUM && !a.runs_ready) {
-                uint32_t st, len;
-                partner_run(key, a.cx.gptr, a.cx.gs, a.cx.rowbits, uint32_t(a.ci[e]), uint32_t(i), LOWER, st, len);
-                rr = make_uint2(st, st + len);
-                a.run.r8[e] = rr;
-                prod_local += len;
-            } else {
-                rr = run_of(a.run, e);
-            }
-            if (small) {
-                start = rr.x;
-            } else {
-                a.cursor[e] = rr.x;
-            }
-        }
+        // (two passes) partner runs
         if constexpr (!NUM) {
-            const uint64_t tot = wave_reduce_sum(prod_local);
-            if (lane == 0 && tot && a.products) atomicAdd(a.products, (unsigned long long)tot);
+            if (!a.runs_ready) {
+                uint64_t prod_local = 0;
+                for (int64_t e = e0 + tid; e < e1; e += kHB) {
+                    uint32_t st, len;
+                    partner_run(key, a.cx.gptr, a.cx.gs, a.cx.rowbits, uint32_t(a.ci[e]), uint32_t(i), LOWER, st, len);
+                    a.run.r8[e] = make_uint2(st, st + len);
+                    prod_local += len;
+                }
+                const uint64_t tot = wave_reduce_sum(prod_local);
+                if (lane == 0 && tot && a.products) atomicAdd(a.products, (unsigned long long)tot);
+                __threadfence_block();
+                __syncthreads();
+            }
         }
+        if (small && tid < E) start = run_of(a.run, e0 + tid).x;
         const int per_group = small ? kHB / int(E) : 1;  // boundaries searched at once
-        if (!NUM && !a.runs_ready) __threadfence_block();
-        __syncthreads();
 
         const int64_t jmax = LOWER ? int64_t(i) : a.m_right;
-        const int64_t nwin = (jmax + kWin - 1) / kWin;
+        const int nwin = int((jmax + kWin - 1) / kWin);
         int64_t count = 0;                          // symbolic: distinct columns so far
         int64_t outp = NUM ? a.c_rp[i] : 0;         // numeric: first output slot of the window
-        for (int64_t k = 0; k < nwin; ++k) {
-            const int64_t B0 = k * kWin;
+        for (int k = 0; k < nwin; ++k) {
+            const int64_t B0 = int64_t(k) * kWin;
             const int64_t B1 = min(jmax, B0 + int64_t(kWin));
             const int nw = int((B1 - B0 + 31) >> 5);
             for (int x = tid; x < nw; x += kHB) bits[x] = 0;
-            // (each entry of a long row is one thread's from here on: its own
-            // writes to the cursor and the window's end are the ones it reads)
+            if (NUM && tid == 0) listed_s = 0;
+            // (each entry of a long row is one thread's in every window: its
+            // own writes to the cursor are the ones it reads)
             const int kg = small ? int(k % per_group) : 0;  // the window in its group
             if (small && kg == 0 && k + 1 < nwin) {
                 // ends at the next per_group window ends, the last one left
@@ -178,7 +245,7 @@ void heavy_kernel(HeavyArgs a, int* queue) {
                 const int eg = tid / int(E), ee = tid - eg * int(E);
                 if (eg < per_group && k + 1 + eg < nwin) {
                     const uint2 r = run_of(a.run, e0 + ee);
-                    win_end[tid] = stretch_end(key, rowmask, r.x, r.y, (k + 1 + eg) * kWin);
+                    win_end[tid] = stretch_end(key, rowmask, r.x, r.y, int64_t(k + 1 + eg) * kWin);
                 }
                 __syncthreads();
             }
@@ -198,24 +265,47 @@ void heavy_kernel(HeavyArgs a, int* queue) {
                     }
                 }
             };
-            for (int64_t c0 = e0; c0 < e1; c0 += kHB) {  // (once for a small row)
-                const int64_t e = c0 + tid;
-                uint32_t lo = start, hi = wend;
+            // (two entries per thread at a time, whose loads go together; a
+            // small row holds its one)
+            for (int64_t c0 = e0; c0 < e1; c0 += 2 * kHB) {
+                uint32_t lo[2] = {start, 0u}, hi[2] = {wend, 0u};
                 if (small) {
-                    if (tid < E) hi = wend = k + 1 < nwin ? win_end[kg * int(E) + tid] : run_of(a.run, e).y;
+                    if (tid < E) hi[0] = wend = k + 1 < nwin ? win_end[kg * int(E) + tid] : run_of(a.run, e0 + tid).y;
                 } else {
-                    lo = hi = 0;
-                    if (e < e1) {
-                        lo = a.cursor[e];
-                        hi = run_of(a.run, e).y;
-                        if (B1 < jmax) hi = stretch_end(key, rowmask, lo, hi, B1);
-                        if constexpr (NUM)
-                            a.rend[e] = hi;
-                        else
-                            a.cursor[e] = hi;
+                    uint32_t row[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int64_t e = c0 + u * kHB + tid;
+                        lo[u] = hi[u] = 0;
+                        if (e >= e1) continue;
+                        const uint2 c = k ? a.cursor[e] : make_uint2(0u, 0u);
+                        if (int64_t(c.y) >= B1) continue;  // nothing in the window
+                        const uint2 r = run_of(a.run, e);
+                        lo[u] = k ? c.x : r.x;
+                        hi[u] = r.y;
+                    }
+                    if (k + 1 < nwin) {
+                        stretch_ends<2>(key, rowmask, lo, hi, row, B1, k > 0);
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const int64_t e = c0 + u * kHB + tid;
+                            if (e < e1 && (k == 0 || lo[u] < hi[u])) a.cursor[e] = make_uint2(hi[u], row[u]);
+                        }
                     }
                 }
-                S.products(lo, hi, In(0), mark);
+#pragma unroll 1
+                for (int u = 0; u < 2 && c0 + u * kHB < e1; ++u) {
+                    const uint32_t l = u ? lo[1] : lo[0], h = u ? hi[1] : hi[0];
+                    S.products(l, h, In(0), mark);
+                    if (NUM && !small) {  // the stretches that are not empty, listed (a wavefront's in a row)
+                        const uint64_t some = __ballot(l < h);
+                        int at = 0;
+                        if (lane == 0 && some) at = atomicAdd(&listed_s, __popcll(some));
+                        at = __builtin_amdgcn_readfirstlane(at);
+                        if (l < h)
+                            a.list[e0 + at + __popcll(some & lanemask_lt())] = {uint32_t(c0 + u * kHB + tid), l, h, 0u};
+                    }
+                }
             }
 
             // ranks: every thread owns a contiguous stretch of words
@@ -227,6 +317,8 @@ void heavy_kernel(HeavyArgs a, int* queue) {
             uint32_t Nw;
             uint32_t off = S.scan(s, &Nw);
             Nw = uniform(Nw);
+            // entries whose values the tiles add, kHB at a time
+            const int nadd = NUM && !small ? __builtin_amdgcn_readfirstlane(listed_s) : int(E);
             if constexpr (!NUM) {
                 count += Nw;
                 start = wend;
@@ -287,22 +379,38 @@ void heavy_kernel(HeavyArgs a, int* queue) {
                         }
                         __syncthreads();
                     }
-                    for (int64_t c0 = e0; c0 < e1; c0 += kHB) {
-                        const int64_t e = c0 + tid;
+                    for (int c0 = 0; c0 < nadd; c0 += kHB) {  // (once for a small row)
                         uint32_t lo = start, hi = wend;
                         In val = In(0);
-                        if constexpr (kVal)
-                            if (e < e1) val = static_cast<const In*>(a.val)[e];
                         if (small) {
-                            if (!last && tid < E) hi = tile_end[qg * int(E) + tid];
+                            if constexpr (kVal) {
+                                // (opaque: the address is formed here, not
+                                // held in registers across the row)
+                                int t = tid;
+                                asm volatile("" : "+v"(t));
+                                if (t < nadd) val = static_cast<const In*>(a.val)[e0 + t];
+                            }
+                            if (!last && tid < nadd) hi = tile_end[qg * nadd + tid];
                             start = hi;
                         } else {
-                            lo = hi = 0;
-                            if (e < e1) {
-                                lo = a.cursor[e];
-                                hi = a.rend[e];
-                                if (!last) hi = stretch_end(key, rowmask, lo, hi, int64_t(tile_col[q + 1]));
-                                a.cursor[e] = hi;
+                            const int at = c0 + tid;
+                            const int64_t x = last ? B1 : int64_t(tile_col[q + 1]);
+                            HeavyStretch l{0u, 0u, 0u, kNoRow};
+                            if (at < nadd) l = a.list[e0 + at];
+                            lo = hi = l.pos;
+                            if (int64_t(l.row) < x) {
+                                hi = l.end;
+                                if constexpr (kVal) val = static_cast<const In*>(a.val)[l.entry];
+                            }
+                            if (!last) {
+                                const uint32_t from[1] = {lo};
+                                uint32_t to[1] = {hi}, row[1];
+                                stretch_ends<1>(key, rowmask, from, to, row, x, q > 0);
+                                if (lo < hi) {
+                                    a.list[e0 + at].pos = to[0];
+                                    a.list[e0 + at].row = row[0];
+                                }
+                                hi = to[0];
                             }
                         }
                         S.products(lo, hi, val, add);

@@ -48,6 +48,7 @@ struct DevCsr {
 // of 2^gs-column groups: the entries of group g occupy [gptr[g], gptr[g+1]).
 // In lower mode the last (largest-row) entry of every column is left out: it
 // is never the partner j < i of another row.
+constexpr int kKeyPad = 4;  // words allocated past the last key, so that four keys can be read from any position
 struct ColIndex {
     int64_t n = 0;          // columns of B
     int64_t m = 0;          // rows of B
@@ -55,7 +56,7 @@ struct ColIndex {
     int rowbits = 1;        // bits of a row id inside a key
     int64_t ngroups = 0;    // groups; gptr has ngroups + 1 entries
     int64_t nkept = 0;      // entries kept (device-side value is authoritative until synced)
-    uint32_t* key = nullptr;
+    uint32_t* key = nullptr;  // (kKeyPad words past the last one are allocated)
     void* val = nullptr;    // double / float values of B, or int32 row lengths of B (Jaccard)
     // non-null (lower mode, plus-times): {key, entry of B} per position instead
     // of key and val, the values then read from B's by entry
@@ -333,6 +334,12 @@ void heavy_sums(const int32_t* rows, int64_t n, const int64_t* rp, const int64_t
 void tile_first_rows(const int64_t* rp, int64_t m, int64_t T, int64_t* trow, hipStream_t s);
 
 // ---- heavy.hip
+constexpr int kHeavySmall = 512;  // entries of a row that the kernel holds one per thread
+struct HeavyStretch {
+    // the entry, its next position, where its part of the window ends, and
+    // the row at the next position (~0 at the end; 0 before the first tile)
+    uint32_t entry, pos, end, row;
+};
 struct HeavyArgs {
     int64_t m = 0;
     const int64_t* rp = nullptr;
@@ -351,8 +358,11 @@ struct HeavyArgs {
     RunTab run;                         // partner run {first, end} of every entry (r8 only
                                         // when the symbolic pass writes it)
     bool runs_ready = false;            // run already filled (the symbolic pass skips its lookups)
-    uint32_t* cursor = nullptr;
-    uint32_t* rend = nullptr;           // end of every heavy entry's run (set with the cursors)
+    // For rows of more than kHeavySmall entries: {next position, row there}
+    // of every entry (~0 where the run is at its end), and (numeric) the
+    // entries with a stretch in the window, from the row's first entry on
+    uint2* cursor = nullptr;
+    HeavyStretch* list = nullptr;
     unsigned long long* products = nullptr;  // optional: add the products formed
     int64_t* row_nnz = nullptr;
     unsigned long long* nnz_total = nullptr; // optional: add the heavy rows' lengths

@@ -26,7 +26,8 @@ struct Stretches {
     uint32_t off[NT + 1];  // first product of every stretch that is not empty, then their total
     uint32_t pos[NT];      // position less product
     In val[VAL ? NT : 1];
-    uint32_t wt[kWaves];
+    uint32_t wt[kWaves];   // (a wavefront's products)
+    uint32_t wn[kWaves];   // a wavefront's stretches that are not empty
     alignas(4) uint8_t mark[kWaves][kPiece];
 
     // exclusive scan over the workgroup's threads; *total gets the sum
@@ -63,10 +64,23 @@ struct Stretches {
         int lane = lane_id();
         asm volatile("" : "+v"(lane));
         const uint32_t w = uniform(threadIdx.x / kWave);
+        // the places and first products of the stretches that are not empty,
+        // by one exchange of every wavefront's counts (the barriers below
+        // order those words' next use)
         const uint32_t len = hi - lo;
-        uint32_t n, total;
-        const uint32_t at = scan(len ? 1u : 0u, &n);
-        const uint32_t first = scan(len, &total);
+        const uint64_t some = __ballot(len != 0);
+        const uint32_t inc = wsort::inclusive_sum(len);
+        if (lane == kWave - 1) {
+            wt[w] = inc;
+            wn[w] = uint32_t(__popcll(some));
+        }
+        __syncthreads();
+        const uint32_t lens = lane < kWaves ? wt[lane] : 0u, nums = lane < kWaves ? wn[lane] : 0u;
+        const uint32_t leni = wsort::inclusive_sum(lens), numi = wsort::inclusive_sum(nums);
+        auto of = [](uint32_t v, uint32_t l) { return uint32_t(__builtin_amdgcn_readlane(int(v), int(l))); };
+        const uint32_t n = of(numi, kWaves - 1), total = of(leni, kWaves - 1);
+        const uint32_t at = of(numi, w) - of(nums, w) + uint32_t(__popcll(some & ((uint64_t(1) << lane) - 1)));
+        const uint32_t first = of(leni, w) - of(lens, w) + inc - len;
         if (len) {
             off[at] = first;
             pos[at] = lo - first;
@@ -74,8 +88,6 @@ struct Stretches {
         }
         if (threadIdx.x == 0) off[n] = total;
         __syncthreads();
-        n = uniform(n);
-        total = uniform(total);
         const uint32_t share = ((total + NT - 1) / NT) * kWave;
         const uint32_t ts = w * share, te = min(total, ts + share);
         if (ts < te) {
