@@ -338,7 +338,7 @@ spsyrk_status spsyrk_debug_flags(uint32_t* flags);
 typedef struct spsyrk_stats {
     int64_t nnz_out;          /* entries in the result */
     int64_t csc_entries;      /* entries kept in the column index built from the right operand */
-    int64_t heavy_rows;       /* rows routed to the dense-tile accumulator */
+    int64_t heavy_rows;       /* rows routed to the heavy-row kernels */
     int64_t light_rows;       /* rows handled by the light-row kernels */
     int64_t products;         /* multiply-adds formed off the diagonal (lower) or in total (offdiag) */
     int64_t heavy_entries;    /* entries of the left operand in heavy rows */
@@ -347,7 +347,7 @@ typedef struct spsyrk_stats {
     int32_t row_bits;         /* bits of the row id inside a packed column key */
     int32_t packed_staging;   /* 1 if the light rows' counts or Jaccard values were staged as one
                                  packed 4-byte word per output (column and value) */
-    int32_t reserved;         /* 0 */
+    int32_t cell_rows;        /* heavy rows that went by cells of output columns (the most products) */
 } spsyrk_stats;
 
 spsyrk_status spsyrk_last_stats(spsyrk_stats* out);

@@ -275,8 +275,7 @@ struct Ctl {
     unsigned long long heavy_sums[2];  // entries of A and output entries of the heavy rows
     unsigned long long chunk_counter;
     unsigned long long maxlen;  // largest row length of the left operand
-    int32_t dense_count;        // rows of at least kDenseProducts products
-    int32_t pad[1];
+    unsigned long long dense[3];  // rows of at least kDenseProducts products, their entries and products
 };
 
 struct HostCtl {
@@ -582,15 +581,13 @@ bool index_keeps_entries(const DevCsr& B, int sr) {
     return local_bits(B.nnz, bit_width_u64(B.n > 1 ? uint64_t(B.n - 1) : 0)) > 0;
 }
 
-// Whether the ndense rows of at least kDenseProducts products go by cells
-// (lower mode): their products are to outnumber the entries, which a pass
-// over all of them (the table of column cells) has to pay for, and the cells
-// of a row are to be few (2^22 rows: 512 cells).  SPSYRK_DENSE_ROWS=0 (read at
-// every call) turns it off.
-bool use_dense(int64_t ndense, int64_t nnz, int64_t m) {
+// Whether the rows of at least kDenseProducts products (rows, entries and
+// products in all) go by cells, lower mode.  SPSYRK_DENSE_ROWS=0 (read at every
+// call) turns it off.
+bool use_dense(const unsigned long long (&dense)[3], int64_t nnz, int64_t m) {
     const char* e = std::getenv("SPSYRK_DENSE_ROWS");
     if (e && e[0] == '0') return false;
-    return ndense > 0 && m <= kDenseMaxRows && ndense * int64_t(kDenseProducts) >= nnz;
+    return dense_rows_pay(int64_t(dense[0]), dense[1], dense[2], nnz, m);
 }
 
 // The buffers build_index takes for the column index of B in lower mode
@@ -682,7 +679,7 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         Phase ph(SPSYRK_PHASE_RUNS, s);
         row_products(L.rp, m, L.nnz, run, ptmp, prod, s, vrows);
         classify_rows(L.rp, prod, m, lower, heavy_rows, &ctl->heavy_count, &ctl->light_cap, &ctl->products, ub, s,
-                      &ctl->maxlen, lower ? &ctl->dense_count : nullptr);
+                      &ctl->maxlen, lower ? ctl->dense : nullptr);
     }
     check_launch();
     // the row classes go to the host; the scan of the staging slots needs
@@ -722,11 +719,10 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
         ar.release(otmp);
     }
     // The rows with the most products, the first of the ordered list, go by
-    // cells (dense.hip), where their products outweigh a pass over the
-    // entries for the table of column cells (their count is a lower bound).
+    // cells (dense.hip) where that pays.
     DenseArgs da;
-    const int64_t ndense = h.dense_count;
-    if (lower && use_dense(ndense, L.nnz, m)) {
+    const int64_t ndense = int64_t(h.dense[0]);
+    if (lower && use_dense(h.dense, L.nnz, m)) {
         da.rp = L.rp;
         da.val = L.v;
         da.cx = cx;
@@ -918,6 +914,7 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
     st.group_shift = cx.gs;
     st.row_bits = cx.rowbits;
     st.packed_staging = pack_rr != 0 ? 1 : 0;
+    st.cell_rows = da.nrows;
     g_stats = st;
     g_stats_valid = true;
 }
@@ -1878,6 +1875,7 @@ spsyrk_status spsyrk_lower_execute(spsyrk_plan* plan, const void* values, const 
         st.nnz_out = C->nnz;
         st.heavy_rows = P.nheavy;
         st.light_rows = P.m - P.nheavy;
+        st.cell_rows = P.dense.nrows;
         g_stats = st;
         g_stats_valid = true;
     });

@@ -276,11 +276,12 @@ void light_fused(const FusedArgs& a, hipStream_t s);
 // the sum of prod over all rows into the two counters
 // and ub[i] = products + diagonal for light rows, 0 for heavy rows (and ub[m]
 // = 0); maxlen
-// (optional, zeroed): the largest row length; dense_count (optional, zeroed):
-// the rows of at least kDenseProducts products
+// (optional, zeroed): the largest row length; dense (optional, zeroed, three
+// words): the rows of at least kDenseProducts products, their entries and
+// their products
 void classify_rows(const int64_t* rp, const unsigned long long* prod, int64_t m, bool lower, int32_t* heavy_rows,
                    int32_t* heavy_count, unsigned long long* light_cap, unsigned long long* prod_sum, int64_t* ub,
-                   hipStream_t s, unsigned long long* maxlen = nullptr, int32_t* dense_count = nullptr);
+                   hipStream_t s, unsigned long long* maxlen = nullptr, unsigned long long* dense = nullptr);
 
 // ---- runs.hip
 // Dense column starts of a CSR matrix's column-sorted copy: cptr[c] =
@@ -376,9 +377,7 @@ void heavy_numeric(const HeavyArgs& a, int* queue, hipStream_t s);
 
 // ---- dense.hip
 // The rows with the most products (lower mode), by cells of output columns
-// (sizes and launches: dense_layout.h).  A row is dense from kDenseProducts
-// products on; ncells = dense_cells(m).
-constexpr unsigned long long kDenseProducts = 1ull << 17;
+// (sizes, launches and when they do: dense_layout.h); ncells = dense_cells(m).
 struct DenseArgs {
     const int64_t* rp = nullptr;       // A
     const void* val = nullptr;

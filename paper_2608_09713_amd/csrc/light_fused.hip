@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "dense_layout.h"
 #include "internal.h"
 #include "lookup.h"
 #include "wave_sort.h"
@@ -755,8 +756,11 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
                                                           bool lower, int32_t* __restrict__ heavy_rows,
                                                           int32_t* heavy_count, unsigned long long* light_cap,
                                                           unsigned long long* prod_sum, int64_t* __restrict__ ub,
-                                                          unsigned long long* maxlen, int32_t* dense_count) {
+                                                          unsigned long long* maxlen, unsigned long long* dense) {
     __shared__ unsigned long long wt[kWavesPerBlock][3];
+    __shared__ unsigned long long dn[3];
+    if (threadIdx.x < 3) dn[threadIdx.x] = 0;
+    __syncthreads();
     unsigned long long cap = 0, ps = 0, ml = 0;
     for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < m; i += int64_t(gridDim.x) * kBlock) {
         const int64_t len = rp[i + 1] - rp[i];
@@ -769,7 +773,11 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
             cap += u;
         } else {
             heavy_rows[atomicAdd(heavy_count, 1)] = int32_t(i);
-            if (dense_count && pr >= kDenseProducts) atomicAdd(dense_count, 1);
+            if (pr >= kDenseProducts) {
+                atomicAdd(&dn[0], 1ull);
+                atomicAdd(&dn[1], (unsigned long long)len);
+                atomicAdd(&dn[2], pr);
+            }
         }
         ub[i] = u;
     }
@@ -794,18 +802,19 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
         if (p) atomicAdd(prod_sum, p);
         if (l && maxlen) atomicMax(maxlen, l);
     }
+    if (dense && threadIdx.x < 3 && dn[threadIdx.x]) atomicAdd(dense + threadIdx.x, dn[threadIdx.x]);
 }
 
 }  // namespace
 
 void classify_rows(const int64_t* rp, const unsigned long long* prod, int64_t m, bool lower, int32_t* heavy_rows,
                    int32_t* heavy_count, unsigned long long* light_cap, unsigned long long* prod_sum, int64_t* ub,
-                   hipStream_t s, unsigned long long* maxlen, int32_t* dense_count) {
+                   hipStream_t s, unsigned long long* maxlen, unsigned long long* dense) {
     if (m <= 0) return;
     int64_t grid = (m + kBlock - 1) / kBlock;
     if (grid > 1024) grid = 1024;
     classify_kernel<<<unsigned(grid), kBlock, 0, s>>>(rp, prod, m, lower, heavy_rows, heavy_count, light_cap,
-                                                      prod_sum, ub, maxlen, dense_count);
+                                                      prod_sum, ub, maxlen, dense);
 }
 
 void light_fused(const FusedArgs& a, hipStream_t s) {

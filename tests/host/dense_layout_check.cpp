@@ -1,7 +1,7 @@
 // Host check of the launches over (row, cell) units of dense.hip: every unit
 // is one workgroup of the grid, and no dimension passes what a launch takes
 // (fewer than 2^32 threads, fewer than 2^16 workgroups in y), for any number
-// of rows and cells the path accepts.
+// of rows and cells the path accepts; and of the rule that takes rows there.
 #include <cstdio>
 #include <initializer_list>
 
@@ -39,6 +39,20 @@ int main() {
             if (blocks * dense_cells(m) > (int64_t(1) << 24) || ((positions + (int64_t(1) << b) - 1) >> b) >= blocks) return 1;
             ++checked;
         }
+    // R-MAT's rows go by cells (scale 19 and 20: rows, entries, products), few
+    // rows of many entries and few partners do not: more lookups than products
+    if (!dense_rows_pay(5408, 3323000, 1674000000, 7970000, int64_t(1) << 19)) return 1;
+    if (!dense_rows_pay(14859, 8180000, 5470000000, 16090000, int64_t(1) << 20)) return 1;
+    if (dense_rows_pay(64, 64 * 131072, 64 * uint64_t(131072), 2 * 64 * 131072, kDenseMaxRows)) return 1;
+    if (dense_rows_pay(63, 6300000, 206000000, 6500000, kDenseMaxRows)) return 1;
+    // never: no rows, too many rows in all, entries that outnumber the products
+    if (dense_rows_pay(0, 0, 0, 0, 1000) || dense_rows_pay(1, 10, 1 << 20, 10, kDenseMaxRows + 1) ||
+        dense_rows_pay(1, 10, 1 << 17, (1 << 17) + 1, 1000))
+        return 1;
+    // a row just within, and just past, its lookups
+    if (!dense_rows_pay(1, (1 << 17) / 512, 1 << 17, 1000, kDenseMaxRows) ||
+        dense_rows_pay(1, (1 << 17) / 512 + 1, 1 << 17, 1000, kDenseMaxRows))
+        return 1;
     std::printf("ok %ld\n", checked);
     return 0;
 }

@@ -1,8 +1,9 @@
 """Rows of 2^17 products and more, which go by cells of 2^13 output columns
 (the heavy rows' units of work otherwise being whole rows), against the
 oracle: rows on both sides of a cell's edge, columns on both sides of the
-length from which the table of cells holds them, more than 1024 entries in a
-row, and the same product with the path switched off."""
+length from which the table of cells holds them (16 entries, 32 in the matrix
+of 128 cells), more than 1024 entries in a row, and the same product with the
+path switched off.  The library's statistics say how many rows went by cells."""
 import numpy as np
 import pytest
 
@@ -16,21 +17,22 @@ pytestmark = pytest.mark.gpu
 VDT = {"f64": np.float64, "f32": np.float32, "count": None, "jaccard": None}
 
 
-def _matrix(seed, m, hubs, share, tail, long_rows):
-    """Hub columns held by a share of all rows, a few sparse entries per row,
-    columns of 30 to 36 and 60 to 70 entries, and long rows of 1500 entries."""
+def _matrix(seed, m, hubs, share, tail, long_rows, last=0):
+    """Hub columns held by a share of all rows and the last rows, a few sparse
+    entries per row, columns of 15 to 18, 30 to 36 and 60 to 70 entries, and
+    long rows of 1500 entries."""
     rng = np.random.default_rng(seed)
     rows, cols = [], []
     for h in range(hubs):
-        r = np.flatnonzero(rng.random(m) < share)
+        r = np.flatnonzero((rng.random(m) < share) | (np.arange(m) >= m - last))
         rows.append(r)
         cols.append(np.full(len(r), h))
     rows.append(np.repeat(np.arange(m), tail))
     cols.append(rng.integers(hubs, hubs + 4 * m, m * tail))
     c = hubs + 4 * m
-    for ln in list(range(30, 37)) + list(range(60, 71)):
-        r = np.sort(rng.choice(m, ln, replace=False))
-        r[-1] = m - 1
+    for ln in [15, 16, 17, 18, *range(30, 37), *range(60, 71)]:
+        r = np.unique(rng.integers(0, m - 1, 2 * ln))
+        r = np.append(np.sort(rng.choice(r, ln - 1, replace=False)), m - 1)
         rows.append(r)
         cols.append(np.full(ln, c))
         c += 1
@@ -56,10 +58,11 @@ def test_dense_rows(semiring, m, monkeypatch):
                                      np.arange(16384, min(m, 16390))]))
     ref = oracle.lower(A, semiring, rows=rows)
     C = sp.lower(dA, semiring)
-    assert sp.stats()["heavy_rows"] > 0 and sp.stats()["products"] > 1 << 27
+    assert 0 < sp.stats()["cell_rows"] <= sp.stats()["heavy_rows"] and sp.stats()["products"] > 1 << 27
     compare_rows(C, ref, rows, semiring, "lower")
     monkeypatch.setenv("SPSYRK_DENSE_ROWS", "0")
     D = sp.lower(dA, semiring)
+    assert sp.stats()["cell_rows"] == 0
     monkeypatch.delenv("SPSYRK_DENSE_ROWS")
     assert C.row_ptr.equal(D.row_ptr) and C.col_idx.equal(D.col_idx)
     if VDT[semiring] is None:
@@ -79,8 +82,52 @@ def test_dense_rows_full():
     """Every row of a small matrix whose upper rows are dense."""
     A = _matrix(3, 9000, 40, 0.7, 2, [8999])
     C = sp.lower(sp.DeviceCSR.from_host(A, "cuda:0"), "f64")
-    assert sp.stats()["heavy_rows"] > 0
+    assert sp.stats()["cell_rows"] > 0
     compare_full(C, oracle.lower(A, "f64"), "f64", "lower")
+
+
+@pytest.mark.parametrize("semiring", ["f64", "count"])
+def test_dense_rows_of_many_cells(semiring):
+    """128 cells: eight groups of the symbolic pass, offsets over more than 64
+    cells, and 32 positions per block of the table of long columns."""
+    m, last = 1 << 20, 300
+    A = _matrix(20, m, 40, 0.004, 3, [m - 2, m - 700], last)
+    A = A.with_values(None if VDT[semiring] is None else A.values)
+    assert A.nnz > (1 << 21) + (1 << 14)  # (16 positions per block would be over 2^17 blocks of 128 cells)
+    dA = sp.DeviceCSR.from_host(A, "cuda:0")
+    print(f"[{semiring}] m={m} nnz={A.nnz}", flush=True)
+    rows = np.unique(np.concatenate([np.arange(0, m, m // 20), np.arange(m - last, m, 13), [m - 700, m - 2, m - 1]]))
+    ref = oracle.lower(A, semiring, rows=rows)
+    C = sp.lower(dA, semiring)
+    assert sp.stats()["cell_rows"] >= last - 1
+    compare_rows(C, ref, rows, semiring, "lower")
+    del C
+    plan, C = sp.lower_plan(dA, semiring)
+    compare_rows(C, ref, rows, semiring, "plan")
+    del C
+    B = A if VDT[semiring] is None else A.with_values(A.values * 2 - 1)
+    got = plan.execute(None if VDT[semiring] is None else sp.DeviceCSR.from_host(B, "cuda:0").values)
+    assert sp.stats()["cell_rows"] >= last - 1
+    compare_rows(got, oracle.lower(B, semiring, rows=rows), rows, semiring, "execute")
+    plan.close()
+
+
+def test_rows_of_more_lookups_than_products_stay_whole():
+    """Four rows of 40,000 entries and four partners each: 160,000 products, but
+    128 cells that would each look up every entry."""
+    m, wide, ln = 1 << 20, 4, 40000
+    rng = np.random.default_rng(5)
+    rows = np.concatenate([rng.permutation(m - wide)[:4 * ln], np.repeat(np.arange(m - wide, m), ln)])
+    cols = np.concatenate([np.tile(np.arange(ln), 4), np.tile(np.arange(ln), wide)])
+    o = np.lexsort((cols, rows))
+    rows, cols = rows[o], cols[o]
+    rp = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(np.bincount(rows, minlength=m), out=rp[1:])
+    A = CSR(m, ln, rp, cols.astype(np.int32), rng.standard_normal(len(cols)))
+    rows = np.concatenate([np.arange(0, m, m // 30), np.arange(m - wide, m)])
+    C = sp.lower(sp.DeviceCSR.from_host(A, "cuda:0"), "f64")
+    assert sp.stats()["heavy_rows"] == wide and sp.stats()["cell_rows"] == 0
+    compare_rows(C, oracle.lower(A, "f64", rows=rows), rows, "f64", "lower")
 
 
 def test_more_units_than_one_grid_dimension_holds():
@@ -101,8 +148,9 @@ def test_more_units_than_one_grid_dimension_holds():
     rows = np.concatenate([[0, m - last - 1, m - last, m - last + 5000], np.arange(m - last + 7000, m, 1999), [m - 1]])
     print(f"[units] nnz={A.nnz} dense rows={int((per_row >= 1 << 17).sum())}", flush=True)
     B = A.with_values(None)
-    compare_rows(sp.lower(sp.DeviceCSR.from_host(B, "cuda:0"), "count"), oracle.lower(B, "count", rows=rows), rows,
-                 "count", "lower")
+    C = sp.lower(sp.DeviceCSR.from_host(B, "cuda:0"), "count")
+    assert sp.stats()["cell_rows"] * 512 > 1 << 23
+    compare_rows(C, oracle.lower(B, "count", rows=rows), rows, "count", "lower")
     plan, C = sp.lower_plan(sp.DeviceCSR.from_host(A, "cuda:0"), "f64")
     compare_rows(C, oracle.lower(A, "f64", rows=rows), rows, "f64", "plan")
     del C
