@@ -15,6 +15,7 @@
 #include "common.h"
 #include "dense_layout.h"
 #include "internal.h"
+#include "sort_layout.h"
 #include "spsyrk.h"
 
 using namespace spsyrk;
@@ -276,6 +277,7 @@ struct Ctl {
     unsigned long long chunk_counter;
     unsigned long long maxlen;  // largest row length of the left operand
     unsigned long long dense[3];  // rows of at least kDenseProducts products, their entries and products
+    uint32_t digit[256];  // the first radix pass's digits of few entries (FirstHist::total)
 };
 
 struct HostCtl {
@@ -410,10 +412,11 @@ void validate(const DevCsr& A, bool upper_forbidden, Arena& ar, Ctl* ctl, hipStr
 // vsrc (N entries): the entry of B behind every position of the index.
 // entries: the index keeps {key, entry of B} instead of keys and values
 // (index_keeps_entries; vsrc is then not written).
+// local: the local sort may be used (hist1 counts its first digit).
 ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ctl, hipStream_t s,
                      const RunTab* run = nullptr, bool need_dir = true, uint32_t* ccount = nullptr, bool* counted = nullptr,
                      uint32_t* vsrc = nullptr, uint32_t* hist1 = nullptr, const int64_t* trow1 = nullptr,
-                   bool entries = false) {
+                   bool entries = false, bool local = true) {
     ColIndex cx;
     cx.n = B.n;
     cx.m = B.m;
@@ -448,6 +451,7 @@ ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ct
     if (sr == kJaccard && runs_given) cx.lenbits = 32 - cx.rowbits;
     cx.val = vb_out && cx.lenbits == 0 && !entries ? ar.get(size_t(N > 0 ? N : 1) * vb_out) : nullptr;
 
+    const int low = local ? local_bits(N, nbits_n) : 0;
     if (N > 0) {
         // records (column, row, entry index) sorted by column; values are
         // gathered by entry index when the keys are packed
@@ -457,10 +461,7 @@ ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ct
         uint32_t* rb = ar.get_t<uint32_t>(N);
         // with no run table and no entry map the local sort needs the entries'
         // values only, so the passes carry them instead of the entry indices
-        const int carried = runs_given && !run && !vsrc && (vb == 4 || vb == 8) && B.v &&
-                                    local_bits(N, nbits_n) > 0
-                                ? vb
-                                : 0;
+        const int carried = runs_given && !run && !vsrc && (vb == 4 || vb == 8) && B.v && low > 0 ? vb : 0;
         const size_t eb_bytes = size_t(N) * size_t(carried ? carried : int(sizeof(uint32_t)));
         uint32_t* ea = static_cast<uint32_t*>(ar.get(eb_bytes));
         uint32_t* eb = static_cast<uint32_t*>(ar.get(eb_bytes));
@@ -487,8 +488,8 @@ ColIndex build_index(const DevCsr& B, bool drop_last, int sr, Arena& ar, Ctl* ct
             pk.carried = carried;
             pk.ke = cx.ke;
         }
-        const int which = radix_sort_csr(B.ci, B.rp, B.m, cx.rowbits, lenbits, ka, kb, ra, rb, ea, eb, N, nbits_n, tmp,
-                                         s, runs_given ? &pk : nullptr, hist1, trow1);
+        const int which = radix_sort_csr(B.ci, B.rp, B.m, cx.rowbits, lenbits, ka, kb, ra, rb, ea, eb, N, nbits_n, low,
+                                         tmp, s, runs_given ? &pk : nullptr, local ? hist1 : nullptr, trow1);
         check_launch();
         ar.release(tmp);
         if (counted) *counted = which < 0 && ccount;
@@ -619,12 +620,13 @@ constexpr size_t kEarlyOutputBytes = size_t(16) << 30;
 // read from dense column starts.
 
 // checked: waits for the operands' validation flags and throws on a bad
-// operand; called before the first kernel that reads their indices.
+// operand; called before the first kernel that reads their indices.  Returns
+// whether the local sort may be used (few entries: by their groups' counts).
 // hist1 (optional): the first radix pass's digit counts of the sorted operand
 // (R), counted by its validation; vrows (optional, lower mode): the
 // validation's table of tile rows of A
 void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar, Ctl* ctl, hipStream_t s,
-                spsyrk_csr_out* C, const std::function<void()>& checked, LowerPlan* plan = nullptr,
+                spsyrk_csr_out* C, const std::function<bool()>& checked, LowerPlan* plan = nullptr,
                 uint32_t* hist1 = nullptr, const int64_t* vrows = nullptr) {
     const int64_t m = L.m;
     const int vbo = out_value_bytes(sr);
@@ -644,26 +646,27 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
     if (lower) {
         HIPCHK(hipMemsetAsync(run.r4, 0, size_t(L.nnz) * sizeof(uint32_t), s));
         if (run.radix == 1) HIPCHK(hipMemsetAsync(run.r8, 0, size_t(L.nnz) * sizeof(uint2), s));
-        const bool entries = index_keeps_entries(L, sr);
+        bool entries = index_keeps_entries(L, sr);
+        reserve_index(L, sr, ar, entries);
+        const bool local = checked();
+        entries = entries && local;
         uint32_t* vsrc = nullptr;
         if (plan && !entries) {
             vsrc = ar.get_t<uint32_t>(L.nnz);
             HIPCHK(hipMemsetAsync(vsrc, 0, size_t(L.nnz) * sizeof(uint32_t), s));
             plan->vsrc = vsrc;
         }
-        reserve_index(L, sr, ar, entries);
-        checked();
         Phase ph(SPSYRK_PHASE_COLINDEX, s);
-        cx = build_index(L, true, sr, ar, ctl, s, &run, true, nullptr, nullptr, vsrc, hist1, vrows, entries);
+        cx = build_index(L, true, sr, ar, ctl, s, &run, true, nullptr, nullptr, vsrc, hist1, vrows, entries, local);
         if (hist1) ar.release(hist1);
     } else {
-        checked();
+        const bool local = checked();
         Phase ph(SPSYRK_PHASE_COLINDEX, s);
         // column starts of R: from the counts the local sort writes, else by counting
         uint32_t* cptr = ar.get_t<uint32_t>(R.n + 1);
         HIPCHK(hipMemsetAsync(cptr, 0, size_t(R.n + 1) * sizeof(uint32_t), s));
         bool counted = false;
-        cx = build_index(R, false, sr, ar, ctl, s, nullptr, false, cptr, &counted, nullptr, hist1);
+        cx = build_index(R, false, sr, ar, ctl, s, nullptr, false, cptr, &counted, nullptr, hist1, nullptr, false, local);
         if (hist1) ar.release(hist1);
         void* ctmp = ar.get(scan_tmp_bytes(R.n + 1));
         if (counted)
@@ -930,7 +933,9 @@ void syrk(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar, hipSt
     const bool fused = (plan || !two_pass()) && (lower || R.n <= kDenseColumns);
     FirstHist fh;
     if (fused && R.nnz > 0 && L.m > 0 && L.nnz > 0) {
-        radix_first_digit(R.nnz, bit_width_u64(R.n > 1 ? uint64_t(R.n - 1) : 0), &fh.shift, &fh.mask);
+        const int nbits = bit_width_u64(R.n > 1 ? uint64_t(R.n - 1) : 0);
+        radix_first_digit(R.nnz, nbits, &fh.shift, &fh.mask);
+        if (local_by_counts(R.nnz, nbits)) fh.total = ctl->digit;
         fh.ntiles = (R.nnz + kRadixTile - 1) / kRadixTile;
         fh.hist = ar.get_t<uint32_t>(size_t(fh.ntiles) * 256);
     }
@@ -947,10 +952,11 @@ void syrk(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar, hipSt
     // allocations and clears that depend on the sizes alone, so that the
     // host prepares them while the validation runs.
     ctl_fetch(ctl, s);
-    const std::function<void()> checked = [&]() {
+    const std::function<bool()> checked = [&]() {
         const Ctl h = ctl_wait();
         check_valid(h.err, lower ? "A" : "Ai");
         if (!lower) check_valid(h.err2, "Aj");
+        return !fh.total || local_groups_fit(h.digit, 256);
     };
 
     const int64_t m = L.m;

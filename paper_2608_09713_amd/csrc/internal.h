@@ -134,6 +134,7 @@ struct FirstHist {
     int shift = 0;
     uint32_t mask = 0;
     int64_t ntiles = 0;
+    uint32_t* total = nullptr;  // (optional, zeroed, 256 words) the digits' counts over all tiles are added here
 };
 // ORs ErrBits into *err.  upper_forbidden: also flag entries with col > row.
 // tmp: validate_tmp_bytes(nnz) of scratch.
@@ -147,12 +148,13 @@ void fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 // Buffers *_a hold the input and the result is returned in the buffer
 // reported by the return value (0 -> *_a, 1 -> *_b).  vbytes in {0, 4, 8}.
 size_t radix_tmp_bytes(int64_t n);
-// scratch of radix_sort_csr for n entries and nbits-bit columns
+// scratch of radix_sort_csr for n entries and nbits-bit columns, by either path
 size_t radix_csr_tmp_bytes(int64_t n, int nbits);
 // Stable sort of the entries of a CSR matrix by column: the records
 // (column, row field, entry index) are formed inside the first pass.  The row
 // field is the row in its low rowbits bits and, if lenbits > 0, the row's
-// length saturated at 2^lenbits - 1 above them.  Returns 0 if the result is in
+// length saturated at 2^lenbits - 1 above them.  L: the low bits sorted inside
+// groups (local_bits; 0: passes over every bit).  Returns 0 if the result is in
 // the *_a buffers, 1 for *_b.
 // The column index in partner-run form, written by the sort itself when it
 // takes the local path: key (the row) and value of every entry at its sorted
@@ -187,13 +189,15 @@ struct LocalPack {
 // entries; -1 where left out), as the validation writes it
 int radix_sort_csr(const int32_t* col_idx, const int64_t* rp, int64_t m, int rowbits, int lenbits, uint32_t* key_a,
                    uint32_t* key_b, uint32_t* row_a, uint32_t* row_b, uint32_t* ent_a, uint32_t* ent_b, int64_t n,
-                   int nbits, void* tmp, hipStream_t s, const LocalPack* pk = nullptr, uint32_t* hist1 = nullptr,
+                   int nbits, int L, void* tmp, hipStream_t s, const LocalPack* pk = nullptr, uint32_t* hist1 = nullptr,
                    const int64_t* trow1 = nullptr);
-// Low column bits sorted inside groups by radix_sort_csr for n entries with
-// nbits-bit columns (0: passes over every bit, no local sort).
+// Low column bits to sort inside groups for n entries with nbits-bit columns
+// (0: passes over every bit, no local sort), and whether that holds only if
+// the groups' counts, the first pass's digits, fit (sort_layout.h).
 int local_bits(int64_t n, int nbits);
+bool local_by_counts(int64_t n, int nbits);
 // The digit of radix_sort_csr's first pass over n entries with nbits-bit
-// columns: (col >> shift) & mask.
+// columns and the low bits of local_bits: (col >> shift) & mask.
 void radix_first_digit(int64_t n, int nbits, int* shift, uint32_t* mask);
 int radix_sort(uint32_t* key_a, uint32_t* key_b, uint32_t* row_a, uint32_t* row_b, void* val_a,
                void* val_b, int vbytes, int64_t n, int nbits, void* tmp, hipStream_t s);

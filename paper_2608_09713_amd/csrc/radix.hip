@@ -15,11 +15,12 @@
 
 #include "common.h"
 #include "internal.h"
+#include "sort_layout.h"
 
 namespace spsyrk {
 namespace {
 
-constexpr int kRBits = 8;
+constexpr int kRBits = kSortDigit;
 constexpr int kDigits = 1 << kRBits;
 constexpr int kRItems = 12;
 constexpr int kRTile = kBlock * kRItems;  // records per tile
@@ -528,8 +529,6 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(const KI* __restrict__ k
 // gathers the records into place; a group too large for LDS is sorted by the
 // same workgroup over global memory, tile by tile.
 
-constexpr int kLBits = 12;       // low bits sorted locally
-constexpr int kLCap = 4096;      // records of a group sorted in LDS
 constexpr int kLCapS = 2048;     // the same in the packed sort's first launch (half the LDS and registers)
 constexpr int kLDig = 6;         // bits per local digit
 constexpr uint32_t kNoGroup = 0xffffffffu;
@@ -1084,30 +1083,14 @@ int digit_plan(int nbits, int (&width)[8]) {
 
 }  // namespace
 
-constexpr int64_t kFewRecords = int64_t(1) << 16;
-
-// Local-sort plan of a CSR column sort: the high h = nbits - L bits by passes,
-// the low L (1..kLBits) bits inside groups of equal high bits, about 2048
-// records per group on average.  Used for wide keys over many entries, and
-// for few entries, where it takes five launches instead of nine and the
-// passes are all latency (there with about 512 records per group, so that
-// more workgroups share them; a hub column's group is at most the whole
-// matrix).
-// (SPSYRK_LOCAL_SORT=1 forces it wherever it applies, =0 turns it off; read
-// at every call).  Returns L, or 0 for passes over all bits.
-int local_bits(int64_t n, int nbits) {
+// (SPSYRK_LOCAL_SORT=1 forces the local sort wherever it applies, =0 turns it
+// off; read at every call)
+static int forced_local() {
     const char* e = std::getenv("SPSYRK_LOCAL_SORT");
-    const bool force = e && e[0] == '1';
-    if (e && e[0] == '0') return 0;
-    const bool few = n <= kFewRecords;
-    if (!force && !few && (nbits < 22 || n < (int64_t(1) << 20))) return 0;
-    int h = nbits - kLBits;
-    const int hg = bit_width_u64(uint64_t(n / (few && !force ? 512 : 2048)));  // groups of about that many records
-    if (hg > h) h = hg;
-    if (h < 1) h = 1;
-    const int L = nbits - h;
-    return L >= 1 ? L : 0;
+    return e && (e[0] == '0' || e[0] == '1') ? e[0] - '0' : -1;
 }
+int local_bits(int64_t n, int nbits) { return local_sort_bits(n, nbits, forced_local()); }
+bool local_by_counts(int64_t n, int nbits) { return local_bits(n, nbits) > 0 && local_sort_checked(n, forced_local()); }
 
 void radix_first_digit(int64_t n, int nbits, int* shift, uint32_t* mask) {
     const int L = local_bits(n, nbits);
@@ -1135,7 +1118,7 @@ size_t radix_tmp_bytes(int64_t n) {
 
 int radix_sort_csr(const int32_t* col_idx, const int64_t* rp, int64_t m, int rowbits, int lenbits, uint32_t* key_a,
                    uint32_t* key_b, uint32_t* row_a, uint32_t* row_b, uint32_t* ent_a, uint32_t* ent_b, int64_t n,
-                   int nbits, void* tmp, hipStream_t s, const LocalPack* pk, uint32_t* hist1,
+                   int nbits, int L, void* tmp, hipStream_t s, const LocalPack* pk, uint32_t* hist1,
                    const int64_t* trow1) {
     if (n <= 0) return 0;
     const int64_t ntiles = (n + kRTile - 1) / kRTile;
@@ -1145,7 +1128,6 @@ int radix_sort_csr(const int32_t* col_idx, const int64_t* rp, int64_t m, int row
     int64_t* trow = reinterpret_cast<int64_t*>(static_cast<char*>(tmp) + hist_bytes);
     void* scan_tmp = static_cast<char*>(tmp) + hist_bytes + table_bytes;
     // passes over all bits, or over the high bits followed by the local sort
-    const int L = local_bits(n, nbits);
     int width[8];
     const int passes = digit_plan(nbits - L, width);
     // bytes of the values carried in place of the entry indices (local sort only)

@@ -181,6 +181,7 @@ __global__ __launch_bounds__(kBlock) void check_csr(const int64_t* __restrict__ 
 #pragma unroll
             for (int q = 0; q < kWavesPerBlock; ++q) t += cnt[q][threadIdx.x];
             fh.hist[int64_t(threadIdx.x) * fh.ntiles + etile] = t;
+            if (fh.total && t) atomicAdd(fh.total + threadIdx.x, t);
         }
     }
     if (bad) atomicOr(&bad_s, bad);

@@ -31,3 +31,8 @@ def test_dense_launches_stay_within_what_a_launch_takes(tmp_path):
     # every (row, cell) unit has a workgroup, no grid dimension reaches 2^32
     # threads, up to 2^22 rows of 512 cells
     assert _run_check("dense_layout_check", tmp_path).startswith("ok")
+
+
+def test_column_sort_groups_stay_in_proportion(tmp_path):
+    # few entries: at most 256 groups, none past what LDS holds
+    assert _run_check("sort_layout_check", tmp_path).startswith("ok")
