@@ -129,6 +129,9 @@ void scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* total, void* 
 // (hist: digit-major, ntiles x 256 words; digit (col >> shift) & mask), so
 // that the pass does not read the column ids once more for them.
 constexpr int kRadixTile = 3072;
+// Rows of a tile that its threads walk to find the records' rows, at most (128
+// per thread; past that a search per record is shorter).
+constexpr int64_t kMarkMost = int64_t(1) << 15;
 struct FirstHist {
     uint32_t* hist = nullptr;
     int shift = 0;

@@ -86,7 +86,9 @@ static_assert(kTileC == kTileE, "one tile table serves the walks and the copies"
 // lower rows' entries to their places in the full rows.  A copy, bound by
 // memory: the tile's entries are loaded first, 16 per thread in flight, while
 // the rows are found: every row that starts in the tile marks its first entry,
-// then a running maximum over the tile, so that no entry searches for its row.
+// then a running maximum over the tile, so that no entry searches for its row
+// (but in a tile of very many rows, almost all empty, where walking the rows
+// would take longer).
 // (60 M entries in rows of about 57, i32: 393 us with a search per entry, 311
 // so; 230 M entries in R-MAT's rows, f32: 920 us, 781 so)
 template <int VB>
@@ -116,21 +118,38 @@ __global__ __launch_bounds__(kBlock) void copy_lower(const int64_t* __restrict__
     }
     __syncthreads();
     const int64_t rlo = bounds[0], rhi = bounds[1];
-    for (int64_t r = rlo + 1 + threadIdx.x; r <= rhi; r += kBlock) {
-        const int64_t a = rp[r];
-        if (a - e0 < n && rp[r + 1] > a) mark[a - e0] = uint32_t(r - rlo);
-    }
-    __syncthreads();
-    uint32_t mine[kPerC], run = 0;
+    if (rhi - rlo > kMarkMost) {
+        int i = threadIdx.x;
+        asm volatile("" : "+v"(i));  // (opaque: no address of this loop is held across the loads' registers)
+#pragma unroll 1
+        for (; i < n; i += kBlock) {
+            uint32_t lo = 0, hi = uint32_t(rhi - rlo);
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi + 1) >> 1;
+                if (rp[rlo + mid] <= e0 + i)
+                    lo = mid;
+                else
+                    hi = mid - 1;
+            }
+            mark[i] = lo;
+        }
+    } else {
+        for (int64_t r = rlo + 1 + threadIdx.x; r <= rhi; r += kBlock) {
+            const int64_t a = rp[r];
+            if (a - e0 < n && rp[r + 1] > a) mark[a - e0] = uint32_t(r - rlo);
+        }
+        __syncthreads();
+        uint32_t mine[kPerC], run = 0;
 #pragma unroll
-    for (int u = 0; u < kPerC; ++u) {
-        run = max(run, mark[threadIdx.x * kPerC + u]);
-        mine[u] = run;
-    }
-    uint32_t all;
-    const uint32_t before = block_exclusive_max(run, wt, &all);
+        for (int u = 0; u < kPerC; ++u) {
+            run = max(run, mark[threadIdx.x * kPerC + u]);
+            mine[u] = run;
+        }
+        uint32_t all;
+        const uint32_t before = block_exclusive_max(run, wt, &all);
 #pragma unroll
-    for (int u = 0; u < kPerC; ++u) mark[threadIdx.x * kPerC + u] = max(before, mine[u]);
+        for (int u = 0; u < kPerC; ++u) mark[threadIdx.x * kPerC + u] = max(before, mine[u]);
+    }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kPerC; ++u) {

@@ -123,9 +123,11 @@ constexpr int kOutArrays = 0, kOutPlace = 1, kOutPlaceKeys = 2;
 // row pointers rp (rows [rlo, rhi] span the tile, rlo holding its first
 // record): every row that starts inside the tile marks its first record,
 // then a running maximum over the tile.  The rows are walked one by one, not
-// staged, so any number of empty rows may lie between (each row pointer is
-// read by about one tile); a tile of few rows compares with their starts
-// instead.  Called by all threads; wt: kWavesPerBlock words.
+// staged (each row pointer is read by about one tile); a tile of few rows
+// compares with their starts instead, and in one of very many rows, almost all
+// empty, every record searches for its row.  (2000 records of 2^24 rows, whole
+// mirror: 48 ms with the rows walked, 1.1 so.)  Called by all threads; wt:
+// kWavesPerBlock words.
 constexpr int kMarkFew = 8;  // rows after the first that are told apart by comparisons
 __device__ inline void tile_rows_mark(const int64_t* __restrict__ rp, int64_t rlo, int64_t rhi, int64_t base,
                                       uint32_t* rowof, uint32_t* wt) {
@@ -142,6 +144,12 @@ __device__ inline void tile_rows_mark(const int64_t* __restrict__ rp, int64_t rl
             for (int k = 0; k < kMarkFew; ++k) r += i >= st[k] ? 1u : 0u;
             rowof[i] = r;
         }
+        __syncthreads();
+        return;
+    }
+    if (rhi - rlo > kMarkMost) {
+#pragma unroll 1
+        for (int i = threadIdx.x; i < kRTile; i += kBlock) rowof[i] = uint32_t(last_leq_i64(rp, rlo, rhi, base + i));
         __syncthreads();
         return;
     }

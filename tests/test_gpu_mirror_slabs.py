@@ -70,3 +70,29 @@ def test_mirror_slab_shapes(dev, shape, m, bits, monkeypatch):
     M = sp.mirror(_raw(dev, rp, ci, m, None), "count")
     np.testing.assert_array_equal(M.to_host()[0], ref.row_ptr)
     np.testing.assert_array_equal(M.to_host()[1], ref.col_idx)
+
+
+@pytest.mark.parametrize("m,lens,diagonal", [
+    (1 << 20, [3] * 40, False),              # tiles of more rows than are walked, almost all empty
+    ((1 << 22) + 5, [2] * 900 + [5000, 3000], False),  # and long rows among them
+    (1 << 21, [2] * 30, True),               # the lower part full of diagonals, its records few
+    (1 << 15, [1] * 20, False),              # just within the rows that are walked
+    ((1 << 15) + 2, [1] * 20, False),
+])
+def test_mirror_of_mostly_empty_rows(dev, m, lens, diagonal):
+    rng = np.random.default_rng(m + len(lens))
+    at = np.sort(rng.choice(m - 1, len(lens), replace=False)) + 1
+    at[0], at[-1] = 1, m - 1
+    rows = np.repeat(at, lens)
+    cols = (rng.random(len(rows)) * rows).astype(np.int64)
+    key = rows * m + cols
+    if diagonal:
+        key = np.concatenate([key, np.arange(m) * (m + 1)])
+    key = np.unique(key)
+    rp = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(np.bincount(key // m, minlength=m), out=rp[1:])
+    ci, v = (key % m).astype(np.int32), rng.standard_normal(len(key))
+    print(f"[mirror mostly empty] m={m} nnz={len(ci)}", flush=True)
+    compare_full(sp.mirror(_raw(dev, rp, ci, m, v), "f64"), oracle.mirror(m, rp, ci, v), "f64", "mirror f64")
+    v32 = v.astype(np.float32)
+    compare_full(sp.mirror(_raw(dev, rp, ci, m, v32), "f32"), oracle.mirror(m, rp, ci, v32), "f32", "mirror f32")
