@@ -1261,7 +1261,11 @@ void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C
     void* va = vb ? ar.get(size_t(rec_max > 0 ? rec_max : 1) * vb) : nullptr;
     void* vbb = vb ? ar.get(size_t(rec_max > 0 ? rec_max : 1) * vb) : nullptr;
     void* rtmp = ar.get(radix_tmp_bytes(rec_max > 0 ? rec_max : 1));
-    int64_t* strow = ar.get_t<int64_t>(int64_t(mirror_tile_bytes(rec_max) / sizeof(int64_t)));
+    // (SPSYRK_SLAB_DIRECT=0, read at every call: the first pass reads extracted
+    // records instead of C_L itself: a pass over memory more)
+    const char* de = std::getenv("SPSYRK_SLAB_DIRECT");
+    const bool direct = !(de && de[0] == '0');
+    int64_t* strow = direct ? nullptr : ar.get_t<int64_t>(int64_t(mirror_tile_bytes(rec_max) / sizeof(int64_t)));
     for (size_t k = 0; k < slabs.size(); ++k) {
         const Slab& sl = slabs[k];
         if (sl.c1 <= sl.c0) continue;
@@ -1288,10 +1292,6 @@ void mirror(const DevCsr& L, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C
             io.before = sl.before;
             io.f_ci = f_ci;
             io.f_val = f_val;
-            // (SPSYRK_SLAB_DIRECT=0, read at every call: the first pass reads
-            // extracted records instead of C_L itself: a pass over memory more)
-            const char* de = std::getenv("SPSYRK_SLAB_DIRECT");
-            const bool direct = !(de && de[0] == '0');
             if (direct)
                 mirror_slab_offsets(row_lo, row_cnt, m, s);
             else

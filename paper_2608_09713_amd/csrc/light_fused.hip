@@ -703,10 +703,12 @@ __device__ void all_chunks(const FusedArgs& a) {
     }
 }
 
-// (Jaccard off the diagonal has no packed words)
-// (six wavefronts per SIMD, 80 VGPRs; plus-times five, 96)
+// Wavefronts per SIMD: six (80 VGPRs), plus-times five (96); Jaccard off the
+// diagonal, which has no packed words and so 64-bit keys of its own in LDS
+// (9 KiB per wavefront), four.
+constexpr int light_waves(int sr, bool lower) { return sr == kF64 || sr == kF32 ? 5 : (sr == kJaccard && !lower ? 4 : 6); }
 template <int SR, bool LOWER>
-__global__ __launch_bounds__(kWave* kWavesF) __attribute__((amdgpu_waves_per_eu(SR == kF64 || SR == kF32 ? 5 : 6)))
+__global__ __launch_bounds__(kWave* kWavesF) __attribute__((amdgpu_waves_per_eu(light_waves(SR, LOWER))))
 void fused_kernel(FusedArgs a) {
     all_chunks<SR, LOWER, SR == kJaccard && !LOWER>(a);
 }
@@ -827,7 +829,5 @@ void light_fused(const FusedArgs& a, hipStream_t s) {
         default: launch<kJaccard>(a, grid, s); break;
     }
 }
-
-int light_fused_waves_per_block() { return kWavesF; }
 
 }  // namespace spsyrk

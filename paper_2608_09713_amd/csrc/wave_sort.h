@@ -205,10 +205,6 @@ __device__ inline uint32_t inclusive_sum(uint32_t v) {
 __device__ inline uint32_t from_lane_before(uint32_t v, uint32_t first) {
     return uint32_t(__builtin_amdgcn_update_dpp(int(first), int(v), 0x138, 0xf, 0xf, false));  // wave_shr:1
 }
-// the value of the lane after (lane 63: last)
-__device__ inline uint32_t from_lane_after(uint32_t v, uint32_t last) {
-    return uint32_t(__builtin_amdgcn_update_dpp(int(last), int(v), 0x130, 0xf, 0xf, false));  // wave_shl:1
-}
 
 // sum over every group of 8 lanes, in all of its lanes
 __device__ inline double sum8(double v) {
