@@ -277,14 +277,18 @@ struct Ctl {
     unsigned long long chunk_counter;
     unsigned long long maxlen;  // largest row length of the left operand
     unsigned long long dense[3];  // rows of at least kDenseProducts products, their entries and products
-    uint32_t digit[256];  // the first radix pass's digits of few entries (FirstHist::total)
+};
+// with the first radix pass's digits of few entries (FirstHist::total)
+struct DigitCtl {
+    Ctl c;
+    uint32_t digit[256];
 };
 
 struct HostCtl {
-    Ctl* h = nullptr;
+    DigitCtl* h = nullptr;
     hipEvent_t ev = nullptr;  // recorded after the copy into h
     HostCtl() {
-        if (hipHostMalloc(reinterpret_cast<void**>(&h), sizeof(Ctl), hipHostMallocDefault) != hipSuccess) h = nullptr;
+        if (hipHostMalloc(reinterpret_cast<void**>(&h), sizeof(DigitCtl), hipHostMallocDefault) != hipSuccess) h = nullptr;
         if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
     }
     ~HostCtl() {
@@ -305,10 +309,10 @@ HostCtl& host_ctl() {
 // Enqueue the copy of the control block to the host; ctl_wait returns it
 // once the copy is done, while the work enqueued after the copy may still
 // run.  (One copy in flight per thread: every ctl_fetch is followed by its
-// ctl_wait before the next.)
-void ctl_fetch(const Ctl* d, hipStream_t s) {
+// ctl_wait before the next.)  digits: d is a DigitCtl, fetched whole.
+void ctl_fetch(const Ctl* d, hipStream_t s, bool digits = false) {
     HostCtl& pin = host_ctl();
-    HIPCHK(hipMemcpyAsync(pin.h, d, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(pin.h, d, digits ? sizeof(DigitCtl) : sizeof(Ctl), hipMemcpyDeviceToHost, s));
     HIPCHK(hipEventRecord(pin.ev, s));
 }
 
@@ -320,7 +324,7 @@ Ctl ctl_wait() {
     while ((e = hipEventQuery(pin.ev)) == hipErrorNotReady) {
     }
     HIPCHK(e);
-    return *pin.h;
+    return pin.h->c;
 }
 
 Ctl read_ctl(const Ctl* d, hipStream_t s) {
@@ -925,17 +929,20 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
 // C = tril(L R^T) (lower) or L R^T (offdiag), with R = L for lower.
 void syrk(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar, hipStream_t s, spsyrk_csr_out* C,
           LowerPlan* plan = nullptr) {
-    Ctl* ctl = ar.get_t<Ctl>(1);
-    zero_ctl(ctl, s);
     // on the single-pass path the validation of the operand whose columns
     // are sorted (R, which is L in lower mode) also counts the first radix
-    // pass's digits
+    // pass's digits, and for few entries their totals beside the control block
     const bool fused = (plan || !two_pass()) && (lower || R.n <= kDenseColumns);
+    const bool counts = fused && R.nnz > 0 && L.m > 0 && L.nnz > 0;
+    const int nbits = bit_width_u64(R.n > 1 ? uint64_t(R.n - 1) : 0);
+    const bool digits = counts && local_by_counts(R.nnz, nbits);
+    const size_t ctl_bytes = digits ? sizeof(DigitCtl) : sizeof(Ctl);
+    Ctl* ctl = static_cast<Ctl*>(ar.get(ctl_bytes));
+    HIPCHK(hipMemsetAsync(ctl, 0, ctl_bytes, s));
     FirstHist fh;
-    if (fused && R.nnz > 0 && L.m > 0 && L.nnz > 0) {
-        const int nbits = bit_width_u64(R.n > 1 ? uint64_t(R.n - 1) : 0);
+    if (counts) {
         radix_first_digit(R.nnz, nbits, &fh.shift, &fh.mask);
-        if (local_by_counts(R.nnz, nbits)) fh.total = ctl->digit;
+        if (digits) fh.total = reinterpret_cast<DigitCtl*>(ctl)->digit;
         fh.ntiles = (R.nnz + kRadixTile - 1) / kRadixTile;
         fh.hist = ar.get_t<uint32_t>(size_t(fh.ntiles) * 256);
     }
@@ -951,12 +958,12 @@ void syrk(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar, hipSt
     // the matrices' indices; the single-pass path first enqueues the
     // allocations and clears that depend on the sizes alone, so that the
     // host prepares them while the validation runs.
-    ctl_fetch(ctl, s);
+    ctl_fetch(ctl, s, digits);
     const std::function<bool()> checked = [&]() {
         const Ctl h = ctl_wait();
         check_valid(h.err, lower ? "A" : "Ai");
         if (!lower) check_valid(h.err2, "Aj");
-        return !fh.total || local_groups_fit(h.digit, 256);
+        return !digits || local_groups_fit(host_ctl().h->digit, 256);
     };
 
     const int64_t m = L.m;
