@@ -276,7 +276,7 @@ struct Ctl {
     unsigned long long heavy_sums[2];  // entries of A and output entries of the heavy rows
     unsigned long long chunk_counter;
     unsigned long long maxlen;  // largest row length of the left operand
-    unsigned long long dense[3];  // rows of at least kDenseProducts products, their entries and products
+    unsigned long long dense[6];  // rows that may go by cells, their entries and products, of dense_row's two kinds
 };
 // with the first radix pass's digits of few entries (FirstHist::total)
 struct DigitCtl {
@@ -586,13 +586,12 @@ bool index_keeps_entries(const DevCsr& B, int sr) {
     return local_bits(B.nnz, bit_width_u64(B.n > 1 ? uint64_t(B.n - 1) : 0)) > 0;
 }
 
-// Whether the rows of at least kDenseProducts products (rows, entries and
-// products in all) go by cells, lower mode.  SPSYRK_DENSE_ROWS=0 (read at every
-// call) turns it off.
-bool use_dense(const unsigned long long (&dense)[3], int64_t nnz, int64_t m) {
+// Which rows go by cells, lower mode (dense_kinds, counts as classify_rows
+// gives them).  SPSYRK_DENSE_ROWS=0 (read at every call) turns it off.
+int use_dense(const unsigned long long (&dense)[6], int64_t nnz, int64_t m) {
     const char* e = std::getenv("SPSYRK_DENSE_ROWS");
-    if (e && e[0] == '0') return false;
-    return dense_rows_pay(int64_t(dense[0]), dense[1], dense[2], nnz, m);
+    if (e && e[0] == '0') return 0;
+    return dense_kinds({dense[0], dense[1], dense[2]}, {dense[3], dense[4], dense[5]}, nnz, m);
 }
 
 // The buffers build_index takes for the column index of B in lower mode
@@ -718,18 +717,18 @@ void syrk_fused(const DevCsr& L, const DevCsr& R, bool lower, int sr, Arena& ar,
     }
     HeavyArgs ha;
     int64_t* heavy_nnz = nullptr;
+    const int cell_kinds = lower ? use_dense(h.dense, L.nnz, m) : 0;
     if (nheavy > 1) {
         // the rows with the most products first, so that none starts last
         void* otmp = ar.get(heavy_order_tmp_bytes(nheavy));
-        heavy_order(heavy_rows, nheavy, prod, otmp, s);
+        heavy_order(heavy_rows, nheavy, prod, L.rp, cell_kinds > 1 ? dense_cells(m) : 0, otmp, s);
         check_launch();
         ar.release(otmp);
     }
-    // The rows with the most products, the first of the ordered list, go by
-    // cells (dense.hip) where that pays.
+    // The first rows of the ordered list go by cells (dense.hip) where that pays.
     DenseArgs da;
-    const int64_t ndense = int64_t(h.dense[0]);
-    if (lower && use_dense(h.dense, L.nnz, m)) {
+    const int64_t ndense = int64_t(h.dense[0] + (cell_kinds > 1 ? h.dense[3] : 0));
+    if (cell_kinds > 0) {
         da.rp = L.rp;
         da.val = L.v;
         da.cx = cx;

@@ -1,8 +1,8 @@
 // Gustavson accumulation of the rows with the most products (power-law
-// graphs: rows of hundreds to thousands of entries that meet hub columns),
-// lower mode.
+// graphs: rows of hundreds to thousands of entries that meet hub columns) and
+// of rows that fill their columns, lower mode.
 //
-// Such a row is too long for one workgroup: on R-MAT scale 19 (f32) the
+// A row of the first kind is too long for one workgroup: on R-MAT scale 19 (f32) the
 // largest rows alone (20,000 entries, 6 million products) kept a workgroup
 // busy for 57 ms, the length of the whole pass, through hundreds of value
 // tiles that each search the ends of every entry's stretch.  Here (12 ms for

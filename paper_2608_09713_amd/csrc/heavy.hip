@@ -16,7 +16,8 @@
 // shared out evenly over the wavefronts (stretches.h).  What bounds a row are
 // its chains of dependent loads (a search is about ten, each a miss in L2)
 // and LDS traffic: marks and values run at about 300 G products/s each.  The
-// rows of 2^17 products and more go to dense.hip in lower mode; together the
+// rows of 2^17 products and more, and shorter ones that fill their columns, go
+// to dense.hip in lower mode; together the
 // two numeric passes take 30 ms on R-MAT scale 19 in f32 (57 ms with one
 // workgroup for every row, whose largest rows set its length).
 //

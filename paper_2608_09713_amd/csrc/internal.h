@@ -283,9 +283,9 @@ void light_fused(const FusedArgs& a, hipStream_t s);
 // the sum of prod over all rows into the two counters
 // and ub[i] = products + diagonal for light rows, 0 for heavy rows (and ub[m]
 // = 0); maxlen
-// (optional, zeroed): the largest row length; dense (optional, zeroed, three
-// words): the rows of at least kDenseProducts products, their entries and
-// their products
+// (optional, zeroed): the largest row length; dense (optional, zeroed, six
+// words): the rows that may go by cells, their entries and their products, of
+// at least kDenseProducts products and then of dense_row's others
 void classify_rows(const int64_t* rp, const unsigned long long* prod, int64_t m, bool lower, int32_t* heavy_rows,
                    int32_t* heavy_count, unsigned long long* light_cap, unsigned long long* prod_sum, int64_t* ub,
                    hipStream_t s, unsigned long long* maxlen = nullptr, unsigned long long* dense = nullptr);
@@ -329,10 +329,12 @@ void compact_rows(int64_t m, int64_t staged, const int64_t* ubp, const int64_t* 
                   const int64_t* rp_a = nullptr);
 // Reorders the heavy-row list rows[0..n) by decreasing magnitude of their
 // product counts (powers of two; stable inside one), so that the rows with
-// the most work are taken first from the heavy kernels' queue.
+// the most work are taken first from the heavy kernels' queue; ncells > 0: the
+// rows that go by cells (dense_row) before all others.
 // tmp: heavy_order_tmp_bytes(n)
 size_t heavy_order_tmp_bytes(int64_t n);
-void heavy_order(int32_t* rows, int64_t n, const unsigned long long* prod, void* tmp, hipStream_t s);
+void heavy_order(int32_t* rows, int64_t n, const unsigned long long* prod, const int64_t* rp, int ncells, void* tmp,
+                 hipStream_t s);
 // Over the rows listed in rows[0..n): adds the entries of A (rp) to out[0]
 // and the output entries (c_rp) to out[1] (zeroed beforehand).
 void heavy_sums(const int32_t* rows, int64_t n, const int64_t* rp, const int64_t* c_rp, unsigned long long* out,

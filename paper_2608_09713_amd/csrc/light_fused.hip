@@ -758,10 +758,11 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
                                                           bool lower, int32_t* __restrict__ heavy_rows,
                                                           int32_t* heavy_count, unsigned long long* light_cap,
                                                           unsigned long long* prod_sum, int64_t* __restrict__ ub,
-                                                          unsigned long long* maxlen, unsigned long long* dense) {
+                                                          unsigned long long* maxlen, unsigned long long* dense,
+                                                          int ncells) {
     __shared__ unsigned long long wt[kWavesPerBlock][3];
-    __shared__ unsigned long long dn[3];
-    if (threadIdx.x < 3) dn[threadIdx.x] = 0;
+    __shared__ unsigned long long dn[6];
+    if (threadIdx.x < 6) dn[threadIdx.x] = 0;
     __syncthreads();
     unsigned long long cap = 0, ps = 0, ml = 0;
     for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < m; i += int64_t(gridDim.x) * kBlock) {
@@ -775,10 +776,11 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
             cap += u;
         } else {
             heavy_rows[atomicAdd(heavy_count, 1)] = int32_t(i);
-            if (pr >= kDenseProducts) {
-                atomicAdd(&dn[0], 1ull);
-                atomicAdd(&dn[1], (unsigned long long)len);
-                atomicAdd(&dn[2], pr);
+            if (dense_row(pr, uint64_t(len), ncells)) {
+                unsigned long long* d = dn + (pr >= kDenseProducts ? 0 : 3);
+                atomicAdd(d, 1ull);
+                atomicAdd(d + 1, (unsigned long long)len);
+                atomicAdd(d + 2, pr);
             }
         }
         ub[i] = u;
@@ -804,7 +806,7 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const int64_t* __restr
         if (p) atomicAdd(prod_sum, p);
         if (l && maxlen) atomicMax(maxlen, l);
     }
-    if (dense && threadIdx.x < 3 && dn[threadIdx.x]) atomicAdd(dense + threadIdx.x, dn[threadIdx.x]);
+    if (dense && threadIdx.x < 6 && dn[threadIdx.x]) atomicAdd(dense + threadIdx.x, dn[threadIdx.x]);
 }
 
 }  // namespace
@@ -816,7 +818,7 @@ void classify_rows(const int64_t* rp, const unsigned long long* prod, int64_t m,
     int64_t grid = (m + kBlock - 1) / kBlock;
     if (grid > 1024) grid = 1024;
     classify_kernel<<<unsigned(grid), kBlock, 0, s>>>(rp, prod, m, lower, heavy_rows, heavy_count, light_cap,
-                                                      prod_sum, ub, maxlen, dense);
+                                                      prod_sum, ub, maxlen, dense, dense_cells(m));
 }
 
 void light_fused(const FusedArgs& a, hipStream_t s) {

@@ -2,6 +2,7 @@
 // light rows into the final CSR arrays, the row of every tile start, and the
 // partner runs of an off-diagonal block from dense column starts.
 #include "common.h"
+#include "dense_layout.h"
 #include "internal.h"
 #include "lookup.h"
 
@@ -441,12 +442,18 @@ void heavy_sums(const int32_t* rows, int64_t n, const int64_t* rp, const int64_t
 }
 
 namespace {
-// sort key of a heavy row: rows with more products first (63 - bits of the count)
+// sort key of a heavy row: with ncells the rows that go by cells first, then
+// rows with more products first (63 - bits of the count)
 __global__ __launch_bounds__(kBlock) void heavy_order_keys(const int32_t* __restrict__ rows, int64_t n,
                                                            const unsigned long long* __restrict__ prod,
+                                                           const int64_t* __restrict__ rp, int ncells,
                                                            uint32_t* __restrict__ key) {
     const int64_t q = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (q < n) key[q] = uint32_t(63 - bit_width_u64(prod[rows[q]]));
+    if (q >= n) return;
+    const int32_t r = rows[q];
+    const uint64_t p = prod[r];
+    const bool cells = ncells > 0 && dense_row(p, uint64_t(rp[r + 1] - rp[r]), ncells);
+    key[q] = uint32_t(63 - bit_width_u64(p)) + (ncells > 0 && !cells ? 64u : 0u);
 }
 }  // namespace
 
@@ -454,16 +461,17 @@ size_t heavy_order_tmp_bytes(int64_t n) {
     return 3 * ((size_t(n) * sizeof(uint32_t) + 255) & ~size_t(255)) + radix_tmp_bytes(n);
 }
 
-void heavy_order(int32_t* rows, int64_t n, const unsigned long long* prod, void* tmp, hipStream_t s) {
+void heavy_order(int32_t* rows, int64_t n, const unsigned long long* prod, const int64_t* rp, int ncells,
+                 void* tmp, hipStream_t s) {
     if (n <= 1) return;
     const size_t a = (size_t(n) * sizeof(uint32_t) + 255) & ~size_t(255);
     uint32_t* ka = static_cast<uint32_t*>(tmp);
     uint32_t* kb = reinterpret_cast<uint32_t*>(static_cast<char*>(tmp) + a);
     uint32_t* rb = reinterpret_cast<uint32_t*>(static_cast<char*>(tmp) + 2 * a);
     void* rtmp = static_cast<char*>(tmp) + 3 * a;
-    heavy_order_keys<<<unsigned((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(rows, n, prod, ka);
+    heavy_order_keys<<<unsigned((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(rows, n, prod, rp, ncells, ka);
     uint32_t* ra = reinterpret_cast<uint32_t*>(rows);
-    if (radix_sort(ka, kb, ra, rb, nullptr, nullptr, 0, n, 6, rtmp, s))
+    if (radix_sort(ka, kb, ra, rb, nullptr, nullptr, 0, n, ncells > 0 ? 7 : 6, rtmp, s))
         (void)hipMemcpyAsync(rows, rb, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
 }
 

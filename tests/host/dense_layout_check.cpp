@@ -41,17 +41,31 @@ int main() {
         }
     // R-MAT's rows go by cells (scale 19 and 20: rows, entries, products), few
     // rows of many entries and few partners do not: more lookups than products
-    if (!dense_rows_pay(5408, 3323000, 1674000000, 7970000, int64_t(1) << 19)) return 1;
-    if (!dense_rows_pay(14859, 8180000, 5470000000, 16090000, int64_t(1) << 20)) return 1;
-    if (dense_rows_pay(64, 64 * 131072, 64 * uint64_t(131072), 2 * 64 * 131072, kDenseMaxRows)) return 1;
-    if (dense_rows_pay(63, 6300000, 206000000, 6500000, kDenseMaxRows)) return 1;
+    const DenseSums no{0, 0, 0};
+    if (dense_kinds({5408, 3323000, 1674000000}, no, 7970000, int64_t(1) << 19) != 1) return 1;
+    if (dense_kinds({14859, 8180000, 5470000000}, no, 16090000, int64_t(1) << 20) != 1) return 1;
+    if (dense_kinds({64, 64 * 131072, 64 * uint64_t(131072)}, no, 2 * 64 * 131072, kDenseMaxRows)) return 1;
+    if (dense_kinds({63, 6300000, 206000000}, no, 6500000, kDenseMaxRows)) return 1;
     // never: no rows, too many rows in all, entries that outnumber the products
-    if (dense_rows_pay(0, 0, 0, 0, 1000) || dense_rows_pay(1, 10, 1 << 20, 10, kDenseMaxRows + 1) ||
-        dense_rows_pay(1, 10, 1 << 17, (1 << 17) + 1, 1000))
+    if (dense_kinds(no, no, 0, 1000) || dense_kinds({1, 10, 1 << 20}, no, 10, kDenseMaxRows + 1) ||
+        dense_kinds({1, 10, 1 << 17}, no, (1 << 17) + 1, 1000))
         return 1;
     // a row just within, and just past, its lookups
-    if (!dense_rows_pay(1, (1 << 17) / 512, 1 << 17, 1000, kDenseMaxRows) ||
-        dense_rows_pay(1, (1 << 17) / 512 + 1, 1 << 17, 1000, kDenseMaxRows))
+    if (dense_kinds({1, (1 << 17) / 512, 1 << 17}, no, 1000, kDenseMaxRows) != 1 ||
+        dense_kinds({1, (1 << 17) / 512 + 1, 1 << 17}, no, 1000, kDenseMaxRows))
+        return 1;
+    // shorter rows: enough products in all, for the matrix's entries too, and
+    // not beside longer rows with more lookups than products
+    const DenseSums few{1000, 100000, kDenseTotal};
+    if (dense_kinds(no, few, 1000, 8192) != 2 || dense_kinds({1, 10, 1 << 17}, few, 1000, 8192) != 2 ||
+        dense_kinds(no, {1000, 100000, kDenseTotal - 1}, 1000, 8192) ||
+        dense_kinds(no, few, int64_t(kDenseTotal / 2) + 1, 8192) || dense_kinds(no, few, 1000, kDenseMaxRows + 1) ||
+        dense_kinds({1, 1 << 17, 1 << 17}, few, 1000, 8193))
+        return 1;
+    // a row of kDenseProducts products in any case, a shorter one that fills its cells
+    if (!dense_row(kDenseProducts, kDenseProducts, 512) || dense_row(kDenseFew - 1, 1, 1) ||
+        !dense_row(kDenseFew, kDenseFew / kDenseFill, 1) || dense_row(kDenseFew, kDenseFew / kDenseFill + 1, 1) ||
+        dense_row(kDenseFew, kDenseFew / kDenseFill, 2))
         return 1;
     std::printf("ok %ld\n", checked);
     return 0;

@@ -1,5 +1,5 @@
-"""Rows of 2^17 products and more, which go by cells of 2^13 output columns
-(the heavy rows' units of work otherwise being whole rows), against the
+"""Rows of 2^17 products and more, and shorter ones that fill their columns,
+which go by cells of 2^13 output columns (the heavy rows' units of work otherwise being whole rows), against the
 oracle: rows on both sides of a cell's edge, columns on both sides of the
 length from which the table of cells holds them (16 entries, 32 in the matrix
 of 128 cells), more than 1024 entries in a row, and the same product with the
@@ -84,6 +84,67 @@ def test_dense_rows_full():
     C = sp.lower(sp.DeviceCSR.from_host(A, "cuda:0"), "f64")
     assert sp.stats()["cell_rows"] > 0
     compare_full(C, oracle.lower(A, "f64"), "f64", "lower")
+
+
+def _cols_shared(m, n, per_row, some):
+    """per_row entries of every row in n columns; with some, every third row's in
+    40 times as many."""
+    rng = np.random.default_rng(m)
+    rows, cols = np.repeat(np.arange(m), per_row), rng.integers(0, n, m * per_row)
+    if some:
+        cols[rows % 3 == 0] += n * rng.integers(1, 41, (rows % 3 == 0).sum())
+    key = np.unique(rows * (41 * n) + cols)
+    rows, cols = key // (41 * n), key % (41 * n)
+    rp = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(np.bincount(rows, minlength=m), out=rp[1:])
+    return CSR(m, 41 * n, rp, cols.astype(np.int32), rng.standard_normal(len(cols)))
+
+
+@pytest.mark.parametrize("semiring", ["f64", "f32", "count", "jaccard"])
+@pytest.mark.parametrize("m, n, per_row, some", [(1400, 600, 200, False), (8193, 3000, 130, True)])
+def test_rows_that_fill_their_cells(semiring, m, n, per_row, some, monkeypatch):
+    """Rows of 2^14 to 2^17 products: of one cell, and of two (at least 128
+    products per entry), beside rows whose columns are too short.  They are
+    more than 2^25 products in all; those of the matrix's upper half are fewer
+    and stay whole."""
+    A = _cols_shared(m, n, per_row, some)
+    A = A.with_values(None if VDT[semiring] is None else A.values.astype(VDT[semiring]))
+    rp = A.row_ptr
+    count = np.zeros(A.ncols, dtype=np.int64)
+    products = np.zeros(m, dtype=np.int64)
+    for i in range(m):
+        c = A.col_idx[rp[i]:rp[i + 1]]
+        products[i] = count[c].sum()
+        count[c] += 1
+    few = (products >= 1 << 14) & (products >= 64 * -(-m // 8192) * np.diff(rp))
+    assert products.max() < 1 << 17 and products[few].sum() >= 1 << 25 and few.sum() < m
+    dA = sp.DeviceCSR.from_host(A, "cuda:0")
+    print(f"[{semiring}] m={m} nnz={A.nnz} rows by cells={few.sum()}", flush=True)
+    rows = np.unique(np.append(np.arange(0, m, 7), [m // 2 - 1, m - 2, m - 1]))
+    ref = oracle.lower(A, semiring, rows=rows)
+    C = sp.lower(dA, semiring)
+    assert sp.stats()["cell_rows"] == few.sum() < sp.stats()["heavy_rows"]
+    compare_rows(C, ref, rows, semiring, "lower")
+    monkeypatch.setenv("SPSYRK_DENSE_ROWS", "0")
+    D = sp.lower(dA, semiring)
+    assert sp.stats()["cell_rows"] == 0
+    monkeypatch.delenv("SPSYRK_DENSE_ROWS")
+    assert C.row_ptr.equal(D.row_ptr) and C.col_idx.equal(D.col_idx)
+    if VDT[semiring] is None:
+        assert C.values.equal(D.values)
+    plan, C = sp.lower_plan(dA, semiring)
+    compare_rows(C, ref, rows, semiring, "plan")
+    compare_rows(plan.execute(dA.values), ref, rows, semiring, "execute")
+    assert sp.stats()["cell_rows"] == few.sum()
+    plan.close()
+    h = m // 2
+    assert products[:h][few[:h]].sum() < 1 << 25
+    U = CSR(h, A.ncols, rp[:h + 1].copy(), A.col_idx[:rp[h]].copy(),
+            None if A.values is None else A.values[:rp[h]].copy())
+    C = sp.lower(sp.DeviceCSR.from_host(U, "cuda:0"), semiring)
+    assert sp.stats()["cell_rows"] == 0
+    rows = rows[rows < h]
+    compare_rows(C, oracle.lower(U, semiring, rows=rows), rows, semiring, "upper half")
 
 
 @pytest.mark.parametrize("semiring", ["f64", "count"])
