@@ -40,7 +40,7 @@ constexpr int kFR = kFusedRows;      // rows per chunk (upper limit: one per lan
 // product slots per batch
 constexpr int slots(bool val) { return val ? 768 : 1024; }
 constexpr int kWavesF = 2;           // wavefronts per workgroup
-constexpr int kDealtBelow = 16;      // chunks per launched wavefront below which chunks are dealt out
+constexpr int64_t kDealtBelow = 98304;  // chunks below which they are dealt out (all_chunks)
 constexpr int kOrdBits = 9;          // product index bits of a 32-bit plus-times key (column above them)
 constexpr uint32_t kNoRun = 0x80000000u;  // a slot where no run starts (starts are below 2^31, slots below 2^11)
 static_assert(kFR <= kWave, "one row per lane");
@@ -655,14 +655,18 @@ struct Chunk {
     }
 };
 
-// Persistent wavefronts.  With few chunks per launched wavefront the chunks
-// are dealt out in turn (c, c + stride, ...).  With many, the wavefronts take
-// runs of consecutive chunks from a counter, so that every wavefront the
-// device holds keeps busy however many of the launched ones are resident at
-// once and however the chunks' costs vary: a run is a quarter of the chunks
-// left per launched wavefront (as last seen), at least one, so the runs
-// shrink towards the end.  The next chunk is taken and its head loaded while
-// the current chunk runs.
+// Persistent wavefronts.  Up to kDealtBelow chunks they are dealt out in turn
+// (c, c + stride, ...).  Past that, the wavefronts take runs of consecutive
+// chunks from a counter, so that every wavefront the device holds keeps busy
+// however many of the launched ones are resident at once and however the
+// chunks' costs vary: a run is a quarter of the chunks left per launched
+// wavefront (as last seen), at least one, so the runs shrink towards the end.
+// The next chunk is taken and its head loaded while the current chunk runs.
+// The runs cost an atomic add on one address each, about 10 ns, 46,000 of them
+// for 65,536 chunks: 0.5 ms, which only long launches hide, so the line lies
+// at a number of chunks (64 rows each there), whatever the wavefronts.  (Dealt
+// against counted: off-diagonal Jaccard, 2^20 rows in 65,536 chunks, whole call
+// 0.96 and 1.38 ms; f64, 1.4 M rows in 87,500 chunks, 1.04 and 1.43.)
 template <int SR, bool LOWER, bool WIDE>
 __device__ void all_chunks(const FusedArgs& a) {
     using C = Chunk<SR, LOWER, WIDE>;
@@ -671,7 +675,7 @@ __device__ void all_chunks(const FusedArgs& a) {
     const int lane = lane_id();
     if (blockIdx.x == 0 && threadIdx.x == 0) a.row_cnt[a.m] = 0;  // (the scan's last input)
     const int64_t nwaves = int64_t(gridDim.x) * kWavesF;
-    const bool dealt = a.nchunks < kDealtBelow * nwaves;
+    const bool dealt = a.nchunks < kDealtBelow;
     int64_t seen = 0, rend = 0;
     auto take = [&]() -> int64_t {
         if (dealt) {

@@ -122,3 +122,23 @@ def test_index_of_entries(semiring, dense, monkeypatch):
         got = plan.execute(sp.DeviceCSR.from_host(B, "cuda:0").values)
         compare_full(got, oracle.lower(B, semiring), semiring, f"execute {k}")
     plan.close()
+
+
+@pytest.mark.parametrize("semiring", ["f64", "jaccard"])
+@pytest.mark.parametrize("m", [98303, 98304, 100001])
+def test_chunks_dealt_and_counted(semiring, m, monkeypatch):
+    """One row per chunk: the most chunks that are dealt out in turn, and the
+    fewest that are taken from a counter; lower (32-bit keys) and off the
+    diagonal (Jaccard: 64-bit keys, fewer wavefronts)."""
+    monkeypatch.setenv("SPSYRK_ROWS_PER_CHUNK", "1")
+    rng = np.random.default_rng(m)
+    D = np.sort(rng.choice(m // 2, (m, 4)), axis=1)
+    keep = np.ones(D.shape, dtype=bool)
+    keep[:, 1:] = D[:, 1:] != D[:, :-1]
+    keep[rng.integers(0, m, 5000)] = False  # (empty rows)
+    rp = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(keep.sum(1), out=rp[1:])
+    A = _as(CSR(m, m // 2, rp, D[keep].astype(np.int32), rng.standard_normal(int(rp[-1]))), semiring)
+    dA = sp.DeviceCSR.from_host(A, "cuda:0")
+    compare_full(sp.lower(dA, semiring), oracle.lower(A, semiring), semiring, "lower")
+    compare_full(sp.offdiag(dA, dA, semiring), oracle.offdiag(A, A, semiring), semiring, "offdiag")
