@@ -18,6 +18,8 @@ constexpr uint64_t kDenseProducts = uint64_t(1) << 17;
 constexpr uint64_t kDenseFew = uint64_t(1) << 14;
 constexpr uint64_t kDenseFill = 64;
 constexpr uint64_t kDenseTotal = uint64_t(1) << 25;  // products of the shorter ones in all, at least
+constexpr int kDenseSplit = 8;         // cells of a row that pay even for a few rows
+constexpr uint64_t kDenseUnits = 512;  // (row, cell) units with fewer cells, at least
 constexpr int64_t kDenseMaxRows = int64_t(1) << 22;  // rows (and output columns) of the matrix, at most: 512 cells
 
 constexpr int dense_cells(int64_t m) { return int((m + kCell - 1) >> kCellBits); }
@@ -60,12 +62,23 @@ constexpr int64_t dense_blocks(int64_t positions, int blk_log) { return (positio
 // columns, 14.1 and 14.5 against 16.7 ms, but R-MAT scale 18 16.1 and 14.2
 // against 13.6.  R-MAT scale 12 to 14 with 2^14 products each and no total:
 // 0.43 to 0.81 ms become 0.51 to 0.92.)
+//
+// Few cells split a row into few units, and then a few rows are not worth the
+// passes of their own, which leave most of the device idle while the other
+// rows wait: two workgroups per compute unit at least.  (64 rows of 32,768
+// entries in 2^18 columns, one cell, 24 rows of 2^17 products and more: 2.70 ms
+// in f64 by cells and 1.87 whole, 2.50 and 1.74 as counts; 1000 of 8192 in
+// 2^18, 480 rows, 2.31 and 2.22; 4000 of 4096, 2000 rows, 4.28 and 4.79.)
 struct DenseSums {
     uint64_t rows, entries, products;
 };
 constexpr int dense_kinds(DenseSums top, DenseSums few, int64_t nnz, int64_t m) {
-    if (m > kDenseMaxRows || top.entries * uint64_t(dense_cells(m)) > top.products) return 0;
-    if (few.products >= kDenseTotal && top.products + few.products >= 2 * uint64_t(nnz)) return 2;
+    const uint64_t cells = uint64_t(dense_cells(m));
+    if (m > kDenseMaxRows || top.entries * cells > top.products) return 0;
+    const bool both = few.products >= kDenseTotal && top.products + few.products >= 2 * uint64_t(nnz);
+    const uint64_t rows = top.rows + (both ? few.rows : 0);
+    if (cells < kDenseSplit && rows * cells < kDenseUnits) return 0;
+    if (both) return 2;
     return top.rows > 0 && top.rows * kDenseProducts >= uint64_t(nnz) ? 1 : 0;
 }
 

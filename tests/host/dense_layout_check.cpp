@@ -62,6 +62,17 @@ int main() {
         dense_kinds(no, few, int64_t(kDenseTotal / 2) + 1, 8192) || dense_kinds(no, few, 1000, kDenseMaxRows + 1) ||
         dense_kinds({1, 1 << 17, 1 << 17}, few, 1000, 8193))
         return 1;
+    // of fewer than eight cells, not a few rows: their units, of either kind, fill the device
+    for (int64_t m : {int64_t(100), int64_t(8192), int64_t(8193), int64_t(7 * 8192), int64_t(7 * 8192 + 1)}) {
+        const uint64_t least = m > 7 * 8192 ? 1 : (512 + dense_cells(m) - 1) / dense_cells(m);
+        for (uint64_t r : {least - 1, least}) {
+            if (r == 0) continue;
+            const uint64_t p = r << 17;
+            if (dense_kinds({r, r, p}, no, 1000, m) != int(r >= least) ||
+                dense_kinds({r - r / 2, r - r / 2, p}, {r / 2, r / 2, kDenseTotal}, 1000, m) != 2 * int(r >= least))
+                return 1;
+        }
+    }
     // a row of kDenseProducts products in any case, a shorter one that fills its cells
     if (!dense_row(kDenseProducts, kDenseProducts, 512) || dense_row(kDenseFew - 1, 1, 1) ||
         !dense_row(kDenseFew, kDenseFew / kDenseFill, 1) || dense_row(kDenseFew, kDenseFew / kDenseFill + 1, 1) ||
