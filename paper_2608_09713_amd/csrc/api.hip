@@ -277,7 +277,10 @@ struct Ctl {
     unsigned long long chunk_counter;
     unsigned long long maxlen;  // largest row length of the left operand
     unsigned long long dense[6];  // rows that may go by cells, their entries and products, of dense_row's two kinds
+    int64_t pad[1];
 };
+// (a fill of another size takes two launches: 4 us of every call)
+static_assert(sizeof(Ctl) % 16 == 0, "one fill clears the control block");
 // with the first radix pass's digits of few entries (FirstHist::total)
 struct DigitCtl {
     Ctl c;
