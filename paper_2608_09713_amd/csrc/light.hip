@@ -15,7 +15,7 @@
 //
 // The symbolic pass writes the row lengths; the numeric pass repeats the same
 // steps and writes columns and values at the scanned row offsets.  Rows whose
-// products or entries exceed the LDS budget are handed to the dense-tile path.
+// products or entries exceed the LDS budget are handed to the heavy-row kernel.
 #include "common.h"
 #include "internal.h"
 #include "lookup.h"

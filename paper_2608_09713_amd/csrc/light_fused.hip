@@ -22,7 +22,7 @@
 // A scan of the exact lengths gives the row pointers and a streaming copy
 // moves the rows into place, so no row waits for the lengths of earlier
 // rows.  Rows with too many entries or products ("heavy") are left to the
-// dense-tile kernel.
+// heavy-row kernels.
 #include <type_traits>
 
 #include "common.h"
