@@ -34,6 +34,7 @@ namespace {
 constexpr int kHB = kHeavySmall;         // threads per workgroup
 constexpr int kHW = kHB / kWave;         // wavefronts per workgroup
 constexpr uint32_t kNoRow = 0xffffffffu;  // (rows are below 2^31)
+constexpr uint32_t kOwnMost = 64;        // products of a stretch that its wavefront walks by itself, at most
 constexpr int kHeavyGroups = 1024;       // workgroups of a heavy-row launch
 
 // Output columns per window and ranks per value tile: the symbolic pass
@@ -145,6 +146,11 @@ void heavy_kernel(HeavyArgs a, int* queue) {
     constexpr int kWords = HeavyCfg<SR, NUM>::kWords;
     constexpr int kHU = HeavyCfg<SR, NUM>::kHU;
     constexpr bool kVal = (SR == kF64 || SR == kF32);
+    // Batches of short stretches by their own wavefronts (long rows; counts of
+    // eight rows of 2^18 entries, whole call: 11.4 ms shared out, 10.0 so; 200
+    // rows of 16,384 0.99 and 0.87).  Not where values are added: the second
+    // walk in that kernel costs R-MAT scale 17 in f32 5.7 -> 6.6 ms.
+    constexpr bool kOwn = !(NUM && kVal);
     constexpr int kTiles = (kWin + kAcc - 1) / kAcc;  // value tiles of a window, at most
 
     __shared__ __align__(16) uint32_t bits[kWords];
@@ -207,6 +213,18 @@ void heavy_kernel(HeavyArgs a, int* queue) {
         // 500,000 entries of one partner, 2^20 columns: 511 ms, 94 so.)
         const bool small = E <= kHB;
         uint32_t start = 0;  // (small rows) the stretch's start
+        // The products of a batch of stretches.  Those of a long row, where all
+        // are short, by their own wavefronts: a batch is too little work for
+        // the barriers of sharing it out.  (The vote's barrier also orders what
+        // was cleared before.)
+        auto walk = [&](uint32_t l, uint32_t h, In v, auto use) {
+            if constexpr (kOwn)
+                if (!small && !__syncthreads_or(int(h - l > kOwnMost))) {
+                    S.own_products(l, h, v, use);
+                    return;
+                }
+            S.products(l, h, v, use);
+        };
 
         // (two passes) partner runs
         if constexpr (!NUM) {
@@ -297,7 +315,7 @@ void heavy_kernel(HeavyArgs a, int* queue) {
 #pragma unroll 1
                 for (int u = 0; u < 2 && c0 + u * kHB < e1; ++u) {
                     const uint32_t l = u ? lo[1] : lo[0], h = u ? hi[1] : hi[0];
-                    S.products(l, h, In(0), mark);
+                    walk(l, h, In(0), mark);
                     if (NUM && !small) {  // the stretches that are not empty, listed (a wavefront's in a row)
                         const uint64_t some = __ballot(l < h);
                         int at = 0;
@@ -308,6 +326,8 @@ void heavy_kernel(HeavyArgs a, int* queue) {
                     }
                 }
             }
+
+            if (kOwn && !small) __syncthreads();  // (marks made without barriers)
 
             // ranks: every thread owns a contiguous stretch of words
             constexpr int kPer = (kWords + kHB - 1) / kHB;
@@ -414,8 +434,9 @@ void heavy_kernel(HeavyArgs a, int* queue) {
                                 hi = to[0];
                             }
                         }
-                        S.products(lo, hi, val, add);
+                        walk(lo, hi, val, add);
                     }
+                    if (kOwn && !small) __syncthreads();  // (sums made without barriers)
                     for (uint32_t x = tid; x < tl; x += kHB) {
                         const int64_t p = outp + T0 + x;
                         SPSYRK_CHECK(p < a.c_rp[i + 1], kDbgHeavyOut);

@@ -96,52 +96,84 @@ struct Stretches {
             for (uint32_t x = 0; x < n; x += kWave)
                 cur += uint32_t(__popcll(__ballot(x + lane < n && off[min(x + lane, n)] <= ts)));
             cur = uniform(cur - 1);
-            uint8_t* mk = mark[w];
-            const uint64_t upto = (uint64_t(2) << lane) - 1;
-            for (uint32_t t = ts; t < te; t += kPiece) {
-                // stretches that begin after product t, in this piece (marked)
-                // or right behind it (then the next piece's first)
-                if (4 * lane < kPiece) reinterpret_cast<uint32_t*>(mk)[lane] = 0;
-                wave_fence();
-                uint32_t begun = 0;
-                for (uint32_t x = 1; x <= uint32_t(kPiece); x += kWave) {
-                    const uint32_t s = cur + x + lane;
-                    const uint32_t d = s < n ? off[s] - t : ~0u;
-                    if (d < uint32_t(kPiece)) mk[d] = uint8_t(x + lane);
-                    const uint32_t c = uint32_t(__popcll(__ballot(d <= uint32_t(kPiece))));
-                    begun += c;
-                    if (c < uint32_t(kWave)) break;
-                }
-                wave_fence();
-                uint32_t p[KU];
-                In a[KU];
-                if (begun == 0) {  // one stretch holds the whole piece
-                    const uint32_t base = pos[cur] + t + lane;
-                    const In v = VAL ? val[VAL ? cur : 0] : In(0);
-#pragma unroll
-                    for (int u = 0; u < KU; ++u) {
-                        p[u] = base + uint32_t(u * kWave);
-                        a[u] = v;
-                    }
-                } else {
-                    uint32_t carry = 0;
-#pragma unroll
-                    for (int u = 0; u < KU; ++u) {
-                        const uint32_t m = mk[u * kWave + lane];
-                        const uint64_t has = __ballot(m != 0), below = has & upto;
-                        const uint32_t mine = uint32_t(__shfl(int(m), 63 - __clzll((long long)below), kWave));
-                        const uint32_t s = cur + (below ? mine : carry);
-                        if (has) carry = uint32_t(__builtin_amdgcn_readlane(int(m), 63 - __clzll((long long)has)));
-                        p[u] = pos[s] + t + uint32_t(u * kWave) + lane;
-                        a[u] = In(0);
-                        if constexpr (VAL) a[u] = val[s];
-                    }
-                }
-                use(t, te, p, a);
-                cur += begun;
-            }
+            pieces(lane, w, n, ts, te, cur, use);
         }
         __syncthreads();
+    }
+
+    // The same by every wavefront for its own 64 stretches, with no barrier:
+    // for batches of short stretches, too few products to share out over the
+    // workgroup.  (Barriers order it before and after products.)
+    template <typename F>
+    __device__ void own_products(uint32_t lo, uint32_t hi, In v, F use) {
+        int lane = lane_id();
+        asm volatile("" : "+v"(lane));
+        const uint32_t w = uniform(threadIdx.x / kWave);
+        const uint32_t len = hi - lo;
+        const uint64_t some = __ballot(len != 0);
+        if (some == 0) return;
+        const uint32_t inc = wsort::inclusive_sum(len);
+        if (len) {
+            const uint32_t at = w * kWave + uint32_t(__popcll(some & ((uint64_t(1) << lane) - 1)));
+            off[at] = inc - len;
+            pos[at] = lo - (inc - len);
+            if constexpr (VAL) val[at] = v;
+        }
+        wave_fence();
+        pieces(lane, w, w * kWave + uint32_t(__popcll(some)), 0u, uint32_t(__builtin_amdgcn_readlane(int(inc), kWave - 1)),
+               w * kWave, use);
+        wave_fence();
+    }
+
+  private:
+    // Products [ts, te) by wavefront w; product ts lies in stretch cur, the
+    // stretches end at n.
+    template <typename F>
+    __device__ void pieces(int lane, uint32_t w, uint32_t n, uint32_t ts, uint32_t te, uint32_t cur, F use) {
+                    uint8_t* mk = mark[w];
+                    const uint64_t upto = (uint64_t(2) << lane) - 1;
+                    for (uint32_t t = ts; t < te; t += kPiece) {
+                        // stretches that begin after product t, in this piece (marked)
+                        // or right behind it (then the next piece's first)
+                        if (4 * lane < kPiece) reinterpret_cast<uint32_t*>(mk)[lane] = 0;
+                        wave_fence();
+                        uint32_t begun = 0;
+                        for (uint32_t x = 1; x <= uint32_t(kPiece); x += kWave) {
+                            const uint32_t s = cur + x + lane;
+                            const uint32_t d = s < n ? off[s] - t : ~0u;
+                            if (d < uint32_t(kPiece)) mk[d] = uint8_t(x + lane);
+                            const uint32_t c = uint32_t(__popcll(__ballot(d <= uint32_t(kPiece))));
+                            begun += c;
+                            if (c < uint32_t(kWave)) break;
+                        }
+                        wave_fence();
+                        uint32_t p[KU];
+                        In a[KU];
+                        if (begun == 0) {  // one stretch holds the whole piece
+                            const uint32_t base = pos[cur] + t + lane;
+                            const In v = VAL ? val[VAL ? cur : 0] : In(0);
+        #pragma unroll
+                            for (int u = 0; u < KU; ++u) {
+                                p[u] = base + uint32_t(u * kWave);
+                                a[u] = v;
+                            }
+                        } else {
+                            uint32_t carry = 0;
+        #pragma unroll
+                            for (int u = 0; u < KU; ++u) {
+                                const uint32_t m = mk[u * kWave + lane];
+                                const uint64_t has = __ballot(m != 0), below = has & upto;
+                                const uint32_t mine = uint32_t(__shfl(int(m), 63 - __clzll((long long)below), kWave));
+                                const uint32_t s = cur + (below ? mine : carry);
+                                if (has) carry = uint32_t(__builtin_amdgcn_readlane(int(m), 63 - __clzll((long long)has)));
+                                p[u] = pos[s] + t + uint32_t(u * kWave) + lane;
+                                a[u] = In(0);
+                                if constexpr (VAL) a[u] = val[s];
+                            }
+                        }
+                        use(t, te, p, a);
+                        cur += begun;
+                    }
     }
 };
 

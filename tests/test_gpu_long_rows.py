@@ -74,3 +74,36 @@ def test_long_rows(semiring, m, dense, monkeypatch):
     monkeypatch.setenv("SPSYRK_TWO_PASS", "1")
     compare_rows(sp.offdiag(dA, dA, semiring), off, rows, semiring, "offdiag, two passes")
     compare_rows(sp.lower(dA, semiring), ref, rows, semiring, "lower, two passes")
+
+
+@pytest.mark.parametrize("semiring", ["f64", "count", "jaccard"])
+@pytest.mark.parametrize("lens", [(1, 63, 64), (0, 64, 65), (65, 200)])
+def test_batches_of_short_and_long_stretches(semiring, lens):
+    """Stretches up to 64 products, which wavefronts walk by themselves where a
+    batch of 512 has no longer one, beside batches that do: the first 512
+    entries of every row hold the short ones only, the rest all of them; two
+    windows in the symbolic pass, three in the numeric one."""
+    rng = np.random.default_rng(lens[0])
+    m, rows, cols, c = (1 << 18) + 500, [], [], 0
+    for k, ln in enumerate([600, 1024, 1500]):
+        r = m - 1 - 2 * k
+        for q in range(ln):
+            n = int(rng.choice([x for x in lens if x <= 64] or lens)) if q < 512 else int(rng.choice(lens))
+            # all before one window's end, so that the stretch is not cut
+            part = (int(rng.integers(0, 2)) << 17) + rng.choice(1 << 16, n, replace=False)
+            rows += list(part) + [r]
+            cols += [c] * (n + 1)
+            c += 1
+    rows, cols = np.array(rows, dtype=np.int64), np.array(cols, dtype=np.int64)
+    key = np.unique(rows * c + cols)
+    rp = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(np.bincount(key // c, minlength=m), out=rp[1:])
+    A = CSR(m, c, rp, (key % c).astype(np.int32), rng.standard_normal(len(key)))
+    A = A.with_values(None if VDT[semiring] is None else A.values)
+    dA = sp.DeviceCSR.from_host(A, "cuda:0")
+    print(f"[stretches {lens} {semiring}] nnz={A.nnz}", flush=True)
+    rows = np.concatenate([np.arange(0, m, m // 50), [m - 5, m - 3, m - 1]])
+    C = sp.lower(dA, semiring)
+    assert sp.stats()["heavy_rows"] >= 3 and sp.stats()["cell_rows"] == 0
+    compare_rows(C, oracle.lower(A, semiring, rows=rows), rows, semiring, "lower")
+    compare_rows(sp.offdiag(dA, dA, semiring), oracle.offdiag(A, A, semiring, rows=rows), rows, semiring, "offdiag")
